@@ -66,11 +66,13 @@ typedef enum bits_status {
 #define BITS_RMI_MAX_POINTS 2048u /* training points per leaf */
 
 /* Search path selection for a call (bits_launch.path). */
-#define BITS_PATH_AUTO    0u      /* learned index if the reference has one, else plain */
+#define BITS_PATH_AUTO    0u      /* learned index if the reference has one, else the tiered search
+                                     (every call that takes AUTO; the batch plan: else plain) */
 #define BITS_PATH_PLAIN   1u      /* LDS Eytzinger top tree + bisection in HBM */
 #define BITS_PATH_LEARNED 2u      /* learned CDF index + error-window search over the line heads (needs learned ref) */
-#define BITS_PATH_TIERED  3u      /* counting only: LDS top tree, then bisection over the
-                                     32-key node tier (the line heads), then one 128-byte line;
+#define BITS_PATH_TIERED  3u      /* counting only: LDS top tree, then a window of the 32-key node
+                                     tier (the line heads) around the interpolated rank, then one
+                                     128-byte line (small references: one window of keys);
                                      no model (the index the learned path is measured against) */
 
 /* Launch shape of the search kernels.  A NULL bits_launch* means the

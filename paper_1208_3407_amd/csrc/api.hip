@@ -81,20 +81,19 @@ int resolve_launch(const bits_ref* ref, const bits_launch* in, LaunchCfg* out) {
         if (in->depth != 0xFFFFFFFFu) c.depth = in->depth < ref->depth ? in->depth : ref->depth;
         c.grid = in->grid;
     }
+    c.open = !in || (!in->block && !in->qpl);
     const uint32_t path = in ? in->path : BITS_PATH_AUTO;
-    if (path == BITS_PATH_AUTO) c.path = ref->learned ? BITS_PATH_LEARNED : BITS_PATH_PLAIN;
+    if (path == BITS_PATH_AUTO) c.path = ref->learned ? BITS_PATH_LEARNED : BITS_PATH_TIERED;
     else if (path == BITS_PATH_PLAIN || path == BITS_PATH_LEARNED || path == BITS_PATH_TIERED) c.path = path;
     else return BITS_E_ARG;
     if (c.path == BITS_PATH_LEARNED && !ref->learned) return BITS_E_ARG;
     if (c.block != 256 && c.block != 512 && c.block != 1024) return BITS_E_ARG;
     if (c.qpl != 1 && c.qpl != 2 && c.qpl != 4) return BITS_E_ARG;
-    // the per-wave scratch of the learned and tiered paths grows with qpl: step
-    // the block down until one workgroup's LDS fits the device
-    while (c.path != BITS_PATH_PLAIN && c.block > 256 &&
-           count_lds_bytes(c.path, c.depth, (int)c.qpl, c.block) + 1024 > device_lds_per_block())
+    // the per-wave scratch of the learned path grows with qpl: step the block down
+    // until one workgroup's LDS fits the device
+    while (c.path == BITS_PATH_LEARNED && c.block > 256 &&
+           search_lds_bytes(true, c.depth, (int)c.qpl, c.block) + 1024 > device_lds_per_block())
         c.block >>= 1;
-    if (c.path == BITS_PATH_TIERED && count_lds_bytes(c.path, c.depth, (int)c.qpl, c.block) > device_lds_per_block())
-        return BITS_E_ARG;
     *out = c;
     return BITS_OK;
 }
@@ -393,7 +392,7 @@ int mc_pvalue_impl(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
     LaunchCfg cfg;
     rc = resolve_launch(ref, launch, &cfg);
     if (rc != BITS_OK) return rc;
-    if (cfg.path == BITS_PATH_TIERED) return BITS_E_ARG;   // a counting-only path
+    if (launch && launch->path == BITS_PATH_TIERED) return BITS_E_ARG;   // a counting-only path
     hipStream_t s = (hipStream_t)stream;
     auto* totals = (unsigned long long*)d_totals;
     auto* obs = (unsigned long long*)d_observed;
@@ -584,7 +583,7 @@ int bits_mc_binned(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
     LaunchCfg cfg;
     rc = resolve_launch(ref, launch, &cfg);
     if (rc != BITS_OK) return rc;
-    if (cfg.path == BITS_PATH_TIERED) return BITS_E_ARG;   // a counting-only path
+    if (launch && launch->path == BITS_PATH_TIERED) return BITS_E_ARG;   // a counting-only path
     hipStream_t s = (hipStream_t)stream;
     auto* totals = (unsigned long long*)d_totals;
     auto* obs = (unsigned long long*)d_observed;
@@ -891,7 +890,7 @@ int bits_decide(const bits_ref* ref, const uint32_t* d_a_start, const uint32_t* 
     LaunchCfg cfg;
     rc = resolve_launch(ref, launch, &cfg);
     if (rc != BITS_OK) return rc;
-    if (cfg.path == BITS_PATH_TIERED) return BITS_E_ARG;   // a counting-only path
+    if (launch && launch->path == BITS_PATH_TIERED) return BITS_E_ARG;   // a counting-only path
     hipStream_t s = (hipStream_t)stream;
     BITS_CHECK_HIP(launch_fill_u32(d_found, 1, 0u, s));
     BITS_CHECK_HIP(launch_fill_u64((unsigned long long*)d_witness, 1, ~0ull, s));

@@ -112,27 +112,35 @@ __host__ __device__ constexpr size_t search_lds_bytes(bool learned, uint32_t dep
     return learned ? (size_t)(block / kWave) * probe_scratch_words(qpl) * 4u : (size_t)tree_lds_words(depth) * 4u;
 }
 
-// Line-probe scratch of the tiered search per wave: (start, x) of 64 owners
-// and 64 counts (2 * 64 words each) per chain, 2 * QPL chains.
-__host__ __device__ constexpr uint32_t tiered_scratch_words(int qpl) { return 4u * 2u * (uint32_t)qpl * kWave; }
-
-// Counting kernel modes (k_count) and their dynamic LDS: the tiered search
-// stages the top trees and, after them, its per-wave probe scratch.
-enum : int { kModePlain = 0, kModeLearned = 1, kModeTiered = 2 };
-__host__ __device__ constexpr size_t count_lds_bytes(uint32_t path, uint32_t depth, int qpl, uint32_t block) {
-    return path == BITS_PATH_TIERED
-               ? ((size_t)tree_lds_words(depth) + (size_t)(block / kWave) * tiered_scratch_words(qpl)) * 4u
-               : search_lds_bytes(path == BITS_PATH_LEARNED, depth, qpl, block);
-}
+// Forms of the search kernels.  The path without a model (BITS_PATH_TIERED,
+// and AUTO on a reference without one) takes kModeDirect up to kDirectKeys
+// keys and kModeTiered above: a window of keys covers the whole bucket of a
+// small reference (1e6 queries against 3e5: 63 against 71 us through the line
+// heads), but misses as buckets grow (against 1e6: 88 and 86 us, against 2e6:
+// 335 and 144 us).
+enum : int { kModePlain = 0, kModeLearned = 1, kModeTiered = 2, kModeDirect = 3 };
+constexpr uint32_t kDirectKeys = 1u << 19;
 
 // Copy the first 2^d - 1 nodes of both trees into LDS: lds[0..2^d) starts,
 // lds[2^d..2^(d+1)) ends, 1-based BFS order (slot 0 unused).
 __device__ __forceinline__ void stage_tree(uint32_t* lds, const uint32_t* tree, uint32_t stride, uint32_t d) {
     if (!d) return;
     const uint32_t m = 1u << d;
-    for (uint32_t k = threadIdx.x; k < m; k += blockDim.x) {
-        lds[k] = tree[k];
-        lds[m + k] = tree[stride + k];
+    if (d < 2) {
+        for (uint32_t k = threadIdx.x; k < m; k += blockDim.x) {
+            lds[k] = tree[k];
+            lds[m + k] = tree[stride + k];
+        }
+        return;
+    }
+    // 16 bytes a load (the trees are 256-byte aligned; m and stride are multiples of 4)
+    const uint4* T0 = reinterpret_cast<const uint4*>(tree);
+    const uint4* T1 = reinterpret_cast<const uint4*>(tree + stride);
+    uint4* L = reinterpret_cast<uint4*>(lds);
+    for (uint32_t k = threadIdx.x; k < m / 4; k += blockDim.x) {
+        const uint4 a = T0[k], b = T1[k];
+        L[k] = a;
+        L[m / 4 + k] = b;
     }
 }
 
@@ -184,6 +192,7 @@ __device__ __forceinline__ int32_t rmi_pred_offset(const float* p, uint32_t cnt,
 
 struct LaunchCfg {
     uint32_t block, qpl, depth, grid, path;
+    bool open = false;   // block and qpl were left to the library
 };
 
 int device_cu_count();

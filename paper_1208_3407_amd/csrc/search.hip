@@ -1,5 +1,6 @@
 // Search kernels of libbits.so (gfx950): ICount (Algorithm 1) over the plain
-// index (LDS Eytzinger top tree + bisection of the bucket in HBM) or the
+// index (LDS Eytzinger top tree + bisection of the bucket in HBM), the same
+// tree with interpolated windows of line heads or keys, or the
 // learned CDF index (route -> leaf model -> one cooperative 128-byte line
 // probe at the predicted rank -> bisection of what is left of the error
 // window -> verification), the per-query / total counters (Algorithm 2),
@@ -187,6 +188,118 @@ __device__ __forceinline__ void probe_lines(const uint32_t* __restrict__ ks, con
 #pragma unroll
     for (int c = 0; c < NC; ++c) cnt[c] = scr[(2 * c + 1) * 2 * kWave + lane];
     wave_lds_sync();
+}
+
+// ------------------------------------------------------------------ quad probe
+// Windows of a sorted array counted by the four lanes of a quad, in
+// registers only: in pass j the quad serves its lane j, whose window start
+// and key the other three read with a quad_perm broadcast.  Each lane takes
+// 16 bytes per 64-byte half window, so one load instruction covers 64
+// contiguous bytes per quad, and two DPP additions leave the count in the
+// owner.  No LDS is touched, so the LDS holds only the top trees.
+template <int J>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
+    int r = __builtin_amdgcn_update_dpp(0, (int)v, J * 0x55, 0xF, 0xF, true);
+    asm volatile("" : "+v"(r));   // kept a move of its own, not folded into its use
+    return (uint32_t)r;
+}
+
+// The 16-byte pieces of the windows of the quad's lane J.
+template <int J, int LOADS, bool NT>
+__device__ __forceinline__ void quad_load(const uint32_t* __restrict__ K, uint32_t start, u32x4 (&v)[LOADS]) {
+    const u32x4* P = reinterpret_cast<const u32x4*>(K + quad_bcast<J>(start)) + (threadIdx.x & 3u);
+#pragma unroll
+    for (int k = 0; k < LOADS; ++k) {
+        if constexpr (NT)
+            v[k] = __builtin_nontemporal_load(P + 4 * k);
+        else
+            v[k] = P[4 * k];
+    }
+}
+
+template <int J, int LOADS>
+__device__ __forceinline__ void quad_sum(const u32x4 (&v)[LOADS], uint32_t x, uint32_t& res) {
+    const uint32_t xx = quad_bcast<J>(x);
+    uint32_t t = 0;
+#pragma unroll
+    for (int k = 0; k < LOADS; ++k) t += count_lt4(v[k], xx);
+    t = group_sum<4>(t);
+    if ((threadIdx.x & 3u) == (uint32_t)J) res = t;
+}
+
+// cnt[c] = #{i in [start[c], start[c] + WIN) : K_c[i] < x[c]}, start a
+// multiple of 4 with the whole window inside K_c; all 64 lanes call it, an
+// idle chain passes any start in bounds.  The loads of all chains are issued
+// before the first count.
+template <int NC, int WIN, bool NT>
+__device__ __forceinline__ void quad_windows(const uint32_t* __restrict__ ks, const uint32_t* __restrict__ ke,
+                                             const uint32_t (&start)[NC], const uint32_t (&x)[NC],
+                                             uint32_t (&cnt)[NC]) {
+    constexpr int kLoads = WIN / 16;
+    static_assert(WIN % 16 == 0, "window geometry");
+    u32x4 v[NC][4][kLoads];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const uint32_t* K = (c & 1) ? ke : ks;
+        quad_load<0, kLoads, NT>(K, start[c], v[c][0]);
+        quad_load<1, kLoads, NT>(K, start[c], v[c][1]);
+        quad_load<2, kLoads, NT>(K, start[c], v[c][2]);
+        quad_load<3, kLoads, NT>(K, start[c], v[c][3]);
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        uint32_t r = 0;
+        quad_sum<0, kLoads>(v[c][0], x[c], r);
+        quad_sum<1, kLoads>(v[c][1], x[c], r);
+        quad_sum<2, kLoads>(v[c][2], x[c], r);
+        quad_sum<3, kLoads>(v[c][3], x[c], r);
+        cnt[c] = r;
+    }
+}
+
+// Lower bounds by windows: on entry r_c = #{K_c < x[c]} lies in
+// [lo[c], hi[c]] and near g[c]; on return lo[c] = r_c.  The first window sits
+// around the guess, the second next to it on the side its count points to,
+// later ones around the middle of what is left, so a bad guess costs speed
+// only.  K_c is readable (and 0xFFFFFFFF past its keys) up to `lim`, a
+// multiple of 4 and at least WIN.  All 64 lanes call it.
+template <int NC, int WIN, bool NT>
+__device__ __forceinline__ void window_search(const uint32_t* __restrict__ ks, const uint32_t* __restrict__ ke,
+                                              uint32_t lim, uint32_t (&lo)[NC], uint32_t (&hi)[NC],
+                                              const uint32_t (&g)[NC], const uint32_t (&x)[NC]) {
+    uint32_t w[NC], cnt[NC];
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        // a range that one window covers needs no guess
+        const uint32_t near = (g[c] > WIN / 2 ? g[c] - WIN / 2 : 0u) & ~3u;
+        w[c] = min(hi[c] - lo[c] <= WIN - 4 ? lo[c] & ~3u : near, lim - WIN);
+        any |= lo[c] < hi[c];
+    }
+    for (uint32_t step = 0; __ballot(any); ++step) {
+        quad_windows<NC, WIN, NT>(ks, ke, w, x, cnt);
+        any = false;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (lo[c] >= hi[c]) continue;
+            const uint32_t r = w[c] + cnt[c];   // keys before the window are below x unless cnt is 0
+            const bool left = cnt[c] == 0u, right = cnt[c] == (uint32_t)WIN;
+            const uint32_t at = min(max(r, lo[c]), hi[c]);
+            if (!left) lo[c] = at;
+            if (!right) hi[c] = at;
+            if (lo[c] >= hi[c]) continue;
+            any = true;
+            const uint32_t half = (hi[c] - lo[c]) / 2;
+            uint32_t s = lo[c];                                  // covers the range, or its left end
+            if (hi[c] - lo[c] > WIN - 4) {
+                if (step)
+                    s += half > WIN / 2 ? half - WIN / 2 : 0u;   // around the middle
+                else if (left)
+                    s = hi[c] - (WIN - 4);                       // up to the right end
+            }
+            w[c] = min(s & ~3u, lim - WIN);
+        }
+    }
 }
 
 // ------------------------------------------------------------------ leaf model
@@ -585,56 +698,96 @@ __device__ __forceinline__ void icount_heads(const SearchArgs& sa, uint32_t* scr
     }
 }
 
-// Plain search with the 32-key node tier, no model: the line heads
-// H[j] = K[32 j] (1/32 of the array, cached in L2 / the Infinity Cache) sit
-// between the LDS top tree and the sorted array.  The tree narrows the lower
-// bound r = #{K < x} to its bucket [base, base + len]; then
-// j = #{H < x} = ceil(r / 32) lies in [ceil(base / 32), ceil((base + len) / 32)]
-// (every head before that range is < x, every head after it >= x), which is
-// bisected over the heads; one cooperative probe of line j - 1 then gives r
-// (r = 0 when j = 0), as in the head search of the Monte-Carlo path.  `scr`
-// is this wave's probe scratch (tiered_scratch_words(QPL) words).  Must be
-// called by all 64 lanes.
-template <int QPL>
-__device__ __forceinline__ void icount_tiered(const SearchArgs& sa, const uint32_t* lds, uint32_t* scr,
-                                              const uint32_t (&as)[QPL], const uint32_t (&ae)[QPL],
-                                              uint32_t (&cnt)[QPL], uint32_t (&fst)[QPL]) {
-    constexpr int NC = 2 * QPL;
-    uint32_t x[NC], base[NC], len[NC];
-#pragma unroll
-    for (int q = 0; q < QPL; ++q) {
-        x[2 * q] = ae[q] + 1u;
-        x[2 * q + 1] = as[q];
-    }
-    tree_bucket<NC>(sa, lds, x, base, len);
-    uint32_t j[NC], jl[NC];
+// Search without a model.  The LDS top tree narrows the lower bound
+// r = #{K < x} to its bucket [base, base + len] and, on the way down, leaves
+// the bucket's bounding keys; keys are dense enough inside a bucket that a
+// straight line between them predicts r to a few keys (about sqrt(len)).
+//   n <= kDirectKeys   a window of 32 keys around the prediction gives r; a
+//                      bucket of at most 28 keys is covered whole.
+//   larger n           j = #{H < x} = ceil(r / 32) over the line heads
+//                      H[j] = K[32 j] (1/32 of the array, kept in L2 / the
+//                      Infinity Cache) by a window of 16 heads around the
+//                      predicted line, then one window over line j - 1
+//                      (r = 0 when j = 0): one data line per search.
+// Exact whatever the prediction (window_search).  All 64 lanes call it.
+// Bound by random reads: one 64-byte window of heads (L2) and one data line
+// per search.  1e7 queries against 1e7 (half clustered): 0.79 ms, against
+// 3.85 ms for the bisection of the bucket in HBM and about 0.35 ms for the
+// data lines alone; 5e7 against 5e7: 6.5 against 18.5 ms.  A whole bisection
+// of the heads costs one L2 request per step where the window costs one.
+template <int NC, bool DIRECT>
+__device__ __forceinline__ void rank_tiered(const SearchArgs& sa, const uint32_t* lds, const uint32_t (&x)[NC],
+                                            uint32_t (&r)[NC]) {
+    const uint32_t d = sa.depth, n = sa.n, m = 1u << d;
+    uint32_t k[NC], klo[NC], khi[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        j[c] = (uint32_t)(((uint64_t)base[c] + 31u) >> 5);
-        jl[c] = (uint32_t)(((uint64_t)base[c] + len[c] + 31u) >> 5) - j[c];
+        const uint32_t* K = (c & 1) ? sa.be : sa.bs;
+        k[c] = 1u;
+        klo[c] = K[0];
+        khi[c] = K[n - 1];
     }
-    bisect_multi<NC>(sa.hs, sa.he, j, jl, x, 32u);
-    uint32_t dw[NC], pc[NC];
+    for (uint32_t l = 0; l < d; ++l) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) dw[c] = j[c] ? (j[c] - 1u) * 32u : kNoLine;
-    probe_lines<NC, true>(sa.bs, sa.be, dw, x, pc, scr);
+        for (int c = 0; c < NC; ++c) {
+            const uint32_t v = lds[(c & 1) * m + k[c]];
+            const bool right = v < x[c];
+            klo[c] = right ? v : klo[c];
+            khi[c] = right ? khi[c] : v;
+            k[c] = 2u * k[c] + (right ? 1u : 0u);
+        }
+    }
+    uint32_t lo[NC], hi[NC], g[NC];
 #pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const uint64_t qb = k[c] - m;
+        const uint32_t base = (uint32_t)((qb * n) >> d), len = (uint32_t)(((qb + 1) * n) >> d) - base;
+        const float f = x[c] > klo[c] ? (float)(x[c] - klo[c]) * __builtin_amdgcn_rcpf((float)(khi[c] - klo[c])) : 0.0f;
+        const uint32_t pos = base + (uint32_t)(fminf(f, 1.0f) * (float)len);   // equal bounding keys give f = inf
+        lo[c] = DIRECT ? base : (uint32_t)(((uint64_t)base + 31u) >> 5);
+        hi[c] = DIRECT ? base + len : (uint32_t)(((uint64_t)base + len + 31u) >> 5);
+        g[c] = DIRECT ? pos : (uint32_t)(((uint64_t)pos + 31u) >> 5);
+    }
+    if constexpr (DIRECT) {
+        window_search<NC, 32, false>(sa.bs, sa.be, (n + 31u) & ~31u, lo, hi, g, x);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) r[c] = lo[c];
+    } else {
+        window_search<NC, 16, false>(sa.hs, sa.he, (uint32_t)heads_len(n), lo, hi, g, x);
+        uint32_t w[NC], pc[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) w[c] = lo[c] ? (lo[c] - 1u) * 32u : 0u;
+        quad_windows<NC, 32, true>(sa.bs, sa.be, w, x, pc);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) r[c] = lo[c] ? w[c] + pc[c] : 0u;
+    }
+}
+
+// One query (two chains) at a time: the windows of more would not fit the registers.
+template <int QPL, bool DIRECT>
+__device__ __forceinline__ void icount_tiered(const SearchArgs& sa, const uint32_t* lds, const uint32_t (&as)[QPL],
+                                              const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL],
+                                              uint32_t (&fst)[QPL]) {
+#pragma unroll 1
     for (int q = 0; q < QPL; ++q) {
-        const uint32_t rs = dw[2 * q] == kNoLine ? 0u : dw[2 * q] + pc[2 * q];
-        const uint32_t re = dw[2 * q + 1] == kNoLine ? 0u : dw[2 * q + 1] + pc[2 * q + 1];
-        const uint32_t first = (ae[q] == 0xFFFFFFFFu) ? sa.n : rs;
-        cnt[q] = first - re;
+        const uint32_t x[2] = {ae[q] + 1u, as[q]};
+        uint32_t r[2];
+        rank_tiered<2, DIRECT>(sa, lds, x, r);
+        const uint32_t first = (ae[q] == 0xFFFFFFFFu) ? sa.n : r[0];
+        cnt[q] = first - r[1];
         fst[q] = first;
     }
 }
 
-template <int QPL, bool LEARNED>
+template <int QPL, int MODE>
 __device__ __forceinline__ void icount(const SearchArgs& sa, uint32_t* lds, const uint32_t (&as)[QPL],
                                        const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL], uint32_t (&fst)[QPL]) {
-    if constexpr (LEARNED)
+    if constexpr (MODE == kModeLearned)
         icount_learned<QPL>(sa, lds + (threadIdx.x / kWave) * probe_scratch_words(QPL), as, ae, cnt, fst);
-    else
+    else if constexpr (MODE == kModePlain)
         icount_plain<QPL>(sa, lds, as, ae, cnt, fst);
+    else
+        icount_tiered<QPL, MODE == kModeDirect>(sa, lds, as, ae, cnt, fst);
 }
 
 
@@ -644,13 +797,14 @@ __device__ __forceinline__ void icount(const SearchArgs& sa, uint32_t* lds, cons
 // coalesced.  Totals: uint64 wave sum, one atomic per wave.
 
 // MODE: kModePlain (LDS tree + bisection), kModeLearned (learned index,
-// error-window head probe + one line) or kModeTiered (LDS tree + line-head tier + one line).
+// error-window head probe + one line), kModeTiered (LDS tree + line-head
+// window + one line) or kModeDirect (LDS tree + one window of keys).
 template <int QPL, int MODE>
 BITS_SEARCH_KERNEL k_count(SearchArgs sa, const uint32_t* __restrict__ a_start,
                                                 const uint32_t* __restrict__ a_end, uint64_t na,
                                                 uint32_t* __restrict__ counts, uint32_t* __restrict__ firsts,
                                                 unsigned long long* total) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     if (MODE != kModeLearned) {
         stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
         __syncthreads();
@@ -675,11 +829,7 @@ BITS_SEARCH_KERNEL k_count(SearchArgs sa, const uint32_t* __restrict__ a_start,
             }
         }
         uint32_t fst[QPL];
-        if constexpr (MODE == kModeTiered)
-            icount_tiered<QPL>(sa, lds, lds + tree_lds_words(sa.depth) + (threadIdx.x / kWave) * tiered_scratch_words(QPL),
-                               as, ae, cnt, fst);
-        else
-            icount<QPL, MODE == kModeLearned>(sa, lds, as, ae, cnt, fst);
+        icount<QPL, MODE>(sa, lds, as, ae, cnt, fst);
 #pragma unroll
         for (int q = 0; q < QPL; ++q) {
             const uint64_t i = t * tile + (uint64_t)q * blockDim.x + threadIdx.x;
@@ -702,12 +852,12 @@ BITS_SEARCH_KERNEL k_count(SearchArgs sa, const uint32_t* __restrict__ a_start,
 // and stops once some query has a non-zero count.  *witness receives the
 // smallest index with a hit among the tiles that ran (initialised to
 // 2^64 - 1 by the caller).
-template <int QPL, bool LEARNED>
+template <int QPL, int MODE>
 BITS_SEARCH_KERNEL k_decide(SearchArgs sa, const uint32_t* __restrict__ a_start, const uint32_t* __restrict__ a_end,
                             uint64_t na, uint32_t* found, unsigned long long* witness) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     __shared__ uint32_t stop;
-    if (!LEARNED) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
+    if (MODE != kModeLearned) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
     __syncthreads();
     const uint64_t tile = (uint64_t)blockDim.x * QPL;
     const uint64_t ntiles = (na + tile - 1) / tile;
@@ -730,7 +880,7 @@ BITS_SEARCH_KERNEL k_decide(SearchArgs sa, const uint32_t* __restrict__ a_start,
                 ae[q] = as[q];
             }
         }
-        icount<QPL, LEARNED>(sa, lds, as, ae, cnt, fst);
+        icount<QPL, MODE>(sa, lds, as, ae, cnt, fst);
         bool hit = false;
 #pragma unroll
         for (int q = 0; q < QPL; ++q) {
@@ -767,24 +917,24 @@ BITS_SEARCH_KERNEL k_decide(SearchArgs sa, const uint32_t* __restrict__ a_start,
 constexpr uint32_t kMaxChunk = 64;
 constexpr uint32_t kXcds = 8;
 
-template <int QPL, bool LEARNED>
+template <int QPL, int MODE>
 __device__ __forceinline__ void icount_mc(const SearchArgs& sa, uint32_t* lds, const uint32_t (&as)[QPL],
                                           const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL]) {
     uint32_t fst[QPL];
-    if constexpr (LEARNED)
+    if constexpr (MODE == kModeLearned)
         icount_heads<QPL>(sa, lds + (threadIdx.x / kWave) * probe_scratch_words(QPL), as, ae, cnt, fst);
     else
-        icount_plain<QPL>(sa, lds, as, ae, cnt, fst);
+        icount<QPL, MODE>(sa, lds, as, ae, cnt, fst);
 }
 
-template <int QPL, bool LEARNED, bool OBSERVED>
+template <int QPL, int MODE, bool OBSERVED>
 BITS_SEARCH_KERNEL k_mc(SearchArgs sa, const uint32_t* __restrict__ a_start, const uint32_t* __restrict__ a_end,
          const uint32_t* __restrict__ off, const uint32_t* __restrict__ span, const uint32_t* __restrict__ len,
          const uint32_t* __restrict__ idx, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf, uint64_t tiles,
          uint32_t chunk, unsigned long long* __restrict__ totals) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     __shared__ unsigned long long acc[kMaxChunk];
-    if (!LEARNED) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
+    if (MODE != kModeLearned) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
     for (uint32_t k = threadIdx.x; k < kMaxChunk; k += blockDim.x) acc[k] = 0ull;
     __syncthreads();
     const uint64_t tile = (uint64_t)blockDim.x * QPL;
@@ -835,7 +985,7 @@ BITS_SEARCH_KERNEL k_mc(SearchArgs sa, const uint32_t* __restrict__ a_start, con
                     ae[q] = valid[q] ? as[q] + ql[q] - 1u : kIdleEnd;
                 }
             }
-            icount_mc<QPL, LEARNED>(sa, lds, as, ae, cnt);
+            icount_mc<QPL, MODE>(sa, lds, as, ae, cnt);
             uint64_t sum = 0;
 #pragma unroll
             for (int q = 0; q < QPL; ++q) sum += valid[q] ? cnt[q] : 0u;
@@ -918,7 +1068,7 @@ BITS_SEARCH_KERNEL k_mc_sorted(SearchArgs sa, const uint32_t* __restrict__ off, 
                                const uint32_t* __restrict__ len, const uint32_t* __restrict__ idx, uint64_t na,
                                uint64_t seed, uint64_t s0, uint64_t nshuf, uint64_t tiles, uint32_t chunk,
                                unsigned long long* __restrict__ totals) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     __shared__ uint32_t hist[kSortBuckets];
     __shared__ uint32_t t_off[kSortMaxTileQ], t_span[kSortMaxTileQ], t_len[kSortMaxTileQ], t_idx[kSortMaxTileQ];
     __shared__ unsigned long long acc[kMaxChunk];
@@ -1277,7 +1427,7 @@ __global__ void __launch_bounds__(1024)
     k_batch(const BatchRef* __restrict__ refs, const BatchQuery* __restrict__ qs, const BatchItem* __restrict__ items,
             const uint32_t* __restrict__ wg_begin, uint32_t n_wg, uint32_t n_ref, uint32_t max_depth,
             unsigned long long* __restrict__ pair_totals, uint32_t* status) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     const uint32_t g = gridDim.x, b = blockIdx.x;
     const uint32_t per_xcd = g / 8u;
     const uint32_t w = (g % 8u == 0u) ? (b % 8u) * per_xcd + b / 8u : b;
@@ -1326,7 +1476,7 @@ __global__ void __launch_bounds__(1024)
         }
         if (sa.n) {   // uniform over the workgroup: every item of the loop is one reference
             uint32_t fst[QPL];
-            icount<QPL, LEARNED>(sa, lds, as, ae, cnt, fst);
+            icount<QPL, LEARNED ? kModeLearned : kModePlain>(sa, lds, as, ae, cnt, fst);
         } else {
 #pragma unroll
             for (int q = 0; q < QPL; ++q) cnt[q] = 0;
@@ -1346,7 +1496,7 @@ __global__ void __launch_bounds__(1024)
 // 1 = B_E): lo = wl, hi = wr, or lo = hi = the resolved rank.
 __global__ void __launch_bounds__(256) k_rmi_window(SearchArgs sa, uint32_t which, const uint32_t* __restrict__ xs,
                                                     uint64_t n, uint32_t* __restrict__ lo, uint32_t* __restrict__ hi) {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     uint32_t* scr = lds + (threadIdx.x / kWave) * probe_scratch_words(1);
     const uint64_t tiles = (n + blockDim.x - 1) / blockDim.x;
     for (uint64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
@@ -1451,11 +1601,18 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s) {
     return hipGetLastError();
 }
 
+// The kernel mode of a launch's path (the tiered path has one form per size).
+static int search_mode(const SearchArgs& sa, const LaunchCfg& cfg) {
+    if (cfg.path == BITS_PATH_LEARNED) return kModeLearned;
+    if (cfg.path == BITS_PATH_TIERED) return sa.n <= kDirectKeys ? kModeDirect : kModeTiered;
+    return kModePlain;
+}
+
 template <int QPL, int MODE>
 static hipError_t launch_count_t(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                                  uint64_t na, uint32_t* counts, uint32_t* firsts, unsigned long long* total,
                                  hipStream_t s) {
-    const size_t lds = count_lds_bytes(cfg.path, sa.depth, QPL, cfg.block);
+    const size_t lds = search_lds_bytes(MODE == kModeLearned, sa.depth, QPL, cfg.block);
     const uint64_t tile = (uint64_t)cfg.block * QPL;
     const void* kern = (const void*)k_count<QPL, MODE>;
     const uint32_t grid = persistent_grid(kern, cfg, lds, (na + tile - 1) / tile);
@@ -1468,19 +1625,34 @@ template <int QPL>
 static hipError_t launch_count_q(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                                  uint64_t na, uint32_t* counts, uint32_t* firsts, unsigned long long* total,
                                  hipStream_t s) {
-    switch (cfg.path) {
-        case BITS_PATH_LEARNED:
+    switch (search_mode(sa, cfg)) {
+        case kModeLearned:
             return launch_count_t<QPL, kModeLearned>(sa, cfg, as, ae, na, counts, firsts, total, s);
-        case BITS_PATH_TIERED:
+        case kModeTiered:
             return launch_count_t<QPL, kModeTiered>(sa, cfg, as, ae, na, counts, firsts, total, s);
+        case kModeDirect:
+            return launch_count_t<QPL, kModeDirect>(sa, cfg, as, ae, na, counts, firsts, total, s);
         default:
             return launch_count_t<QPL, kModePlain>(sa, cfg, as, ae, na, counts, firsts, total, s);
     }
 }
 
-hipError_t launch_count(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
+// The shape of a search without a model when the caller left it open: one
+// query per lane, and the largest workgroup that still gives every CU one
+// (each stages its own copy of the top trees).
+static LaunchCfg open_shape(const LaunchCfg& cfg, uint64_t na) {
+    LaunchCfg c = cfg;
+    if (!c.open || c.path != BITS_PATH_TIERED) return c;
+    const uint64_t cus = (uint64_t)device_cu_count();
+    c.qpl = 1;
+    c.block = na >= 1024 * cus ? 1024u : na >= 512 * cus ? 512u : 256u;
+    return c;
+}
+
+hipError_t launch_count(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t* as, const uint32_t* ae,
                         uint64_t na, uint32_t* counts, unsigned long long* total, hipStream_t s, uint32_t* firsts) {
     if (!na) return hipSuccess;
+    const LaunchCfg cfg = open_shape(cfg0, na);
     switch (cfg.qpl) {
         case 1: return launch_count_q<1>(sa, cfg, as, ae, na, counts, firsts, total, s);
         case 4: return launch_count_q<4>(sa, cfg, as, ae, na, counts, firsts, total, s);
@@ -1520,17 +1692,18 @@ hipError_t launch_mc_prepare(const uint32_t* as, const uint32_t* ae, uint64_t na
     return hipGetLastError();
 }
 
-template <int QPL, bool LEARNED>
+template <int QPL, int MODE>
 static hipError_t launch_mc_t(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                               const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
                               unsigned long long* totals, unsigned long long* observed, hipStream_t s) {
+    constexpr bool LEARNED = MODE == kModeLearned;
     const size_t lds = search_lds_bytes(LEARNED, sa.depth, QPL, cfg.block);
     const uint64_t tile = (uint64_t)cfg.block * QPL;
     const uint64_t tps = (na + tile - 1) / tile;
     if (observed) {
-        const void* ko = (const void*)k_mc<QPL, LEARNED, true>;
+        const void* ko = (const void*)k_mc<QPL, MODE, true>;
         const uint32_t go = persistent_grid(ko, cfg, lds, tps);
-        hipLaunchKernelGGL((k_mc<QPL, LEARNED, true>), dim3(go), dim3(cfg.block), lds, s, sa, as, ae, tab.off,
+        hipLaunchKernelGGL((k_mc<QPL, MODE, true>), dim3(go), dim3(cfg.block), lds, s, sa, as, ae, tab.off,
                            tab.span, tab.len, tab.idx, na, seed, s0, (uint64_t)1, tps, 1u, observed);
     }
     // the sorted kernel when its LDS (dynamic + ~7 KB static) fits the device's per-workgroup limit
@@ -1544,54 +1717,75 @@ static hipError_t launch_mc_t(const SearchArgs& sa, const LaunchCfg& cfg, const 
         hipLaunchKernelGGL(k_mc_sorted, dim3(gm), dim3(cfg.block), lds1, s, sa, tab.off, tab.span, tab.len, tab.idx,
                            na, seed, s0, nshuf, tq, chunk, totals);
     } else if (nshuf) {
-        const void* km = (const void*)k_mc<QPL, LEARNED, false>;
+        const void* km = (const void*)k_mc<QPL, MODE, false>;
         const uint32_t gm = persistent_grid(km, cfg, lds, nshuf * tps);
         // shuffles per work item: as many as keep >= 8 items per workgroup
         uint32_t chunk = kMaxChunk;
         while (chunk > 1 && tps * ((nshuf + chunk - 1) / chunk) < 8ull * gm) chunk >>= 1;
-        hipLaunchKernelGGL((k_mc<QPL, LEARNED, false>), dim3(gm), dim3(cfg.block), lds, s, sa, as, ae, tab.off,
+        hipLaunchKernelGGL((k_mc<QPL, MODE, false>), dim3(gm), dim3(cfg.block), lds, s, sa, as, ae, tab.off,
                            tab.span, tab.len, tab.idx, na, seed, s0, nshuf, tps, chunk, totals);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_mc(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
-                     const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
-                     unsigned long long* totals, unsigned long long* observed, hipStream_t s) {
-    if (!na) return hipSuccess;
-    const bool L = cfg.path == BITS_PATH_LEARNED;
-    switch (cfg.qpl) {
-        case 1: return L ? launch_mc_t<1, true>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s)
-                         : launch_mc_t<1, false>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
-        case 4: return L ? launch_mc_t<4, true>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s)
-                         : launch_mc_t<4, false>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
-        default: return L ? launch_mc_t<2, true>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s)
-                          : launch_mc_t<2, false>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
+template <int QPL>
+static hipError_t launch_mc_q(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
+                              const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
+                              unsigned long long* totals, unsigned long long* observed, hipStream_t s) {
+    switch (search_mode(sa, cfg)) {
+        case kModeLearned:
+            return launch_mc_t<QPL, kModeLearned>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
+        case kModeTiered:
+            return launch_mc_t<QPL, kModeTiered>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
+        case kModeDirect:
+            return launch_mc_t<QPL, kModeDirect>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
+        default:
+            return launch_mc_t<QPL, kModePlain>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
     }
 }
 
-template <int QPL, bool LEARNED>
+hipError_t launch_mc(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t* as, const uint32_t* ae,
+                     const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
+                     unsigned long long* totals, unsigned long long* observed, hipStream_t s) {
+    if (!na) return hipSuccess;
+    const LaunchCfg cfg = open_shape(cfg0, na * (nshuf ? nshuf : 1));
+    switch (cfg.qpl) {
+        case 1: return launch_mc_q<1>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
+        case 4: return launch_mc_q<4>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
+        default: return launch_mc_q<2>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
+    }
+}
+
+template <int QPL, int MODE>
 static hipError_t launch_decide_t(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                                   uint64_t na, uint32_t* found, unsigned long long* witness, hipStream_t s) {
-    const size_t lds = search_lds_bytes(LEARNED, sa.depth, QPL, cfg.block);
+    const size_t lds = search_lds_bytes(MODE == kModeLearned, sa.depth, QPL, cfg.block);
     const uint64_t tile = (uint64_t)cfg.block * QPL;
-    const void* kern = (const void*)k_decide<QPL, LEARNED>;
+    const void* kern = (const void*)k_decide<QPL, MODE>;
     const uint32_t grid = persistent_grid(kern, cfg, lds, (na + tile - 1) / tile);
-    hipLaunchKernelGGL((k_decide<QPL, LEARNED>), dim3(grid), dim3(cfg.block), lds, s, sa, as, ae, na, found, witness);
+    hipLaunchKernelGGL((k_decide<QPL, MODE>), dim3(grid), dim3(cfg.block), lds, s, sa, as, ae, na, found, witness);
     return hipGetLastError();
 }
 
-hipError_t launch_decide(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
+template <int QPL>
+static hipError_t launch_decide_q(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
+                                  uint64_t na, uint32_t* found, unsigned long long* witness, hipStream_t s) {
+    switch (search_mode(sa, cfg)) {
+        case kModeLearned: return launch_decide_t<QPL, kModeLearned>(sa, cfg, as, ae, na, found, witness, s);
+        case kModeTiered: return launch_decide_t<QPL, kModeTiered>(sa, cfg, as, ae, na, found, witness, s);
+        case kModeDirect: return launch_decide_t<QPL, kModeDirect>(sa, cfg, as, ae, na, found, witness, s);
+        default: return launch_decide_t<QPL, kModePlain>(sa, cfg, as, ae, na, found, witness, s);
+    }
+}
+
+hipError_t launch_decide(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t* as, const uint32_t* ae,
                          uint64_t na, uint32_t* found, unsigned long long* witness, hipStream_t s) {
     if (!na) return hipSuccess;
-    const bool L = cfg.path == BITS_PATH_LEARNED;
+    const LaunchCfg cfg = open_shape(cfg0, na);
     switch (cfg.qpl) {
-        case 1: return L ? launch_decide_t<1, true>(sa, cfg, as, ae, na, found, witness, s)
-                         : launch_decide_t<1, false>(sa, cfg, as, ae, na, found, witness, s);
-        case 4: return L ? launch_decide_t<4, true>(sa, cfg, as, ae, na, found, witness, s)
-                         : launch_decide_t<4, false>(sa, cfg, as, ae, na, found, witness, s);
-        default: return L ? launch_decide_t<2, true>(sa, cfg, as, ae, na, found, witness, s)
-                          : launch_decide_t<2, false>(sa, cfg, as, ae, na, found, witness, s);
+        case 1: return launch_decide_q<1>(sa, cfg, as, ae, na, found, witness, s);
+        case 4: return launch_decide_q<4>(sa, cfg, as, ae, na, found, witness, s);
+        default: return launch_decide_q<2>(sa, cfg, as, ae, na, found, witness, s);
     }
 }
 

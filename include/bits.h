@@ -67,7 +67,7 @@ typedef enum bits_status {
 
 /* Search path selection for a call (bits_launch.path). */
 #define BITS_PATH_AUTO    0u      /* learned index if the reference has one, else the tiered search
-                                     (every call that takes AUTO; the batch plan: else plain) */
+                                     (the batch plan: all references learned, else as bits_batch_create says) */
 #define BITS_PATH_PLAIN   1u      /* LDS Eytzinger top tree + bisection in HBM */
 #define BITS_PATH_LEARNED 2u      /* learned CDF index + error-window search over the line heads (needs learned ref) */
 #define BITS_PATH_TIERED  3u      /* counting only: LDS top tree, then a window of the 32-key node
@@ -467,21 +467,34 @@ int bits_enumerate(const void *d_index, uint64_t n, const uint32_t *d_a_start, c
 
 typedef struct bits_batch_plan bits_batch_plan;   /* opaque host object */
 
-/* Workspace bytes for a plan over n_q query sets of sizes na[] (host). */
+/* Workspace bytes for a plan over n_q query sets of sizes na[] (host): the
+ * reference and query tables, and the larger of the work list (16 bytes per
+ * 256 queries and reference) and, from 2^22 queries x references on (up to
+ * 192 sets and 2^26 queries), the sorted form's lists (about 44 bytes per
+ * query plus 1 byte per query and 32 references). */
 int bits_batch_workspace(const uint64_t *na, uint32_t n_q, uint32_t n_ref, size_t *bytes);
 
 /* Builds a plan that computes d_pair_totals[i * n_ref + j] = total count of
- * query set i against reference j for all pairs, as one zero-fill kernel and
- * one persistent kernel captured into a HIP graph.  Work items (pair, tile)
- * are ordered by reference so a workgroup re-stages the LDS top tree only
- * when its reference changes.  Uploads the work list into d_ws (synchronous
- * on `stream`).  refs and the query pointers are host arrays; the device
- * buffers they name must stay valid while the plan is used.
+ * query set i against reference j for all pairs, captured into a HIP graph.
+ * Two forms, the same totals:
+ *   searched  a zero-fill kernel and one persistent kernel.  Work items (pair,
+ *             tile) are ordered by reference so a workgroup re-stages the LDS
+ *             top tree only when its reference changes;
+ *   sorted    each replay sorts the starts and the ends of all query sets
+ *             (a pair's total is a sum over its query keys, in any order) and
+ *             walks both lists once against 64 references at a time.  Taken
+ *             when launch leaves path, block, qpl and grid open, not every
+ *             reference is learned, the sizes make it the faster form, and
+ *             the workspace holds its lists.
+ * Uploads the tables into d_ws (synchronous on `stream`).  refs and the query
+ * pointers are host arrays; the device buffers they name must stay valid
+ * while the plan is used, and every replay reads them anew.
  * launch (nullable): block, qpl, depth, grid and path of the persistent
  * kernel.  path BITS_PATH_LEARNED searches every pair through its
  * reference's learned index (BITS_E_ARG unless every reference is learned);
  * BITS_PATH_AUTO (and launch = NULL) picks it when every reference is
- * learned, else the plain path.  The learned path's fallbacks are counted in
+ * learned, else the search without a model (BITS_PATH_TIERED itself is
+ * refused) or the sorted form.  The learned path's fallbacks are counted in
  * each reference's own counter; interval errors go to refs[0]'s status. */
 int bits_batch_create(const bits_ref *refs, uint32_t n_ref, const uint32_t *const *d_a_start,
                       const uint32_t *const *d_a_end, const uint64_t *na, uint32_t n_q,

@@ -929,6 +929,9 @@ int bits_batch_workspace(const uint64_t* na, uint32_t n_q, uint32_t n_ref, size_
     uint64_t tiles = 0;
     for (uint32_t i = 0; i < n_q; ++i) tiles += (na[i] + 255) / 256;   // smallest tile: 256 x 1
     *bytes = batch_ws(n_ref, n_q, tiles * n_ref, kMaxBatchWg).total;
+    MergeLayout M;
+    if (merge_layout(na, n_q, n_ref, &M))
+        *bytes = std::max(*bytes, batch_ws(n_ref, n_q, 0, 0).total + M.bytes);
     return BITS_OK;
 }
 
@@ -949,7 +952,8 @@ int bits_batch_create(const bits_ref* refs, uint32_t n_ref, const uint32_t* cons
         if (na[i] && (!d_a_start[i] || !d_a_end[i])) return BITS_E_ARG;
         if (na[i] > 0xFFFFFFFFull) return BITS_E_ARG;
     }
-    LaunchCfg cfg{1024u, 2u, max_depth, 0u, all_learned ? BITS_PATH_LEARNED : BITS_PATH_PLAIN};
+    LaunchCfg cfg{1024u, 2u, max_depth, 0u, all_learned ? BITS_PATH_LEARNED : BITS_PATH_TIERED};
+    if (cfg.path == BITS_PATH_TIERED && (!launch || (!launch->block && !launch->qpl))) cfg.qpl = 1u;
     if (launch) {
         if (launch->block) cfg.block = launch->block;
         if (launch->qpl) cfg.qpl = launch->qpl;
@@ -968,10 +972,21 @@ int bits_batch_create(const bits_ref* refs, uint32_t n_ref, const uint32_t* cons
     if (cfg.path == BITS_PATH_LEARNED) cfg.depth = 0;
     const uint32_t tile = cfg.block * cfg.qpl;
 
+    // With the path and the shape left open, many pairs are counted from sorted
+    // query keys when the caller's workspace has room for them; any other launch
+    // searches pair by pair.
+    MergeLayout M;
+    const BatchWs MW = batch_ws(n_ref, n_q, 0, 0);
+    std::vector<uint64_t> nb(n_ref);
+    for (uint32_t j = 0; j < n_ref; ++j) nb[j] = refs[j].n;
+    const bool merge = cfg.path == BITS_PATH_TIERED && (!launch || (!launch->block && !launch->qpl && !launch->grid)) &&
+                       merge_layout(na, n_q, n_ref, &M) && ws_bytes >= MW.total + M.bytes &&
+                       merge_pays(M, nb.data(), n_ref);
+
     // Work list ordered by reference, then query set, then tile.
     std::vector<BatchItem> items;
     std::vector<double> cost;
-    for (uint32_t j = 0; j < n_ref; ++j) {
+    for (uint32_t j = 0; j < n_ref && !merge; ++j) {
         const double per_q = std::log2((double)refs[j].n + 2.0) + 8.0;
         for (uint32_t i = 0; i < n_q; ++i)
             for (uint64_t b = 0; b < na[i]; b += tile) {
@@ -982,7 +997,7 @@ int bits_batch_create(const bits_ref* refs, uint32_t n_ref, const uint32_t* cons
     }
     uint32_t n_wg = cfg.grid ? cfg.grid : (uint32_t)device_cu_count() * (uint32_t)batch_blocks_per_cu(cfg, cfg.depth);
     n_wg = std::max(1u, std::min({n_wg, kMaxBatchWg, (uint32_t)std::max<size_t>(items.size(), 1)}));
-    const BatchWs W = batch_ws(n_ref, n_q, items.size(), n_wg);
+    const BatchWs W = merge ? MW : batch_ws(n_ref, n_q, items.size(), n_wg);
     if (ws_bytes < W.total) return BITS_E_WORKSPACE;
     // Contiguous partition of the work list with near-equal cost per workgroup.
     std::vector<uint32_t> wg(n_wg + 1, (uint32_t)items.size());
@@ -999,9 +1014,8 @@ int bits_batch_create(const bits_ref* refs, uint32_t n_ref, const uint32_t* cons
     for (uint32_t j = 0; j < n_ref; ++j) {
         const bits_ref& r = refs[j];
         const bool L = cfg.path == BITS_PATH_LEARNED;
-        rtab[j] = {r.bs, r.be, r.tree, L ? (const bits_rmi_model*)r.rmi : nullptr, L ? r.heads : nullptr,
-                   L ? r.heads + heads_len(r.n) : nullptr, fallback_counter(&r), (uint32_t)r.n, 1u << r.depth,
-                   std::min(r.depth, cfg.depth), 0u};
+        rtab[j] = {r.bs, r.be, r.tree, L ? (const bits_rmi_model*)r.rmi : nullptr, r.heads, r.heads + heads_len(r.n),
+                   fallback_counter(&r), (uint32_t)r.n, 1u << r.depth, std::min(r.depth, cfg.depth), 0u};
     }
     std::vector<BatchQuery> qtab(n_q);
     for (uint32_t i = 0; i < n_q; ++i) qtab[i] = {d_a_start[i], d_a_end[i], na[i]};
@@ -1012,7 +1026,14 @@ int bits_batch_create(const bits_ref* refs, uint32_t n_ref, const uint32_t* cons
     if (!items.empty())
         BITS_CHECK_HIP(hipMemcpyAsync(b + W.items, items.data(), sizeof(BatchItem) * items.size(),
                                       hipMemcpyHostToDevice, s));
-    BITS_CHECK_HIP(hipMemcpyAsync(b + W.wg, wg.data(), sizeof(uint32_t) * (n_wg + 1), hipMemcpyHostToDevice, s));
+    std::vector<uint32_t> offs(n_q + 1, 0u);
+    if (merge) {
+        for (uint32_t i = 0; i < n_q; ++i) offs[i + 1] = offs[i] + (uint32_t)na[i];
+        BITS_CHECK_HIP(hipMemcpyAsync(b + W.total + M.offs, offs.data(), sizeof(uint32_t) * (n_q + 1),
+                                      hipMemcpyHostToDevice, s));
+    } else {
+        BITS_CHECK_HIP(hipMemcpyAsync(b + W.wg, wg.data(), sizeof(uint32_t) * (n_wg + 1), hipMemcpyHostToDevice, s));
+    }
     BITS_CHECK_HIP(hipStreamSynchronize(s));
 
     bits_batch_plan* p = new (std::nothrow) bits_batch_plan();
@@ -1024,8 +1045,12 @@ int bits_batch_create(const bits_ref* refs, uint32_t n_ref, const uint32_t* cons
     }
     bool ok = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) == hipSuccess;
     if (ok) {
-        ok = launch_fill_u64((unsigned long long*)d_pair_totals, (uint64_t)n_q * n_ref, 0ull, cs) == hipSuccess;
-        ok = ok && launch_batch((const BatchRef*)(b + W.refs), (const BatchQuery*)(b + W.qs),
+        if (merge)
+            ok = launch_merge((const BatchRef*)(b + W.refs), n_ref, (const BatchQuery*)(b + W.qs), n_q, M, b + W.total,
+                              (unsigned long long*)d_pair_totals, refs[0].status, cs) == BITS_OK;
+        else
+            ok = launch_fill_u64((unsigned long long*)d_pair_totals, (uint64_t)n_q * n_ref, 0ull, cs) == hipSuccess &&
+                 launch_batch((const BatchRef*)(b + W.refs), (const BatchQuery*)(b + W.qs),
                                 (const BatchItem*)(b + W.items), (const uint32_t*)(b + W.wg), n_wg, n_ref, cfg.depth,
                                 cfg, (unsigned long long*)d_pair_totals, refs[0].status, cs) == hipSuccess;
         hipGraph_t g = nullptr;

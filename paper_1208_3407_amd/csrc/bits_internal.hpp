@@ -290,6 +290,24 @@ hipError_t launch_batch(const BatchRef* refs, const BatchQuery* qs, const BatchI
                         hipStream_t s);
 int batch_blocks_per_cu(const LaunchCfg& cfg, uint32_t max_depth);
 
+// merge.hip: every pair at once from sorted query keys.
+constexpr uint64_t kMergeMaxKeys = 1ull << 26;           // query keys over all sets
+constexpr uint32_t kMergeMaxSets = 192;                  // their accumulators (512 bytes each) fit the LDS
+constexpr uint32_t kMergeMaxRefs = 4096;
+constexpr uint64_t kMergeMinEvaluations = 1ull << 22;    // queries x references; fewer never pay for the sort
+constexpr uint32_t kMergeCus = 256;
+struct MergeLayout {
+    uint32_t total, chunks, groups, wgs;
+    size_t offs, in, sid, out, sets, splits, part, sort, sort_bytes, bytes;
+};
+// Workspace of the sorted form for these sets; false where only the search per pair is used.
+bool merge_layout(const uint64_t* na, uint32_t n_q, uint32_t n_ref, MergeLayout* L);
+// Whether the sorted form is expected to be the faster one against references of nb[j] keys.
+bool merge_pays(const MergeLayout& L, const uint64_t* nb, uint32_t n_ref);
+// offs (uint32[n_q + 1], the sets' first positions) is already in ws.
+int launch_merge(const BatchRef* refs, uint32_t n_ref, const BatchQuery* qs, uint32_t n_q, const MergeLayout& L, void* ws,
+                 unsigned long long* totals, uint32_t* status, hipStream_t s);
+
 // sort.hip
 // One segment to sort: n keys in -> out, optionally with one uint32 value per
 // key moved along (vmode 1: values from vin; 2: the input index 0..n-1).

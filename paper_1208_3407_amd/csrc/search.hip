@@ -1420,14 +1420,16 @@ __global__ void k_project(ChromTab ct, const uint32_t* __restrict__ chrom, const
 // only when the reference changes.  Consecutive logical workgroups run on the
 // same XCD (hardware dispatches workgroups round-robin over the 8 XCDs), so
 // an XCD's L2 sees few distinct references (and, on the learned path, their
-// leaf records).  LEARNED searches every pair through the reference's learned
+// leaf records).  kModeTiered takes the form for each reference's size;
+// kModeLearned searches every pair through the reference's learned
 // index (leaf model, error-window head probe, one line), with the per-wave scratch in LDS.
-template <int QPL, bool LEARNED>
+template <int QPL, int MODE>
 __global__ void __launch_bounds__(1024)
     k_batch(const BatchRef* __restrict__ refs, const BatchQuery* __restrict__ qs, const BatchItem* __restrict__ items,
             const uint32_t* __restrict__ wg_begin, uint32_t n_wg, uint32_t n_ref, uint32_t max_depth,
             unsigned long long* __restrict__ pair_totals, uint32_t* status) {
     extern __shared__ __align__(16) uint32_t lds[];
+    constexpr bool LEARNED = MODE == kModeLearned;
     const uint32_t g = gridDim.x, b = blockIdx.x;
     const uint32_t per_xcd = g / 8u;
     const uint32_t w = (g % 8u == 0u) ? (b % 8u) * per_xcd + b / 8u : b;
@@ -1476,7 +1478,10 @@ __global__ void __launch_bounds__(1024)
         }
         if (sa.n) {   // uniform over the workgroup: every item of the loop is one reference
             uint32_t fst[QPL];
-            icount<QPL, LEARNED ? kModeLearned : kModePlain>(sa, lds, as, ae, cnt, fst);
+            if (MODE == kModeTiered && sa.n <= kDirectKeys)
+                icount<QPL, kModeDirect>(sa, lds, as, ae, cnt, fst);
+            else
+                icount<QPL, MODE>(sa, lds, as, ae, cnt, fst);
         } else {
 #pragma unroll
             for (int q = 0; q < QPL; ++q) cnt[q] = 0;
@@ -1843,16 +1848,20 @@ hipError_t launch_project(const uint32_t* chrom_len, uint32_t n_chrom, const uin
     return hipGetLastError();
 }
 
-template <int QPL, bool LEARNED>
-static const void* batch_kernel() {
-    return (const void*)k_batch<QPL, LEARNED>;
+template <int QPL>
+static const void* batch_kernel_q(uint32_t path) {
+    switch (path) {
+        case BITS_PATH_LEARNED: return (const void*)k_batch<QPL, kModeLearned>;
+        case BITS_PATH_TIERED: return (const void*)k_batch<QPL, kModeTiered>;
+        default: return (const void*)k_batch<QPL, kModePlain>;
+    }
 }
 
-static const void* batch_kernel(uint32_t qpl, bool learned) {
+static const void* batch_kernel(uint32_t qpl, uint32_t path) {
     switch (qpl) {
-        case 1: return learned ? batch_kernel<1, true>() : batch_kernel<1, false>();
-        case 4: return learned ? batch_kernel<4, true>() : batch_kernel<4, false>();
-        default: return learned ? batch_kernel<2, true>() : batch_kernel<2, false>();
+        case 1: return batch_kernel_q<1>(path);
+        case 4: return batch_kernel_q<4>(path);
+        default: return batch_kernel_q<2>(path);
     }
 }
 
@@ -1864,15 +1873,14 @@ hipError_t launch_batch(const BatchRef* refs, const BatchQuery* qs, const BatchI
                         uint32_t n_wg, uint32_t n_ref, uint32_t max_depth, const LaunchCfg& cfg,
                         unsigned long long* pair_totals, uint32_t* status, hipStream_t s) {
     const size_t lds = batch_lds(cfg, max_depth);
-    const bool L = cfg.path == BITS_PATH_LEARNED;
-    const void* k = batch_kernel(cfg.qpl, L);
+    const void* k = batch_kernel(cfg.qpl, cfg.path);
     void* args[] = {(void*)&refs, (void*)&qs, (void*)&items, (void*)&wg_begin, (void*)&n_wg, (void*)&n_ref,
                     (void*)&max_depth, (void*)&pair_totals, (void*)&status};
     return hipLaunchKernel(k, dim3(n_wg), dim3(cfg.block), args, lds, s);
 }
 
 int batch_blocks_per_cu(const LaunchCfg& cfg, uint32_t max_depth) {
-    return blocks_per_cu(batch_kernel(cfg.qpl, cfg.path == BITS_PATH_LEARNED), (int)cfg.block,
+    return blocks_per_cu(batch_kernel(cfg.qpl, cfg.path), (int)cfg.block,
                          batch_lds(cfg, max_depth));
 }
 

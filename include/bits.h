@@ -364,7 +364,8 @@ int bits_mc_binned_stage_ms(float *ms);
 
 /* Workspace bytes of bits_mc_resort for |B| = nb and `batch` rounds per
  * sort launch (1 <= batch <= 4096): 16 bytes per interval of B, 16 bytes per
- * interval per round of the batch, and the segmented sort's workspace. */
+ * interval (nb rounded up to 32) per round of the batch, and the segmented
+ * sort's workspace. */
 int bits_mc_resort_workspace(uint64_t nb, uint32_t batch, size_t *bytes);
 
 /* The Monte-Carlo loop in the paper's orientation (Sec. 3.2, Table 1): every
@@ -372,7 +373,8 @@ int bits_mc_resort_workspace(uint64_t nb, uint32_t batch, size_t *bytes);
  * Philox stream of bits_mc_pvalue with the roles of A and B swapped: round s
  * places interval j of B with counter g = s * nb + j), sorts B_S and B_E
  * again on the device (segmented radix sort, `batch` rounds per launch) and
- * counts the fixed query set A against it by plain bisection.  The count is
+ * counts the fixed query set A against it (top trees of every round, then a
+ * window of keys or line heads, as BITS_PATH_TIERED).  The count is
  * symmetric in A and B, so the per-round totals equal bits_mc_pvalue's with
  * a reference built from A and B as the queries, which needs no per-round
  * sort; this entry point is the literal form, for comparison.

@@ -764,16 +764,16 @@ int bits_enumerate(const void* d_index, uint64_t n, const uint32_t* d_a_start, c
 namespace {
 struct ResortWs {
     size_t tab, status, s_in, e_in, s_out, e_out, sort, total;
-    size_t seg;   // bytes of one round's keys
+    uint64_t stride;   // words from one round's keys to the next: whole 128-byte lines
 };
 ResortWs resort_ws(uint64_t nb, uint32_t batch) {
     ResortWs W;
     size_t o = 0;
     const size_t col = align256((size_t)nb * sizeof(uint32_t));
-    W.seg = (size_t)nb * sizeof(uint32_t);
+    W.stride = (nb + 31) & ~31ull;
     W.tab = o; o += 4 * col + 2 * align256(BITS_MAX_CHROM * sizeof(uint32_t));
     W.status = o; o += 256;   // status word used when the caller passes none
-    const size_t keys = align256((size_t)batch * W.seg);
+    const size_t keys = align256((size_t)batch * W.stride * sizeof(uint32_t));
     W.s_in = o; o += keys;
     W.e_in = o; o += keys;
     W.s_out = o; o += keys;
@@ -831,18 +831,22 @@ int bits_mc_resort(const uint32_t* d_a_start, const uint32_t* d_a_end, uint64_t 
         // B's per-interval table (chromosome offset, legal starts, length, index), computed once
         uint32_t* status = d_status ? d_status : (uint32_t*)(w + W.status);
         BITS_CHECK_HIP(launch_mc_prepare(d_b_start, d_b_end, nb, chrom_len, n_chrom, tab, status, s));
+        // the sort leaves the words between two rounds alone; the searches read them as +inf
+        BITS_CHECK_HIP(launch_fill_tails(S_out, E_out, nb, W.stride, (uint32_t)std::min<uint64_t>(batch, std::max<uint64_t>(ns, 1)), s));
         auto run = [&](uint64_t first, uint32_t rounds, bool identity, unsigned long long* out) -> int {
-            BITS_CHECK_HIP(launch_place_rounds(tab, d_b_start, nb, seed, first, rounds, identity, S_in, E_in, s));
+            BITS_CHECK_HIP(launch_place_rounds(tab, d_b_start, nb, W.stride, seed, first, rounds, identity, S_in, E_in, s));
             std::vector<SortSeg> segs;
             segs.reserve(2 * (size_t)rounds);
             for (uint32_t r = 0; r < rounds; ++r) {
-                segs.push_back({S_in + (size_t)r * nb, S_out + (size_t)r * nb, nb});
-                segs.push_back({E_in + (size_t)r * nb, E_out + (size_t)r * nb, nb});
+                segs.push_back({S_in + r * W.stride, S_out + r * W.stride, nb});
+                segs.push_back({E_in + r * W.stride, E_out + r * W.stride, nb});
             }
             const int rc = launch_sort(segs.data(), 2 * rounds, sort_ws, sort_bytes, s);
             if (rc != BITS_OK) return rc;
             BITS_CHECK_HIP(launch_sort_report(sort_ws, status, s));
-            BITS_CHECK_HIP(launch_count_rounds(S_out, E_out, nb, rounds, d_a_start, d_a_end, na, out, status, s));
+            // the unsorted keys are no longer needed: their buffers take the rounds' trees and heads
+            BITS_CHECK_HIP(launch_count_rounds(S_out, E_out, nb, W.stride, rounds, S_in, E_in, d_a_start, d_a_end, na,
+                                               out, status, s));
             return BITS_OK;
         };
         int rc = run(0, 1, true, obs);

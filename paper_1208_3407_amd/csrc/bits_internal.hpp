@@ -98,6 +98,14 @@ struct SearchArgs {
 // 32-entry window starting at or before head ceil(n / 32) - 1 + 16 stays in bounds.
 __host__ __device__ constexpr uint64_t heads_len(uint64_t n) { return ((n + 31) / 32 + 32 + 31) / 32 * 32; }
 
+// Boundary rank of node k of an Eytzinger top tree over n keys (level
+// l = floor(log2 k), j = k - 2^l): floor((2j + 1) n / 2^(l + 1)); the node
+// holds the key before it, the last of the bucket on its left.
+__host__ __device__ constexpr uint64_t tree_rank(uint32_t k, uint64_t n) {
+    uint32_t l = 31u - (uint32_t)__builtin_clz(k);
+    return ((2 * (uint64_t)(k - (1u << l)) + 1) * n) >> (l + 1);
+}
+
 // Number of LDS words a search kernel stages for depth d (both arrays).
 __host__ __device__ constexpr uint32_t tree_lds_words(uint32_t d) { return d ? (2u << d) : 0u; }
 
@@ -224,11 +232,16 @@ hipError_t launch_decide(const SearchArgs& sa, const LaunchCfg& cfg, const uint3
                          uint64_t na, uint32_t* found, unsigned long long* witness, hipStream_t s);
 hipError_t launch_select_u64(const unsigned long long* v, uint64_t n, uint64_t k0, uint64_t k1,
                              unsigned long long* out0, unsigned long long* out1, hipStream_t s);
-hipError_t launch_place_rounds(const McTable& tab, const uint32_t* b_start, uint64_t nb, uint64_t seed, uint64_t s0,
-                               uint32_t rounds, bool identity, uint32_t* S, uint32_t* E, hipStream_t s);
-hipError_t launch_count_rounds(const uint32_t* S, const uint32_t* E, uint64_t nb, uint32_t rounds, const uint32_t* as,
-                               const uint32_t* ae, uint64_t na, unsigned long long* totals, uint32_t* status,
+// Rounds lie `stride` words apart, a multiple of 32 that is >= nb.
+hipError_t launch_place_rounds(const McTable& tab, const uint32_t* b_start, uint64_t nb, uint64_t stride,
+                               uint64_t seed, uint64_t s0, uint32_t rounds, bool identity, uint32_t* S, uint32_t* E,
                                hipStream_t s);
+hipError_t launch_fill_tails(uint32_t* S, uint32_t* E, uint64_t nb, uint64_t stride, uint32_t rounds, hipStream_t s);
+// Sorted rounds, 0xFFFFFFFF between nb and stride; trees and heads: scratch of
+// `stride` words per round each.
+hipError_t launch_count_rounds(const uint32_t* S, const uint32_t* E, uint64_t nb, uint64_t stride, uint32_t rounds,
+                               uint32_t* trees, uint32_t* heads, const uint32_t* as, const uint32_t* ae, uint64_t na,
+                               unsigned long long* totals, uint32_t* status, hipStream_t s);
 // binned.hip: the Monte-Carlo path binned by genome region.
 struct BinLayout {
     uint64_t ncells, nreg_max;

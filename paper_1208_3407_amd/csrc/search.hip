@@ -1251,14 +1251,15 @@ __global__ void __launch_bounds__(1024) k_mc_prepare(const uint32_t* __restrict_
 // database set B and sorts it again, then counts the fixed query set A.
 // Round r of a batch places interval idx[p] of B (table position p) by the
 // rule and stream of k_mc with the roles swapped, g = (s0 + r) * nb + idx[p],
-// and writes keys S[r * nb + p], E[r * nb + p] as one segment per round for
+// and writes keys S[r * stride + p], E[r * stride + p] as one segment per round for
 // the segmented sort.  An interval outside its chromosome (span 0) becomes
 // the sentinel [2^32 - 1, 2^32 - 1], which no query with end < 2^32 - 1
 // counts.  identity = true writes the unshuffled set (the observed round).
 __global__ void k_place_rounds(const uint32_t* __restrict__ off, const uint32_t* __restrict__ span,
                                const uint32_t* __restrict__ len, const uint32_t* __restrict__ idx,
-                               const uint32_t* __restrict__ b_start, uint64_t nb, uint64_t seed, uint64_t s0,
-                               uint32_t rounds, uint32_t identity, uint32_t* __restrict__ S, uint32_t* __restrict__ E) {
+                               const uint32_t* __restrict__ b_start, uint64_t nb, uint64_t stride, uint64_t seed,
+                               uint64_t s0, uint32_t rounds, uint32_t identity, uint32_t* __restrict__ S,
+                               uint32_t* __restrict__ E) {
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     const uint64_t total = (uint64_t)rounds * nb;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
@@ -1278,51 +1279,88 @@ __global__ void k_place_rounds(const uint32_t* __restrict__ off, const uint32_t*
             }
             en = st + len[p] - 1u;
         }
-        S[t] = st;
-        E[t] = en;
+        S[r * stride + p] = st;
+        E[r * stride + p] = en;
     }
 }
 
-// Counts the fixed query set A against every sorted round of a batch
-// (segments S[r * nb ..], E[r * nb ..]) by plain bisection of the whole
-// segment (no top tree: the arrays change every round).  Work item = (round,
-// tile of A); one atomic per wave per item into totals[r].
-template <int QPL>
-BITS_SEARCH_KERNEL k_count_rounds(SearchArgs sa0, const uint32_t* __restrict__ S, const uint32_t* __restrict__ E,
-                                  uint64_t nb, uint32_t rounds, const uint32_t* __restrict__ a_start,
-                                  const uint32_t* __restrict__ a_end, uint64_t na, uint64_t tiles,
-                                  unsigned long long* __restrict__ totals) {
-    const uint64_t tile = (uint64_t)blockDim.x * QPL;
-    uint32_t bad = 0;
-    for (uint64_t item = blockIdx.x; item < (uint64_t)rounds * tiles; item += gridDim.x) {
-        const uint64_t r = item / tiles, t = item - r * tiles;
-        SearchArgs sa = sa0;
-        sa.bs = S + r * nb;
-        sa.be = E + r * nb;
-        sa.n = (uint32_t)nb;
-        sa.depth = 0;
-        uint32_t as[QPL], ae[QPL], cnt[QPL], fst[QPL];
-        bool valid[QPL];
-#pragma unroll
-        for (int q = 0; q < QPL; ++q) {
-            const uint64_t i = t * tile + (uint64_t)q * blockDim.x + threadIdx.x;
-            valid[q] = i < na;
-            as[q] = valid[q] ? a_start[i] : 0u;
-            ae[q] = valid[q] ? a_end[i] : kIdleEnd;
-            if (as[q] > ae[q]) {
-                bad = 1;
-                valid[q] = false;
-                ae[q] = as[q];
-            }
-        }
-        icount_plain<QPL>(sa, nullptr, as, ae, cnt, fst);
-        uint64_t sum = 0;
-#pragma unroll
-        for (int q = 0; q < QPL; ++q) sum += valid[q] ? cnt[q] : 0u;
-        sum = wave_sum_u64(sum);
-        if ((threadIdx.x & (kWave - 1)) == 0 && sum) atomicAdd(totals + r, (unsigned long long)sum);
+// 0xFFFFFFFF from nb to stride of every round.
+__global__ void k_fill_tails(uint32_t* __restrict__ S, uint32_t* __restrict__ E, uint64_t nb, uint64_t stride,
+                             uint32_t rounds) {
+    const uint32_t tail = (uint32_t)(stride - nb);
+    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < rounds * tail; t += gridDim.x * blockDim.x) {
+        const uint64_t at = (uint64_t)(t / tail) * stride + nb + t % tail;
+        S[at] = 0xFFFFFFFFu;
+        E[at] = 0xFFFFFFFFu;
     }
-    if (bad && sa0.status) atomicOr(sa0.status, BITS_FLAG_INTERVAL);
+}
+
+// What the search without a model needs of every sorted round (segments
+// S[r * stride ..], E[r * stride ..] of nb keys): the top trees of both arrays
+// at trees + r * stride, and above kDirectKeys their line heads at
+// heads + r * stride.  blockIdx.y = round.
+__global__ void __launch_bounds__(256) k_round_index(const uint32_t* __restrict__ S, const uint32_t* __restrict__ E,
+                                                     uint32_t nb, uint64_t stride, uint32_t depth,
+                                                     uint32_t* __restrict__ trees, uint32_t* __restrict__ heads) {
+    const uint64_t o = blockIdx.y * stride;
+    const uint32_t m = 1u << depth, hl = nb > kDirectKeys ? (uint32_t)heads_len(nb) : 0u, lines = (nb + 31u) / 32u;
+    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < 2u * (m + hl); t += gridDim.x * blockDim.x) {
+        if (t < 2u * m) {
+            const uint32_t k = t & (m - 1u);
+            const uint32_t* K = (t < m ? S : E) + o;
+            trees[o + t] = k ? K[tree_rank(k, nb) - 1u] : 0u;
+        } else {
+            const uint32_t a = t - 2u * m >= hl ? 1u : 0u, k = t - 2u * m - a * hl;
+            heads[o + t - 2u * m] = k < lines ? (a ? E : S)[o + 32u * (uint64_t)k] : 0xFFFFFFFFu;
+        }
+    }
+}
+
+// Counts the fixed query set A against every sorted round of a batch: `per`
+// workgroups a round, each staging the round's top trees once for its share
+// of A.  Random reads of the round's sorted arrays bound it, so a round
+// belongs to one XCD (workgroups b = r mod 8) and few rounds are in flight on
+// it, to be served from its L2: 64 rounds of 1e5 intervals against 1e5
+// queries take 128 us with 16 workgroups a round (8: 159, 32: 161, 64: 229,
+// from staging), 367 us with rounds spread over all XCDs, and 710 us for a
+// bisection of the whole segment per search.  Fewer than 8 rounds are spread
+// over the whole chip.
+constexpr uint32_t kRoundParts = 16;   // most workgroups of a round
+template <int MODE>
+BITS_SEARCH_KERNEL k_count_rounds(SearchArgs sa0, uint64_t stride, uint32_t rounds, uint32_t per,
+                                  const uint32_t* __restrict__ a_start, const uint32_t* __restrict__ a_end, uint64_t na,
+                                  unsigned long long* __restrict__ totals) {
+    extern __shared__ __align__(16) uint32_t lds[];
+    const uint32_t xg = rounds >= kXcds ? kXcds : 1u;
+    const uint32_t slot = blockIdx.x / xg, turn = slot / per, part = slot - turn * per;
+    const uint32_t r = turn * xg + blockIdx.x % xg;
+    if (r >= rounds) return;
+    SearchArgs sa = sa0;
+    sa.bs += r * stride;
+    sa.be += r * stride;
+    sa.tree += r * stride;
+    sa.hs += r * stride;
+    sa.he += r * stride;
+    stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
+    __syncthreads();
+    const uint64_t tiles = (na + blockDim.x - 1) / blockDim.x;
+    uint32_t bad = 0;
+    uint64_t sum = 0;
+    for (uint64_t t = part; t < tiles; t += per) {
+        const uint64_t i = t * blockDim.x + threadIdx.x;
+        bool valid = i < na;
+        uint32_t as[1] = {valid ? a_start[i] : 0u}, ae[1] = {valid ? a_end[i] : kIdleEnd}, cnt[1], fst[1];
+        if (as[0] > ae[0]) {
+            bad = 1;
+            valid = false;
+            ae[0] = as[0];
+        }
+        icount<1, MODE>(sa, lds, as, ae, cnt, fst);
+        sum += valid ? cnt[0] : 0u;
+    }
+    sum = wave_sum_u64(sum);
+    if ((threadIdx.x & (kWave - 1)) == 0 && sum) atomicAdd(totals + r, (unsigned long long)sum);
+    if (bad && sa.status) atomicOr(sa.status, BITS_FLAG_INTERVAL);
 }
 
 __global__ void k_mc_tail(const unsigned long long* __restrict__ totals, uint64_t nshuf,
@@ -1800,33 +1838,55 @@ hipError_t launch_select_u64(const unsigned long long* v, uint64_t n, uint64_t k
     return hipGetLastError();
 }
 
-hipError_t launch_place_rounds(const McTable& tab, const uint32_t* b_start, uint64_t nb, uint64_t seed, uint64_t s0,
-                               uint32_t rounds, bool identity, uint32_t* S, uint32_t* E, hipStream_t s) {
+hipError_t launch_place_rounds(const McTable& tab, const uint32_t* b_start, uint64_t nb, uint64_t stride,
+                               uint64_t seed, uint64_t s0, uint32_t rounds, bool identity, uint32_t* S, uint32_t* E,
+                               hipStream_t s) {
     const uint64_t total = (uint64_t)rounds * nb;
     if (!total) return hipSuccess;
     uint64_t g = (total + 255) / 256;
     if (g > 16384) g = 16384;
     hipLaunchKernelGGL(k_place_rounds, dim3((uint32_t)g), dim3(256), 0, s, tab.off, tab.span, tab.len, tab.idx,
-                       b_start, nb, seed, s0, rounds, identity ? 1u : 0u, S, E);
+                       b_start, nb, stride, seed, s0, rounds, identity ? 1u : 0u, S, E);
     return hipGetLastError();
 }
 
-hipError_t launch_count_rounds(const uint32_t* S, const uint32_t* E, uint64_t nb, uint32_t rounds, const uint32_t* as,
-                               const uint32_t* ae, uint64_t na, unsigned long long* totals, uint32_t* status,
-                               hipStream_t s) {
+hipError_t launch_fill_tails(uint32_t* S, uint32_t* E, uint64_t nb, uint64_t stride, uint32_t rounds, hipStream_t s) {
+    const uint32_t words = (uint32_t)(stride - nb) * rounds;   // < 32 * 4096
+    if (!words) return hipSuccess;
+    hipLaunchKernelGGL(k_fill_tails, dim3((words + 255) / 256), dim3(256), 0, s, S, E, nb, stride, rounds);
+    return hipGetLastError();
+}
+
+hipError_t launch_count_rounds(const uint32_t* S, const uint32_t* E, uint64_t nb, uint64_t stride, uint32_t rounds,
+                               uint32_t* trees, uint32_t* heads, const uint32_t* as, const uint32_t* ae, uint64_t na,
+                               unsigned long long* totals, uint32_t* status, hipStream_t s) {
     if (!na || !rounds) return hipSuccess;
-    constexpr int QPL = 2;
-    const uint32_t block = 256;
-    const uint64_t tile = (uint64_t)block * QPL;
-    const uint64_t tiles = (na + tile - 1) / tile;
     SearchArgs sa{};
     sa.status = status;
     sa.n = (uint32_t)nb;
-    LaunchCfg cfg{block, QPL, 0, 0, BITS_PATH_PLAIN};
-    const void* kern = (const void*)k_count_rounds<QPL>;
-    const uint32_t grid = persistent_grid(kern, cfg, 0, (uint64_t)rounds * tiles);
-    hipLaunchKernelGGL(k_count_rounds<QPL>, dim3(grid), dim3(block), 0, s, sa, S, E, nb, rounds, as, ae, na, tiles,
-                       totals);
+    sa.bs = S;
+    sa.be = E;
+    sa.tree = trees;
+    sa.hs = heads;
+    sa.he = heads + heads_len(nb);
+    // both trees of a round fit its segment: 2 * 2^depth <= stride, and depth <= floor(log2 nb)
+    while (sa.depth < BITS_MAX_DEPTH && (4ull << sa.depth) <= stride && (2ull << sa.depth) <= nb) ++sa.depth;
+    sa.tree_stride = 1u << sa.depth;
+    const uint64_t words = (2ull << sa.depth) + (nb > kDirectKeys ? 2 * heads_len(nb) : 0);
+    hipLaunchKernelGGL(k_round_index, dim3((uint32_t)((words + 255) / 256 < 256 ? (words + 255) / 256 : 256), rounds),
+                       dim3(256), 0, s, S, E, (uint32_t)nb, stride, sa.depth, trees, heads);
+    const uint32_t block = 512;
+    const uint64_t tiles = (na + block - 1) / block;
+    const uint32_t xg = rounds >= kXcds ? kXcds : 1u, turns = (rounds + xg - 1) / xg;
+    const uint64_t most = rounds >= kXcds ? kRoundParts : 2ull * device_cu_count() / rounds;
+    const uint32_t per = (uint32_t)(tiles < most ? tiles : most);
+    const size_t lds = search_lds_bytes(false, sa.depth, 1, block);
+    if (nb > kDirectKeys)
+        hipLaunchKernelGGL(k_count_rounds<kModeTiered>, dim3(xg * turns * per), dim3(block), lds, s, sa, stride, rounds,
+                           per, as, ae, na, totals);
+    else
+        hipLaunchKernelGGL(k_count_rounds<kModeDirect>, dim3(xg * turns * per), dim3(block), lds, s, sa, stride, rounds,
+                           per, as, ae, na, totals);
     return hipGetLastError();
 }
 

@@ -422,22 +422,13 @@ __global__ void k_copy_if_idle(const SegDesc* __restrict__ descs, uint32_t nseg,
     }
 }
 
-// Eytzinger top tree: node k (level l = floor(log2 k), j = k - 2^l) holds
-// keys[p - 1] with p = floor((2j + 1) n / 2^(l + 1)), i.e. the last key of
-// the bucket left of boundary p.  The first 2^d - 1 nodes form the depth-d
+// Eytzinger top tree: node k holds keys[tree_rank(k, n) - 1], the last key of
+// the bucket left of its boundary.  The first 2^d - 1 nodes form the depth-d
 // tree for every d <= depth.
 __global__ void k_build_tree(const uint32_t* __restrict__ keys, uint64_t n, uint32_t depth, uint32_t* __restrict__ tree) {
     const uint32_t m = 1u << depth;
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < m; k += gridDim.x * blockDim.x) {
-        if (k == 0) {
-            tree[0] = 0u;
-            continue;
-        }
-        const uint32_t l = 31u - __clz(k);
-        const uint64_t j = k - (1u << l);
-        const uint64_t pos = ((2 * j + 1) * n) >> (l + 1);
-        tree[k] = keys[pos - 1];
-    }
+    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < m; k += gridDim.x * blockDim.x)
+        tree[k] = k ? keys[tree_rank(k, n) - 1] : 0u;
 }
 
 // Line heads: the first key of every 128-byte line, then +inf padding.

@@ -4,7 +4,8 @@ and one key more, arrays of less than a line and of lines plus or minus one
 key, both sides of the size where windows of keys give way to line heads, and
 key patterns that a straight line does not predict (equal keys, runs far
 apart, a curve).  Counts, first ranks, decisions and Monte-Carlo observed
-totals against the oracle."""
+totals against the oracle; the re-sorting Monte-Carlo, whose rounds are
+searched the same way, against the other orientation."""
 import numpy as np
 import pytest
 
@@ -71,3 +72,28 @@ def test_windows(kind, n):
     mc = bits.bits_mc_pvalue(ref, up(a0[inside]), up(a1[inside]), [TOP], 7, 0, 2)
     assert int(mc.observed.item()) == int(exp[inside].astype(np.uint64).sum())
     assert bits.bits_get_status(ref) == 0
+
+
+@pytest.mark.parametrize("nb,rounds,batch", [(1, 3, 2), (2, 9, 9), (31, 8, 8), (33, 17, 16), (100, 1, 1),
+                                             (8193, 20, 12), (28 * 8192 + 5, 10, 10), ((1 << 19) + 37, 9, 9)])
+def test_resort_rounds(nb, rounds, batch):
+    print("case: resort", nb, rounds, batch, flush=True)
+    rng = np.random.default_rng(nb)
+    lens = [40_000_000, 300_000, 1_000]
+    off = np.concatenate([[0], np.cumsum(lens)])
+
+    def one(n):
+        c = rng.integers(0, 3, n)
+        L = rng.integers(1, 900, n)
+        s = off[c] + (rng.random(n) * (np.array(lens)[c] - L)).astype(np.int64)
+        return s, s + L - 1
+    a, b = one(2500), one(nb)
+    if nb > 50:
+        b[1][7] += 50_000_000                    # outside its chromosome
+    qa, qb = (up(a[0]), up(a[1])), (up(b[0]), up(b[1]))
+    status = torch.zeros(1, dtype=torch.uint32, device=DEV)
+    got = bits.bits_mc_resort(*qa, *qb, lens, 11, 3, 3 + rounds, batch=batch, status=status)
+    exp = bits.bits_mc_pvalue(bits.bits_sort_ref(*qa), *qb, lens, 11, 3, 3 + rounds)
+    for name in ("totals", "observed", "n_ge", "n_le"):
+        assert torch.equal(getattr(got, name).view(torch.int64), getattr(exp, name).view(torch.int64)), name
+    assert int(status.item()) == (bits.BITS_FLAG_CHROM if nb > 50 else 0)

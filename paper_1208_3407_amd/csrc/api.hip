@@ -210,28 +210,20 @@ int bits_sort_refs_workspace(const uint64_t* n, uint32_t n_ref, size_t* bytes) {
     return BITS_OK;
 }
 
-// Builds the rest of a reference index from its sorted arrays; the status
-// block was cleared before the sort.
-static int finish_ref(const bits_ref* r, const bits_train& tr, void* ws, hipStream_t s) {
-    if (r->n) {
-        // keys past n up to the end of the last 128-byte line read as +inf
-        const uint64_t pad = ((r->n + 31) & ~31ull) - r->n;
-        BITS_CHECK_HIP(launch_fill_u32(r->bs + r->n, pad, 0xFFFFFFFFu, s));
-        BITS_CHECK_HIP(launch_fill_u32(r->be + r->n, pad, 0xFFFFFFFFu, s));
-        BITS_CHECK_HIP(launch_build_tree(r->bs, r->n, r->depth, r->tree, s));
-        BITS_CHECK_HIP(launch_build_tree(r->be, r->n, r->depth, r->tree + ((size_t)1 << r->depth), s));
-    } else {
-        BITS_CHECK_HIP(launch_fill_u32(r->tree, (uint64_t)2 << r->depth, 0u, s));
+static FinishRef finish_of(const bits_ref* r) {
+    // the learned build's pass over the keys also writes the heads
+    return {{r->bs, r->be}, r->tree, r->learned && r->n ? nullptr : r->heads, (uint32_t)r->n, r->depth};
+}
+
+// The learned index of a reference whose arrays are sorted and trees built.
+static int build_model(const bits_ref* r, const bits_train& tr, void* ws, hipStream_t s) {
+    if (!r->learned) return BITS_OK;
+    if (!r->n) {
+        BITS_CHECK_HIP(launch_fill_u32((uint32_t*)r->rmi, 2 * sizeof(bits_rmi_model) / 4, 0u, s));
+        return BITS_OK;
     }
-    uint32_t* he = r->heads + heads_len(r->n);
-    if (r->learned && r->n) {   // the learned build's pass over the keys also writes the heads
-        bits_rmi_model* m = (bits_rmi_model*)r->rmi;
-        return launch_rmi_build2(r->bs, r->be, r->n, m, m + 1, r->heads, he, tr, ws, s);
-    }
-    BITS_CHECK_HIP(launch_build_heads(r->bs, r->n, r->heads, s));
-    BITS_CHECK_HIP(launch_build_heads(r->be, r->n, he, s));
-    if (r->learned) BITS_CHECK_HIP(launch_fill_u32((uint32_t*)r->rmi, 2 * sizeof(bits_rmi_model) / 4, 0u, s));
-    return BITS_OK;
+    bits_rmi_model* m = (bits_rmi_model*)r->rmi;
+    return launch_rmi_build2(r->bs, r->be, r->n, m, m + 1, r->heads, r->heads + heads_len(r->n), tr, ws, s);
 }
 
 int bits_sort_ref(const uint32_t* d_b_start, const uint32_t* d_b_end, const bits_ref* ref, void* d_ws,
@@ -242,14 +234,17 @@ int bits_sort_ref(const uint32_t* d_b_start, const uint32_t* d_b_end, const bits
     bits_sort_ref_workspace(ref->n, &need);
     if (ref->n && ws_bytes < need) return BITS_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    BITS_CHECK_HIP(launch_fill_u32(ref->status, kStatusBytes / 4, 0u, s));
     if (ref->n) {
-        SortSeg segs[2] = {{d_b_start, ref->bs, ref->n}, {d_b_end, ref->be, ref->n}};
+        const SortSeg segs[2] = {{d_b_start, ref->bs, ref->n, 0u, nullptr, nullptr, ref->status, kStatusBytes / 4},
+                                 {d_b_end, ref->be, ref->n, 0u, nullptr, nullptr, ref->status}};
         const int rc = launch_sort(segs, 2, d_ws, ws_bytes, s);
         if (rc != BITS_OK) return rc;
-        BITS_CHECK_HIP(launch_sort_report(d_ws, ref->status, s));
+    } else {
+        BITS_CHECK_HIP(launch_fill_u32(ref->status, kStatusBytes / 4, 0u, s));
     }
-    return finish_ref(ref, train_defaults(train), d_ws, s);
+    const FinishRef f = finish_of(ref);
+    BITS_CHECK_HIP(launch_finish_refs(&f, 1, s));
+    return build_model(ref, train_defaults(train), d_ws, s);
 }
 
 int bits_sort_refs(const uint32_t* const* d_b_start, const uint32_t* const* d_b_end, const bits_ref* refs,
@@ -258,25 +253,27 @@ int bits_sort_refs(const uint32_t* const* d_b_start, const uint32_t* const* d_b_
     if (!d_b_start || !d_b_end || !refs || !d_ws) return BITS_E_ARG;
     std::vector<uint64_t> ns(n_ref);
     std::vector<SortSeg> segs;
+    std::vector<FinishRef> fin;
     segs.reserve(2 * (size_t)n_ref);
+    fin.reserve(n_ref);
     for (uint32_t j = 0; j < n_ref; ++j) {
         if (!ref_ok(&refs[j])) return BITS_E_ARG;
         if (refs[j].n && (!d_b_start[j] || !d_b_end[j])) return BITS_E_ARG;
         ns[j] = refs[j].n;
-        segs.push_back({d_b_start[j], refs[j].bs, refs[j].n});
-        segs.push_back({d_b_end[j], refs[j].be, refs[j].n});
+        segs.push_back({d_b_start[j], refs[j].bs, refs[j].n, 0u, nullptr, nullptr, refs[j].status, kStatusBytes / 4});
+        segs.push_back({d_b_end[j], refs[j].be, refs[j].n, 0u, nullptr, nullptr, refs[j].status});
+        fin.push_back(finish_of(&refs[j]));
     }
     size_t need = 0;
     bits_sort_refs_workspace(ns.data(), n_ref, &need);
     if (ws_bytes < need) return BITS_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    for (uint32_t j = 0; j < n_ref; ++j) BITS_CHECK_HIP(launch_fill_u32(refs[j].status, kStatusBytes / 4, 0u, s));
     int rc = launch_sort(segs.data(), (uint32_t)segs.size(), d_ws, ws_bytes, s);
     if (rc != BITS_OK) return rc;
-    for (uint32_t j = 0; j < n_ref; ++j) BITS_CHECK_HIP(launch_sort_report(d_ws, refs[j].status, s));
+    BITS_CHECK_HIP(launch_finish_refs(fin.data(), n_ref, s));
     const bits_train tr = train_defaults(train);
     for (uint32_t j = 0; j < n_ref; ++j) {
-        rc = finish_ref(&refs[j], tr, d_ws, s);
+        rc = build_model(&refs[j], tr, d_ws, s);
         if (rc != BITS_OK) return rc;
     }
     return BITS_OK;
@@ -838,12 +835,11 @@ int bits_mc_resort(const uint32_t* d_a_start, const uint32_t* d_a_end, uint64_t 
             std::vector<SortSeg> segs;
             segs.reserve(2 * (size_t)rounds);
             for (uint32_t r = 0; r < rounds; ++r) {
-                segs.push_back({S_in + r * W.stride, S_out + r * W.stride, nb});
-                segs.push_back({E_in + r * W.stride, E_out + r * W.stride, nb});
+                segs.push_back({S_in + r * W.stride, S_out + r * W.stride, nb, 0u, nullptr, nullptr, status});
+                segs.push_back({E_in + r * W.stride, E_out + r * W.stride, nb, 0u, nullptr, nullptr, status});
             }
             const int rc = launch_sort(segs.data(), 2 * rounds, sort_ws, sort_bytes, s);
             if (rc != BITS_OK) return rc;
-            BITS_CHECK_HIP(launch_sort_report(sort_ws, status, s));
             // the unsorted keys are no longer needed: their buffers take the rounds' trees and heads
             BITS_CHECK_HIP(launch_count_rounds(S_out, E_out, nb, W.stride, rounds, S_in, E_in, d_a_start, d_a_end, na,
                                                out, status, s));

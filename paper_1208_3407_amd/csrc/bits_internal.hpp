@@ -331,17 +331,25 @@ struct SortSeg {
     uint32_t vmode = 0;
     const uint32_t* vin = nullptr;
     uint32_t* vout = nullptr;
+    // gets BITS_FLAG_SORT if a tile's look-back walk gave up (never expected; the
+    // sorted output is then invalid); its first `clear` words (at most 256) are zeroed first
+    uint32_t* status = nullptr;
+    uint32_t clear = 0;
 };
 size_t sort_workspace_bytes(const uint64_t* n, uint32_t nseg, const uint32_t* vmode = nullptr);
 int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, hipStream_t s);
-// After launch_sort, before anything else writes ws: ORs BITS_FLAG_SORT into
-// *status if a tile's look-back walk gave up (never expected; the sorted
-// output is then invalid).
-hipError_t launch_sort_report(const void* ws, uint32_t* status, hipStream_t s);
-hipError_t launch_build_tree(const uint32_t* keys, uint64_t n, uint32_t depth, uint32_t* tree, hipStream_t s);
-// Line heads of a sorted array: H[j] = keys[32 j] for j < ceil(n / 32), then
-// 0xFFFFFFFF up to heads_len(n) entries.
-hipError_t launch_build_heads(const uint32_t* keys, uint64_t n, uint32_t* heads, hipStream_t s);
+// Trees, line tails and (heads != nullptr) line heads of sorted references.
+struct FinishRef {
+    uint32_t* k[2];      // sorted starts and ends
+    uint32_t* tree;      // [2][2^depth]
+    uint32_t* heads;     // [2][heads_len(n)] or nullptr
+    uint32_t n, depth;
+};
+constexpr uint32_t kFinishRefs = 64;   // references per launch (40 bytes of arguments each)
+struct FinishChunk {
+    FinishRef r[kFinishRefs];
+};
+hipError_t launch_finish_refs(const FinishRef* refs, uint32_t n_ref, hipStream_t s);
 
 // enum.hip
 uint64_t scan_tiles(uint64_t n);

@@ -308,10 +308,9 @@ int launch_merge(const BatchRef* refs, uint32_t n_ref, const BatchQuery* qs, uin
     auto* part = (unsigned long long*)(b + L.part);
     const uint32_t gg = std::min<uint32_t>((L.total + 255) / 256, 4096);
     hipLaunchKernelGGL(k_merge_gather, dim3(gg), dim3(256), 0, s, qs, offs, n_q, L.total, in_s, in_e, sid, status);
-    const SortSeg segs[2] = {{in_s, out_s, L.total, 1u, sid, set_s}, {in_e, out_e, L.total, 1u, sid, set_e}};
+    const SortSeg segs[2] = {{in_s, out_s, L.total, 1u, sid, set_s, status}, {in_e, out_e, L.total, 1u, sid, set_e, status}};
     const int rc = launch_sort(segs, 2, b + L.sort, L.sort_bytes, s);
     if (rc != BITS_OK) return rc;
-    BITS_CHECK_HIP(launch_sort_report(b + L.sort, status, s));
     hipLaunchKernelGGL(k_merge_splits, dim3((L.chunks + 256 * kSplitPer) / (256 * kSplitPer), n_ref, 2), dim3(256), 0, s, refs, n_ref, out_s,
                        out_e, L.total, L.chunks, splits);
     hipLaunchKernelGGL(k_merge_count, dim3(L.wgs, L.groups), dim3(kMergeThreads), (size_t)n_q * kWave * 8, s, refs,

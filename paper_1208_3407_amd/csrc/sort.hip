@@ -6,14 +6,15 @@
 // value per key carried along (explicit, or the implicit 0..n-1 input order;
 // the sort is stable, so equal keys keep their input order).  One read of
 // the input counts all four 8-bit digits of every segment; then each pass is
-// a single kernel over tiles of 16384 keys taken in order from a counter:
-// the tile ranks its keys by digit, publishes its digit counts, adds up the
-// counts of the tiles before it in its segment by decoupled look-back (the
-// nearest tile that has published its inclusive prefix ends the walk), and
-// writes its keys out in digit runs.  Every key is read once and written
-// once per pass.  A digit that is constant over every segment is skipped
-// (decided on the device, so the sort never waits for the host).  Inputs
-// are never written.
+// a single kernel over tiles taken in order from a counter: the tile ranks
+// its keys by digit, publishes its digit counts, adds up the counts of the
+// tiles before it in its segment by decoupled look-back (the nearest tile
+// that has published its inclusive prefix ends the walk), and writes its keys
+// out in digit runs.  Every key is read once and written once per pass.  A
+// segment's digits that are constant over it are skipped (each tile reads the
+// segment's four histograms and works out the same schedule, so the sort
+// never waits for the host and needs no launch for it).  Segments that fit
+// one tile are sorted by one workgroup in LDS.  Inputs are never written.
 #include <string.h>
 
 #include <vector>
@@ -28,18 +29,24 @@ constexpr int kThreads = 256;                  // histogram, scan and copy kerne
 constexpr int kWaves = kThreads / kWave;
 constexpr int kSweepThreads = 1024;            // one pass of the sort
 constexpr int kSweepWaves = kSweepThreads / kWave;
-// Keys per wave per tile: 20 rounds of 64 keys held in registers (20480-key
-// tiles) for a keys-only sort; 16 rounds (16384-key tiles) when values ride
-// along, so that keys and values both fit the tile's LDS.
-template <bool VALS>
-struct TileShape {
-    static constexpr uint32_t kPerWave = VALS ? 1024u : 1280u;
-    static constexpr uint32_t kTile = kPerWave * kSweepWaves;
-    static constexpr int kRounds = (int)(kPerWave / kWave);
-};
-__host__ __device__ constexpr uint32_t tile_keys(bool vals) {
-    return vals ? TileShape<true>::kTile : TileShape<false>::kTile;
-}
+// A tile is ROUNDS rounds of 1024 keys held in registers, and a shape is taken
+// from kWant* tiles on.  Few keys want many small tiles: at 20 rounds a tile
+// takes 17 us however idle the chip is (index of 1e5 intervals: 105 us at 20
+// rounds, 48 at 4; of 1e6: 107 at 4, 94 at 12).  Many keys want what two
+// workgroups on a CU hold in 64 registers and 80 KB of LDS each, so that one
+// ranks while the other waits for its loads, its look-back or its stores:
+// index of 5e7 intervals 1738 us at 20 rounds (one workgroup a CU), 1551 at
+// 10, 1446 at 12, 1520 at 14 (spills).  With values along, two workgroups hold
+// 7 rounds (2e6 keys: 166 us at 4 rounds, 150 at 7, 159 at 16; 1e7: 677, 540,
+// 543) until the look-back steps of many tiles cost more (2e7: 1121 at 7, 1040
+// at 16).
+constexpr int kRoundsKeys[2] = {4, 12};
+constexpr uint64_t kWantKeys[2] = {0, 110};
+constexpr int kRoundsVals[3] = {4, 7, 16};
+constexpr uint64_t kWantVals[3] = {0, 200, 730};
+// A segment sorted by one workgroup.  At 16 rounds that takes longer (index of
+// 1.6e4 intervals: 47 us) than small tiles on several CUs (2e4: 42 us).
+constexpr uint32_t kLoneTile = 8u * kSweepThreads;
 // Look-back words, one per (tile, digit): bits 0-31 the count, bits 32-39
 // the pass (1 + p; 0 = not yet published in this call), bit 40 set once the
 // count is the inclusive prefix over the segment's tiles up to this one
@@ -61,21 +68,17 @@ struct SegDesc {
     uint32_t* vping;
     uint32_t* vout;
     uint32_t vmode;   // 0 keys only, 1 values from vin, 2 values = input index
-    uint32_t pad;
+    uint32_t clear;   // status words cleared before the sort
+    uint32_t* status; // gets BITS_FLAG_SORT if a tile gave up its look-back walk (nullable)
 };
-static_assert(sizeof(SegDesc) == 64, "SegDesc layout");
+static_assert(kRoundsKeys[0] == kRoundsVals[0], "smallest tile");
+static_assert(sizeof(SegDesc) == 72, "SegDesc layout");
 
 struct SortPlan {
-    uint32_t active[4];
-    uint32_t src[4];   // 0 = input, 1 = ping, 2 = output
-    uint32_t dst[4];
-    uint32_t n_active;
     uint32_t next_tile[4];   // tile counter of each pass
-    uint32_t error;          // nonzero: a look-back walk gave up (output invalid)
-    uint32_t pad[2];
 };
 
-constexpr int kDescChunk = 48;   // 3 KB of kernel arguments
+constexpr int kDescChunk = 44;   // about 3 KB of kernel arguments
 struct DescChunk {
     SegDesc d[kDescChunk];
 };
@@ -102,31 +105,19 @@ __device__ __forceinline__ uint32_t* vbuf_rw(const SegDesc& d, uint32_t sel) {
     return sel == 1 ? d.vping : d.vout;
 }
 
-// Exclusive scan of one value per thread over a 256-thread block.
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* tmp, uint32_t* total) {
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
+// The sort's setup in one launch: a chunk of descriptors from the kernel
+// arguments into the workspace, the status words the descriptors ask to
+// clear, and with the first chunk the zeros (tile counters, histograms,
+// look-back words) as uint4.
+__global__ void __launch_bounds__(256) k_sort_init(SegDesc* dst, DescChunk chunk, uint32_t count, uint4* zero,
+                                                   uint64_t nzero) {
+    if (blockIdx.x == 0) {
+        for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) dst[i] = chunk.d[i];
+        for (uint32_t i = 0; i < count; ++i)
+            if (threadIdx.x < chunk.d[i].clear) chunk.d[i].status[threadIdx.x] = 0u;
     }
-    if (lane == kWave - 1) tmp[w] = x;
-    __syncthreads();
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-        if (k < w) pre += tmp[k];
-        tot += tmp[k];
-    }
-    __syncthreads();
-    if (total) *total = tot;
-    return pre + x - v;
-}
-
-__global__ void k_write_descs(SegDesc* dst, DescChunk chunk, uint32_t count) {
-    const uint32_t i = threadIdx.x;
-    if (i < count) dst[i] = chunk.d[i];
+    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nzero; k += (uint64_t)gridDim.x * blockDim.x)
+        zero[k] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // All four digit histograms of every segment in one read of the input.
@@ -186,119 +177,43 @@ __global__ void __launch_bounds__(kThreads) k_hist_all(const SegDesc* __restrict
     }
 }
 
-// Block (s, p): exclusive prefix over digits of segment s's pass-p histogram;
-// marks pass p active when the digit takes two or more values in s.
-__global__ void __launch_bounds__(kThreads) k_seg_scan(const uint32_t* __restrict__ seg_hist,
-                                                       uint32_t* __restrict__ seg_pre, SortPlan* plan) {
-    __shared__ uint32_t tmp[kWaves];
-    const uint32_t sp = blockIdx.x;   // s * 4 + p
-    const uint32_t v = seg_hist[(size_t)sp * 256 + threadIdx.x];
-    uint32_t tot = 0;
-    seg_pre[(size_t)sp * 256 + threadIdx.x] = block_excl_scan(v, tmp, &tot);
-    const uint64_t nz = __ballot(v != 0);
-    __shared__ uint32_t nzc[kWaves];
-    if ((threadIdx.x & (kWave - 1)) == 0) nzc[threadIdx.x / kWave] = (uint32_t)__popcll(nz);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t c = 0;
-        for (int k = 0; k < kWaves; ++k) c += nzc[k];
-        if (c >= 2) atomicOr(&plan->active[sp & 3u], 1u);
-    }
-}
-
-// Buffer schedule: the last active pass writes the output, earlier ones
-// alternate so that the first reads the input.
-__global__ void k_plan(SortPlan* plan) {
-    if (threadIdx.x != 0) return;
-    uint32_t na = 0;
-    for (int p = 0; p < 4; ++p) na += plan->active[p] ? 1u : 0u;
-    plan->n_active = na;
-    uint32_t r = 0, prev_dst = 0;
-    for (int p = 0; p < 4; ++p) {
-        if (!plan->active[p]) continue;
-        const uint32_t dst = ((na - 1 - r) % 2 == 0) ? 2u : 1u;
-        plan->src[p] = r == 0 ? 0u : prev_dst;
-        plan->dst[p] = dst;
-        prev_dst = dst;
-        ++r;
-    }
-}
-
 // The look-back word of (tile, digit).
 __device__ __forceinline__ unsigned long long* lb_word(unsigned long long* lb, uint32_t ntiles, uint32_t tile,
                                                       uint32_t dg) {
     return lb + (size_t)tile * 256 + dg;
 }
 
-template <int WAVES>
-__device__ __forceinline__ uint32_t block_excl_scan_n(uint32_t v, uint32_t* tmp) {
+// Exclusive prefix over the first 256 threads of two values at once (the low
+// and the high word of v; neither sum reaches 2^32).  All threads call it.
+__device__ __forceinline__ uint64_t excl_scan_256(uint64_t v, uint64_t* tmp) {
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    uint32_t x = v;
+    uint64_t x = v;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o);
+        const uint64_t y = __shfl_up(x, o);
         if (lane >= o) x += y;
     }
-    if (lane == kWave - 1) tmp[w] = x;
+    if (w < 4 && lane == kWave - 1) tmp[w] = x;
     __syncthreads();
-    uint32_t pre = 0;
+    uint64_t pre = 0;
 #pragma unroll
-    for (int k = 0; k < WAVES; ++k)
+    for (int k = 0; k < 3; ++k)
         if (k < w) pre += tmp[k];
-    __syncthreads();
     return pre + x - v;
 }
 
-// One pass of the sort over one tile (taken from the pass's counter).  Wave
-// w ranks keys [w*kPerWave, (w+1)*kPerWave) of the tile in kRounds rounds; within a
-// round, lanes holding the same digit are found with 8 ballots (each folded
-// into the lane's peer mask by one v_bitop3 per half) and ranked by lane
-// order.  The tile's digit counts are published, the exclusive prefix
-// over the segment's earlier tiles is gathered by look-back (one thread per
-// digit), and the tile, sorted by digit in LDS, is written out in digit runs.
-template <bool VALS>
-__global__ void __launch_bounds__(kSweepThreads) k_onesweep(const SegDesc* __restrict__ descs, uint32_t nseg,
-                                                            SortPlan* plan, int p,
-                                                            unsigned long long* __restrict__ lb, uint32_t ntiles,
-                                                            const uint32_t* __restrict__ seg_pre) {
-    if (!plan->active[p]) return;
-    constexpr uint32_t kPerWave = TileShape<VALS>::kPerWave, kTile = TileShape<VALS>::kTile;
-    constexpr int kRounds = TileShape<VALS>::kRounds;
-    __shared__ uint32_t keys_lds[kTile];
-    __shared__ uint32_t vals_lds[VALS ? kTile : 1];
-    __shared__ uint32_t wcnt[kSweepWaves][256];
-    __shared__ uint32_t dstart[256];
-    __shared__ uint32_t goff[256];
-    __shared__ uint32_t tmp[kSweepWaves];
-    __shared__ uint32_t tile_sh;
-    if (threadIdx.x == 0) tile_sh = atomicAdd(&plan->next_tile[p], 1u);
-    for (int k = threadIdx.x; k < kSweepWaves * 256; k += kSweepThreads) (&wcnt[0][0])[k] = 0;
-    __syncthreads();
-    const uint32_t t = tile_sh;
-    const uint32_t s = seg_of_tile(descs, nseg, t);
-    const SegDesc d = descs[s];
-    const uint32_t begin = (t - d.tile0) * kTile;
-    const uint32_t cnt = min(kTile, d.n - begin);
-    const uint32_t* src = buf_ro(d, plan->src[p]) + begin;
-    uint32_t* dst = buf_rw(d, plan->dst[p]);
-    // values: vmode 2 reads the input index on the first active pass
-    const bool vals = VALS && d.vmode != 0;
-    const bool iota = d.vmode == 2 && plan->src[p] == 0;
-    const uint32_t* vsrc = vals && !iota ? vbuf_ro(d, plan->src[p]) + begin : nullptr;
-    uint32_t* vdst = vals ? vbuf_rw(d, plan->dst[p]) : nullptr;
-    const uint32_t shift = 8u * p;
+// Rank of each of a wave's keys among the keys of its digit seen so far by
+// the wave (register round r holds keys [w ROUNDS + r] 64 .. + 63 of the tile), and in
+// wcnt[w] the wave's digit counts.  Within a round, lanes holding the same
+// digit are found with 8 ballots (each folded into the lane's peer mask by
+// one v_bitop3 per half) and ranked by lane order.
+template <int ROUNDS>
+__device__ __forceinline__ void rank_keys(const uint32_t (&key)[ROUNDS], uint32_t cnt, uint32_t shift,
+                                          uint32_t (*wcnt)[256], uint32_t (&rank)[ROUNDS]) {
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-
-    uint32_t key[kRounds], rank[kRounds];
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const uint32_t idx = (uint32_t)w * kPerWave + (uint32_t)r * kWave + lane;
-        key[r] = idx < cnt ? src[idx] : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const uint32_t idx = (uint32_t)w * kPerWave + (uint32_t)r * kWave + lane;
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
         const bool valid = idx < cnt;
         const uint32_t dg = (key[r] >> shift) & 255u;
         const uint64_t pv = __ballot(valid);
@@ -311,18 +226,96 @@ __global__ void __launch_bounds__(kSweepThreads) k_onesweep(const SegDesc* __res
             plo = __builtin_amdgcn_bitop3_b32(plo, (uint32_t)m, sb, 0x90);
             phi = __builtin_amdgcn_bitop3_b32(phi, (uint32_t)(m >> 32), sb, 0x90);
         }
-        const uint64_t peers = ((uint64_t)phi << 32) | plo;
-        const uint32_t before = (uint32_t)__popcll(peers & lt_mask);
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
         uint32_t old = 0;
         if (valid) old = wcnt[w][dg];
         rank[r] = old + before;
-        if (valid && before == 0) wcnt[w][dg] = old + (uint32_t)__popcll(peers);
+        if (valid && before == 0) wcnt[w][dg] = old + (uint32_t)(__popc(plo) + __popc(phi));
         __builtin_amdgcn_wave_barrier();
     }
+}
+
+// One pass of the sort over one tile (taken from the pass's counter).  Wave
+// w ranks keys [w ROUNDS 64, (w + 1) ROUNDS 64) of the tile.  The tile's digit
+// counts are published, the exclusive prefix over the segment's earlier tiles
+// is gathered by look-back (one thread per digit), and the tile, sorted by
+// digit in LDS, is written out in digit runs.  The last pass copies a segment
+// whose keys are all equal.
+// Eight waves per SIMD (two workgroups a CU) up to 12 rounds.
+template <bool VALS, int ROUNDS>
+__global__ void __launch_bounds__(kSweepThreads, ROUNDS <= 12 ? 8 : 4) k_onesweep(const SegDesc* __restrict__ descs, uint32_t nseg,
+                                                            SortPlan* plan, int p,
+                                                            unsigned long long* __restrict__ lb, uint32_t ntiles,
+                                                            const uint32_t* __restrict__ seg_hist) {
+    constexpr uint32_t kTile = ROUNDS * kSweepThreads;
+    __shared__ uint32_t keys_lds[kTile];
+    __shared__ uint32_t vals_lds[VALS ? kTile : 1];
+    __shared__ uint32_t wcnt[kSweepWaves][256];
+    __shared__ uint32_t dstart[256];
+    __shared__ uint32_t goff[256];
+    __shared__ uint64_t tmp[4];
+    __shared__ uint32_t nzc[kSweepWaves];
+    __shared__ uint32_t tile_sh;
+    if (threadIdx.x == 0) tile_sh = atomicAdd(&plan->next_tile[p], 1u);
+    for (int k = threadIdx.x; k < kSweepWaves * 256; k += kSweepThreads) (&wcnt[0][0])[k] = 0;
+    __syncthreads();
+    const uint32_t t = tile_sh;
+    const uint32_t s = seg_of_tile(descs, nseg, t);
+    const SegDesc d = descs[s];
+    const uint32_t begin = (t - d.tile0) * kTile;
+    const uint32_t cnt = min(kTile, d.n - begin);
+    const uint32_t shift = 8u * p;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const uint32_t dg = threadIdx.x;
+    // The schedule: pass q is active when digit q takes two or more values in the segment;
+    // the last active pass writes the output, earlier ones alternate so that the first
+    // reads the input.  The keys are loaded for the usual case, every pass active, while
+    // the histograms arrive.
+    const uint32_t hv = seg_hist[(size_t)s * 1024 + threadIdx.x];   // digit dg & 255 of pass dg / 256
+    const uint32_t hp = dg < 256 ? seg_hist[((size_t)s * 4 + p) * 256 + dg] : 0u;
+    const uint32_t usual = p == 0 ? 0u : (p & 1) ? 1u : 2u;
+    uint32_t key[ROUNDS], rank[ROUNDS];
+    const uint32_t* src = buf_ro(d, usual) + begin;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
+        key[r] = idx < cnt ? src[idx] : 0u;
+    }
+    const uint64_t nz = __ballot(hv != 0u);
+    if (lane == 0) nzc[w] = (uint32_t)__popcll(nz);
+    __syncthreads();
+    uint32_t act = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (nzc[4 * q] + nzc[4 * q + 1] + nzc[4 * q + 2] + nzc[4 * q + 3] >= 2u) act |= 1u << q;
+    const uint32_t na = (uint32_t)__popc(act), r = (uint32_t)__popc(act & ((1u << p) - 1u));
+    if (!((act >> p) & 1u)) {
+        if (act || p != 3) return;
+        for (uint32_t k = threadIdx.x; k < cnt; k += kSweepThreads) {
+            d.out[begin + k] = d.in[begin + k];
+            if (VALS && d.vmode) d.vout[begin + k] = d.vmode == 2 ? begin + k : d.vin[begin + k];
+        }
+        return;
+    }
+    const uint32_t to = ((na - 1u - r) & 1u) ? 1u : 2u, from = r == 0 ? 0u : 3u - to;
+    if (from != usual) {
+        src = buf_ro(d, from) + begin;
+#pragma unroll
+        for (int k = 0; k < ROUNDS; ++k) {
+            const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)k) * kWave + lane;
+            key[k] = idx < cnt ? src[idx] : 0u;
+        }
+    }
+    uint32_t* dst = buf_rw(d, to);
+    // values: vmode 2 reads the input index on the first active pass
+    const bool vals = VALS && d.vmode != 0;
+    const bool iota = d.vmode == 2 && from == 0;
+    const uint32_t* vsrc = vals && !iota ? vbuf_ro(d, from) + begin : nullptr;
+    uint32_t* vdst = vals ? vbuf_rw(d, to) : nullptr;
+    rank_keys<ROUNDS>(key, cnt, shift, wcnt, rank);
     __syncthreads();
     // per digit: wave offsets within the tile, the tile's count, published at once
     uint32_t tot = 0;
-    const uint32_t dg = threadIdx.x;
     const unsigned long long tag = (unsigned long long)(p + 1) << 32;
     if (dg < 256) {
 #pragma unroll
@@ -334,7 +327,9 @@ __global__ void __launch_bounds__(kSweepThreads) k_onesweep(const SegDesc* __res
         __hip_atomic_store(lb_word(lb, ntiles, t, dg), (d.tile0 == t ? kLbPrefix : 0ull) | tag | tot, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
-    const uint32_t ds = block_excl_scan_n<kSweepWaves>(dg < 256 ? tot : 0u, tmp);
+    // tile offset of the digit (low word) and its first place in the segment (high word)
+    const uint64_t both = excl_scan_256(((uint64_t)hp << 32) | tot, tmp);
+    const uint32_t ds = (uint32_t)both;
     if (dg < 256) {
         // wave offsets become tile offsets: each key then needs one LDS read
         dstart[dg] = ds;
@@ -344,12 +339,12 @@ __global__ void __launch_bounds__(kSweepThreads) k_onesweep(const SegDesc* __res
     __syncthreads();
     // the tile sorted by digit in LDS (needs only tile-local offsets)
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const uint32_t idx = (uint32_t)w * kPerWave + (uint32_t)r * kWave + lane;
+    for (int k = 0; k < ROUNDS; ++k) {
+        const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)k) * kWave + lane;
         if (idx < cnt) {
-            const uint32_t kd = (key[r] >> shift) & 255u;
-            const uint32_t at = wcnt[w][kd] + rank[r];
-            keys_lds[at] = key[r];
+            const uint32_t kd = (key[k] >> shift) & 255u;
+            const uint32_t at = wcnt[w][kd] + rank[k];
+            keys_lds[at] = key[k];
             if constexpr (VALS) {
                 if (vals) vals_lds[at] = iota ? begin + idx : vsrc[idx];
             }
@@ -377,7 +372,7 @@ __global__ void __launch_bounds__(kSweepThreads) k_onesweep(const SegDesc* __res
                     const uint32_t tk = tp - (uint32_t)k;
                     while ((v[k] & (0xFFull << 32)) != tag) {
                         if (++spins > kLbSpinLimit) {
-                            atomicOr(&plan->error, 1u);
+                            if (d.status) atomicOr(d.status, BITS_FLAG_SORT);
                             v[k] = kLbPrefix | tag;
                             break;
                         }
@@ -393,7 +388,7 @@ __global__ void __launch_bounds__(kSweepThreads) k_onesweep(const SegDesc* __res
             __hip_atomic_store(lb_word(lb, ntiles, t, dg), kLbPrefix | tag | (excl + tot), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
-        goff[dg] = seg_pre[((size_t)s * 4 + p) * 256 + dg] + excl;
+        goff[dg] = (uint32_t)(both >> 32) + excl;
     }
     __syncthreads();
     for (uint32_t k = threadIdx.x; k < cnt; k += kSweepThreads) {
@@ -407,62 +402,159 @@ __global__ void __launch_bounds__(kSweepThreads) k_onesweep(const SegDesc* __res
     }
 }
 
-// When no digit varies the input is already sorted (all keys equal): copy.
-__global__ void k_copy_if_idle(const SegDesc* __restrict__ descs, uint32_t nseg, const SortPlan* __restrict__ plan,
-                               uint32_t tile) {
-    if (plan->n_active) return;
-    const uint32_t t = blockIdx.x;
-    const uint32_t s = seg_of_tile(descs, nseg, t);
-    const SegDesc d = descs[s];
-    const uint32_t begin = (t - d.tile0) * tile;
-    const uint32_t cnt = min(tile, d.n - begin);
-    for (uint32_t k = threadIdx.x; k < cnt; k += kThreads) {
-        d.out[begin + k] = d.in[begin + k];
-        if (d.vmode) d.vout[begin + k] = d.vmode == 2 ? begin + k : d.vin[begin + k];
+// A segment of at most ROUNDS * 1024 keys, sorted by one workgroup: the four
+// passes go through LDS.  Workgroup b sorts segment b.
+template <bool VALS, int ROUNDS>
+__global__ void __launch_bounds__(kSweepThreads) k_sort_lone(const SegDesc* __restrict__ descs) {
+    constexpr uint32_t kTile = ROUNDS * kSweepThreads;
+    __shared__ uint32_t keys_lds[kTile];
+    __shared__ uint32_t vals_lds[VALS ? kTile : 1];
+    __shared__ uint32_t wcnt[kSweepWaves][256];
+    __shared__ uint64_t tmp[4];
+    const SegDesc d = descs[blockIdx.x];
+    const uint32_t cnt = d.n, dg = threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const bool vals = VALS && d.vmode != 0;
+    uint32_t key[ROUNDS], val[VALS ? ROUNDS : 1], rank[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
+        key[r] = idx < cnt ? d.in[idx] : 0u;
+        if constexpr (VALS) val[r] = d.vmode == 1 && idx < cnt ? d.vin[idx] : idx;
+    }
+#pragma unroll 1
+    for (uint32_t p = 0; p < 4; ++p) {
+        const uint32_t shift = 8u * p;
+        for (int k = threadIdx.x; k < kSweepWaves * 256; k += kSweepThreads) (&wcnt[0][0])[k] = 0;
+        __syncthreads();
+        rank_keys<ROUNDS>(key, cnt, shift, wcnt, rank);
+        __syncthreads();
+        uint32_t tot = 0;
+        if (dg < 256) {
+#pragma unroll
+            for (int k = 0; k < kSweepWaves; ++k) {
+                const uint32_t c = wcnt[k][dg];
+                wcnt[k][dg] = tot;
+                tot += c;
+            }
+        }
+        const uint32_t ds = (uint32_t)excl_scan_256(tot, tmp);
+        if (dg < 256) {
+#pragma unroll
+            for (int k = 0; k < kSweepWaves; ++k) wcnt[k][dg] += ds;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
+            if (idx < cnt) {
+                const uint32_t at = wcnt[w][(key[r] >> shift) & 255u] + rank[r];
+                keys_lds[at] = key[r];
+                if constexpr (VALS) vals_lds[at] = val[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
+            if (idx < cnt) {
+                key[r] = keys_lds[idx];
+                if constexpr (VALS) val[r] = vals_lds[idx];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
+        if (idx < cnt) {
+            d.out[idx] = key[r];
+            if constexpr (VALS) {
+                if (vals) d.vout[idx] = val[r];
+            }
+        }
     }
 }
 
-// Eytzinger top tree: node k holds keys[tree_rank(k, n) - 1], the last key of
-// the bucket left of its boundary.  The first 2^d - 1 nodes form the depth-d
-// tree for every d <= depth.
-__global__ void k_build_tree(const uint32_t* __restrict__ keys, uint64_t n, uint32_t depth, uint32_t* __restrict__ tree) {
-    const uint32_t m = 1u << depth;
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < m; k += gridDim.x * blockDim.x)
-        tree[k] = k ? keys[tree_rank(k, n) - 1] : 0u;
-}
-
-// Line heads: the first key of every 128-byte line, then +inf padding.
-__global__ void k_build_heads(const uint32_t* __restrict__ keys, uint64_t n, uint64_t hl, uint32_t* __restrict__ heads) {
-    const uint64_t m = (n + 31) / 32;
-    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < hl; j += (uint64_t)gridDim.x * blockDim.x)
-        heads[j] = j < m ? keys[32 * j] : 0xFFFFFFFFu;
+// The rest of reference indexes over their sorted arrays, one launch for up to
+// kFinishRefs references (blockIdx.y): the top trees (node k holds
+// keys[tree_rank(k, n) - 1]; the first 2^d - 1 nodes form the depth-d tree for
+// every d <= depth), 0xFFFFFFFF after the keys up to the end of the last
+// 128-byte line, and unless the learned build writes them the line heads
+// (the first key of every line, then 0xFFFFFFFF).
+__global__ void __launch_bounds__(256) k_finish_refs(FinishChunk F) {
+    const FinishRef R = F.r[blockIdx.y];
+    const uint32_t m = 1u << R.depth, lines = (uint32_t)(((uint64_t)R.n + 31) / 32);
+    const uint32_t hl = R.heads ? (uint32_t)heads_len(R.n) : 0u, tail = (uint32_t)((uint64_t)lines * 32 - R.n);
+    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < 2u * (m + tail + hl); t += gridDim.x * blockDim.x) {
+        if (t < 2u * m) {
+            const uint32_t k = t & (m - 1u);
+            R.tree[t] = k && R.n ? R.k[t < m ? 0 : 1][tree_rank(k, R.n) - 1] : 0u;
+        } else if (t < 2u * (m + tail)) {
+            const uint32_t k = t - 2u * m, a = k >= tail ? 1u : 0u;
+            R.k[a][(uint64_t)R.n + (k - a * tail)] = 0xFFFFFFFFu;
+        } else {
+            const uint32_t k = t - 2u * (m + tail), a = k >= hl ? 1u : 0u, j = k - a * hl;
+            R.heads[k] = j < lines ? R.k[a][32u * (uint64_t)j] : 0xFFFFFFFFu;
+        }
+    }
 }
 
 struct WsLayout {
-    size_t descs, plan, seg_hist, seg_pre, lb, ping, vping, total;
+    size_t descs, plan, seg_hist, lb, zero_end, ping, vping, total;
 };
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-static WsLayout ws_layout(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
-    bool any_vals = false;
-    for (uint32_t s = 0; s < nseg; ++s) any_vals |= vmode && vmode[s];
-    const uint64_t tile = tile_keys(any_vals);
-    uint64_t ntiles = 0, nkeys = 0, nvals = 0;
+// The tile a sort takes, from its segments' sizes.
+struct SortShape {
+    bool vals, lone;   // lone: every segment fits one workgroup
+    int rounds;
+    uint64_t ntiles;
+};
+
+static uint64_t tiles_at(const uint64_t* n, uint32_t nseg, int rounds) {
+    const uint64_t tile = (uint64_t)rounds * kSweepThreads;
+    uint64_t t = 0;
+    for (uint32_t s = 0; s < nseg; ++s) t += (n[s] + tile - 1) / tile;
+    return t;
+}
+
+static SortShape sort_shape(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
+    SortShape S{false, true, 0, 0};
+    uint64_t most = 0;
     for (uint32_t s = 0; s < nseg; ++s) {
-        ntiles += (n[s] + tile - 1) / tile;
+        S.vals |= vmode && vmode[s];
+        most = n[s] > most ? n[s] : most;
+    }
+    S.lone = most <= kLoneTile;
+    const int* R = S.vals ? kRoundsVals : kRoundsKeys;
+    const uint64_t* want = S.vals ? kWantVals : kWantKeys;
+    int k = S.vals ? 2 : 1;
+    while (k > 0 && tiles_at(n, nseg, R[k]) < want[k]) --k;
+    S.rounds = R[k];
+    if (S.lone) S.rounds = most <= 4u * kSweepThreads ? 4 : 8;
+    S.ntiles = tiles_at(n, nseg, S.rounds);
+    return S;
+}
+
+static WsLayout ws_layout(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
+    const SortShape S = sort_shape(n, nseg, vmode);
+    uint64_t nkeys = 0, nvals = 0;
+    for (uint32_t s = 0; s < nseg; ++s) {
         nkeys += n[s];
         if (vmode && vmode[s]) nvals += n[s];
     }
     WsLayout L;
     size_t o = 0;
-    L.plan = o; o = align256(o + sizeof(SortPlan));   // first: launch_sort_report finds it at 0
+    // cleared by the first launch: [plan, zero_end)
+    L.plan = o; o = align256(o + sizeof(SortPlan));
+    L.seg_hist = o; o = align256(o + (S.lone ? 0 : (size_t)nseg * 1024 * 4));
+    // room for the smallest tiles, so that fewer segments of the same sizes never need more
+    L.lb = o; o = align256(o + (S.lone ? 0 : (size_t)tiles_at(n, nseg, kRoundsKeys[0]) * 256 * 8));
+    L.zero_end = S.lone ? L.lb : L.lb + (size_t)S.ntiles * 256 * 8;
     L.descs = o; o = align256(o + sizeof(SegDesc) * nseg);
-    L.seg_hist = o; o = align256(o + (size_t)nseg * 1024 * 4);
-    L.seg_pre = o; o = align256(o + (size_t)nseg * 1024 * 4);
-    L.lb = o; o = align256(o + (size_t)ntiles * 256 * 8);
-    L.ping = o; o = align256(o + (size_t)nkeys * 4);
-    L.vping = o; o = align256(o + (size_t)nvals * 4);
+    L.ping = o; o = align256(o + (S.lone ? 0 : (size_t)nkeys * 4));
+    L.vping = o; o = align256(o + (S.lone ? 0 : (size_t)nvals * 4));
     L.total = o;
     return L;
 }
@@ -471,6 +563,14 @@ static WsLayout ws_layout(const uint64_t* n, uint32_t nseg, const uint32_t* vmod
 
 size_t sort_workspace_bytes(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
     return ws_layout(n, nseg, vmode).total;
+}
+
+template <bool VALS, int ROUNDS>
+static void launch_passes(const SegDesc* descs, uint32_t nseg, SortPlan* plan, unsigned long long* lb, uint32_t ntiles,
+                          const uint32_t* seg_hist, hipStream_t s) {
+    for (int p = 0; p < 4; ++p)
+        hipLaunchKernelGGL((k_onesweep<VALS, ROUNDS>), dim3(ntiles), dim3(kSweepThreads), 0, s, descs, nseg, plan, p, lb,
+                           ntiles, seg_hist);
 }
 
 int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, hipStream_t s) {
@@ -483,15 +583,13 @@ int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, h
         vm[i] = segs[i].vmode;
     }
     const WsLayout L = ws_layout(ns.data(), nseg, vm.data());
-    bool any_vals = false;
-    for (uint32_t i = 0; i < nseg; ++i) any_vals |= vm[i] != 0;
-    const uint32_t tile = tile_keys(any_vals);
+    const SortShape S = sort_shape(ns.data(), nseg, vm.data());
+    const uint32_t tile = (uint32_t)S.rounds * kSweepThreads;
     if (ws_bytes < L.total) return BITS_E_WORKSPACE;
     char* base = (char*)ws;
     SegDesc* descs = (SegDesc*)(base + L.descs);
     SortPlan* plan = (SortPlan*)(base + L.plan);
     uint32_t* seg_hist = (uint32_t*)(base + L.seg_hist);
-    uint32_t* seg_pre = (uint32_t*)(base + L.seg_pre);
     unsigned long long* lb = (unsigned long long*)(base + L.lb);
     uint32_t* ping = (uint32_t*)(base + L.ping);
     uint32_t* vping = (uint32_t*)(base + L.vping);
@@ -512,6 +610,8 @@ int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, h
             ch.d[i].n = (uint32_t)g.n;
             ch.d[i].tile0 = tile0;
             ch.d[i].vmode = g.vmode;
+            ch.d[i].status = g.status;
+            ch.d[i].clear = g.clear;
             if (g.vmode) {
                 ch.d[i].vin = g.vmode == 1 ? g.vin : nullptr;
                 ch.d[i].vping = vping + voff;
@@ -521,57 +621,56 @@ int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, h
             tile0 += (uint32_t)((g.n + tile - 1) / tile);
             koff += g.n;
         }
-        hipLaunchKernelGGL(k_write_descs, dim3(1), dim3(128), 0, s, descs + c0, ch, cnt);
+        const uint64_t nzero = c0 == 0 && !S.lone ? (L.zero_end - L.plan) / 16 : 0;
+        const uint64_t gz = (nzero + 255) / 256;
+        hipLaunchKernelGGL(k_sort_init, dim3((uint32_t)(gz < 1 ? 1 : gz > 2048 ? 2048 : gz)), dim3(256), 0, s,
+                           descs + c0, ch, cnt, (uint4*)(base + L.plan), nzero);
     }
     const uint32_t ntiles = tile0;
-    BITS_CHECK_HIP(launch_fill_u32((uint32_t*)plan, sizeof(SortPlan) / 4, 0u, s));
-    BITS_CHECK_HIP(launch_fill_u32(seg_hist, (uint64_t)nseg * 1024, 0u, s));
     if (ntiles == 0) {
         BITS_CHECK_HIP(hipGetLastError());
         return BITS_OK;
     }
-
-    BITS_CHECK_HIP(launch_fill_u64(lb, (uint64_t)ntiles * 256, 0ull, s));
+    if (S.lone) {
+        if (S.vals && S.rounds == 4)
+            hipLaunchKernelGGL((k_sort_lone<true, 4>), dim3(nseg), dim3(kSweepThreads), 0, s, descs);
+        else if (S.vals)
+            hipLaunchKernelGGL((k_sort_lone<true, 8>), dim3(nseg), dim3(kSweepThreads), 0, s, descs);
+        else if (S.rounds == 4)
+            hipLaunchKernelGGL((k_sort_lone<false, 4>), dim3(nseg), dim3(kSweepThreads), 0, s, descs);
+        else
+            hipLaunchKernelGGL((k_sort_lone<false, 8>), dim3(nseg), dim3(kSweepThreads), 0, s, descs);
+        BITS_CHECK_HIP(hipGetLastError());
+        return BITS_OK;
+    }
     const uint32_t hg = ntiles < 2048u ? ntiles : 2048u;
     hipLaunchKernelGGL(k_hist_all, dim3(hg), dim3(kThreads), 0, s, descs, nseg, ntiles, tile, seg_hist);
-    hipLaunchKernelGGL(k_seg_scan, dim3(nseg * 4), dim3(kThreads), 0, s, seg_hist, seg_pre, plan);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(64), 0, s, plan);
-    for (int p = 0; p < 4; ++p) {
-        if (any_vals)
-            hipLaunchKernelGGL(k_onesweep<true>, dim3(ntiles), dim3(kSweepThreads), 0, s, descs, nseg, plan, p, lb,
-                               ntiles, seg_pre);
-        else
-            hipLaunchKernelGGL(k_onesweep<false>, dim3(ntiles), dim3(kSweepThreads), 0, s, descs, nseg, plan, p, lb,
-                               ntiles, seg_pre);
+    if (S.vals) {
+        if (S.rounds == kRoundsVals[0]) launch_passes<true, kRoundsVals[0]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
+        else if (S.rounds == kRoundsVals[1]) launch_passes<true, kRoundsVals[1]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
+        else launch_passes<true, kRoundsVals[2]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
+    } else {
+        if (S.rounds == kRoundsKeys[0]) launch_passes<false, kRoundsKeys[0]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
+        else launch_passes<false, kRoundsKeys[1]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
     }
-    hipLaunchKernelGGL(k_copy_if_idle, dim3(ntiles), dim3(kThreads), 0, s, descs, nseg, plan, tile);
     BITS_CHECK_HIP(hipGetLastError());
     return BITS_OK;
 }
 
-// Ors BITS_FLAG_SORT into *status if the last sort in ws gave up a look-back.
-__global__ void k_sort_report(const SortPlan* plan, uint32_t* status) {
-    if (threadIdx.x == 0 && plan->error) atomicOr(status, BITS_FLAG_SORT);
-}
-
-hipError_t launch_sort_report(const void* ws, uint32_t* status, hipStream_t s) {
-    hipLaunchKernelGGL(k_sort_report, dim3(1), dim3(64), 0, s,
-                       reinterpret_cast<const SortPlan*>(ws), status);
-    return hipGetLastError();
-}
-
-hipError_t launch_build_tree(const uint32_t* keys, uint64_t n, uint32_t depth, uint32_t* tree, hipStream_t s) {
-    const uint32_t m = 1u << depth;
-    const uint32_t g = (m + 255) / 256;
-    hipLaunchKernelGGL(k_build_tree, dim3(g), dim3(256), 0, s, keys, n, depth, tree);
-    return hipGetLastError();
-}
-
-hipError_t launch_build_heads(const uint32_t* keys, uint64_t n, uint32_t* heads, hipStream_t s) {
-    const uint64_t hl = heads_len(n);
-    uint64_t g = (hl + 255) / 256;
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(k_build_heads, dim3((uint32_t)g), dim3(256), 0, s, keys, n, hl, heads);
+hipError_t launch_finish_refs(const FinishRef* refs, uint32_t n_ref, hipStream_t s) {
+    for (uint32_t j0 = 0; j0 < n_ref; j0 += kFinishRefs) {
+        FinishChunk F;
+        memset(&F, 0, sizeof(F));
+        const uint32_t cnt = n_ref - j0 < kFinishRefs ? n_ref - j0 : kFinishRefs;
+        uint64_t most = 0;
+        for (uint32_t i = 0; i < cnt; ++i) {
+            F.r[i] = refs[j0 + i];
+            const uint64_t words = (2ull << refs[j0 + i].depth) + 64 + (refs[j0 + i].heads ? 2 * heads_len(refs[j0 + i].n) : 0);
+            most = words > most ? words : most;
+        }
+        const uint64_t g = (most + 255) / 256;
+        hipLaunchKernelGGL(k_finish_refs, dim3((uint32_t)(g < 4096 ? g : 4096), cnt), dim3(256), 0, s, F);
+    }
     return hipGetLastError();
 }
 

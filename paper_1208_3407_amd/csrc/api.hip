@@ -393,8 +393,7 @@ int mc_pvalue_impl(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
     hipStream_t s = (hipStream_t)stream;
     auto* totals = (unsigned long long*)d_totals;
     auto* obs = (unsigned long long*)d_observed;
-    BITS_CHECK_HIP(launch_fill_u64(totals, ns, 0ull, s));
-    BITS_CHECK_HIP(launch_fill_u64(obs, 1, 0ull, s));
+    if (!(na && ref->n)) BITS_CHECK_HIP(launch_mc_zero(totals, ns, obs, nullptr, s));
     if (na && ref->n) {
         const size_t stride = align256((size_t)na * sizeof(uint32_t));
         const size_t cstride = align256(BITS_MAX_CHROM * sizeof(uint32_t));
@@ -406,7 +405,8 @@ int mc_pvalue_impl(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
         tab.idx = (uint32_t*)(w + 3 * stride);
         tab.hist = (uint32_t*)(w + 4 * stride);
         tab.cursor = (uint32_t*)(w + 4 * stride + cstride);
-        BITS_CHECK_HIP(launch_mc_prepare(d_a_start, d_a_end, na, chrom_len, n_chrom, tab, ref->status, s));
+        BITS_CHECK_HIP(launch_mc_zero(totals, ns, obs, &tab, s));
+        BITS_CHECK_HIP(launch_mc_prepare(d_a_start, d_a_end, na, chrom_len, n_chrom, tab, nullptr, ref->status, s));
         BITS_CHECK_HIP(launch_mc(make_search_args(ref, cfg), cfg, d_a_start, d_a_end, tab, na, seed, s0, ns, totals,
                                  obs, s));
     }
@@ -521,7 +521,7 @@ int bits_mc_binned_stage_ms(float* ms) {
 namespace {
 struct BinWsLayout {
     BinLayout L;
-    size_t table, rs, re, flag, offsets, tiles, cell_region, desc, seg_start, seg_cnt, partial, packed, recs, total;
+    size_t table, rs, re, nreg, cell_region, desc, seg_start, seg_cnt, partial, packed, recs, total;
 };
 
 bool bin_ws_layout(uint64_t na, uint64_t n, const uint32_t* chrom_len, uint32_t n_chrom, uint32_t batch,
@@ -533,9 +533,12 @@ bool bin_ws_layout(uint64_t na, uint64_t n, const uint32_t* chrom_len, uint32_t 
     o += 4 * align256((size_t)na * sizeof(uint32_t)) + 2 * align256(BITS_MAX_CHROM * sizeof(uint32_t));
     W->rs = o; o = align256(o + nc * sizeof(uint32_t));
     W->re = o; o = align256(o + nc * sizeof(uint32_t));
-    W->flag = o; o = align256(o + nc * sizeof(uint32_t));
-    W->offsets = o; o = align256(o + (nc + 1) * sizeof(uint64_t));
-    W->tiles = o; o = align256(o + scan_tiles(nc) * sizeof(uint64_t));
+    // 12 bytes per cell of which one word is used: the size stays what the header
+    // states and callers may have laid out
+    W->nreg = o;
+    o = align256(o + nc * sizeof(uint32_t));
+    o = align256(o + (nc + 1) * sizeof(uint64_t));
+    o = align256(o + scan_tiles(nc) * sizeof(uint64_t));
     W->cell_region = o; o = align256(o + nc * sizeof(uint32_t));
     W->desc = o; o = align256(o + (nr + 1) * 16);
     W->seg_start = o; o = align256(o + (size_t)batch * nr * sizeof(uint32_t));
@@ -584,8 +587,7 @@ int bits_mc_binned(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
     hipStream_t s = (hipStream_t)stream;
     auto* totals = (unsigned long long*)d_totals;
     auto* obs = (unsigned long long*)d_observed;
-    BITS_CHECK_HIP(launch_fill_u64(totals, ns, 0ull, s));
-    BITS_CHECK_HIP(launch_fill_u64(obs, 1, 0ull, s));
+    if (!(na && ref->n)) BITS_CHECK_HIP(launch_mc_zero(totals, ns, obs, nullptr, s));
     if (na && ref->n) {
         char* w = (char*)d_ws;
         const size_t stride = align256((size_t)na * sizeof(uint32_t));
@@ -600,9 +602,7 @@ int bits_mc_binned(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
         BinWs bw;
         bw.rs = (uint32_t*)(w + W.rs);
         bw.re = (uint32_t*)(w + W.re);
-        bw.flag = (uint32_t*)(w + W.flag);
-        bw.offsets = (uint64_t*)(w + W.offsets);
-        bw.scan_tiles = (uint64_t*)(w + W.tiles);
+        bw.nreg = (uint64_t*)(w + W.nreg);
         bw.cell_region = (uint32_t*)(w + W.cell_region);
         bw.desc = w + W.desc;
         bw.seg_start = (uint32_t*)(w + W.seg_start);
@@ -612,13 +612,12 @@ int bits_mc_binned(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
         bw.packed = w + W.packed;
         bw.nreg_max = (uint32_t)W.L.nreg_max;
         bw.splits = W.L.splits;
-        BITS_CHECK_HIP(launch_mc_prepare(d_a_start, d_a_end, na, chrom_len, n_chrom, tab, ref->status, s));
+        BITS_CHECK_HIP(launch_mc_zero(totals, ns, obs, &tab, s));
+        BITS_CHECK_HIP(launch_mc_prepare(d_a_start, d_a_end, na, chrom_len, n_chrom, tab, bw.packed, ref->status, s));
         BITS_CHECK_HIP(launch_mc(make_search_args(ref, cfg), cfg, d_a_start, d_a_end, tab, na, seed, s0, 0, totals,
                                  obs, s));
-        if (W.L.ncells && ns) {   // a genome of length 0 holds no legal placement
+        if (W.L.ncells && ns)   // a genome of length 0 holds no legal placement
             BITS_CHECK_HIP(launch_bin_regions(chrom_len, n_chrom, ref->bs, ref->be, ref->n, bw, ref->status, s));
-            BITS_CHECK_HIP(launch_bin_pack(tab, na, bw, s));
-        }
         BinTiming& tm = bin_timing();
         std::unique_lock<std::mutex> tl(tm.mu);
         tm.used = 0;
@@ -807,8 +806,7 @@ int bits_mc_resort(const uint32_t* d_a_start, const uint32_t* d_a_end, uint64_t 
     hipStream_t s = (hipStream_t)stream;
     auto* totals = (unsigned long long*)d_totals;
     auto* obs = (unsigned long long*)d_observed;
-    BITS_CHECK_HIP(launch_fill_u64(totals, ns, 0ull, s));
-    BITS_CHECK_HIP(launch_fill_u64(obs, 1, 0ull, s));
+    if (!(nb && na)) BITS_CHECK_HIP(launch_mc_zero(totals, ns, obs, nullptr, s));
     if (nb && na) {
         char* w = (char*)d_ws;
         const size_t col = align256((size_t)nb * sizeof(uint32_t)), cstride = align256(BITS_MAX_CHROM * 4);
@@ -827,7 +825,8 @@ int bits_mc_resort(const uint32_t* d_a_start, const uint32_t* d_a_end, uint64_t 
         const size_t sort_bytes = W.total - W.sort;
         // B's per-interval table (chromosome offset, legal starts, length, index), computed once
         uint32_t* status = d_status ? d_status : (uint32_t*)(w + W.status);
-        BITS_CHECK_HIP(launch_mc_prepare(d_b_start, d_b_end, nb, chrom_len, n_chrom, tab, status, s));
+        BITS_CHECK_HIP(launch_mc_zero(totals, ns, obs, &tab, s));
+        BITS_CHECK_HIP(launch_mc_prepare(d_b_start, d_b_end, nb, chrom_len, n_chrom, tab, nullptr, status, s));
         // the sort leaves the words between two rounds alone; the searches read them as +inf
         BITS_CHECK_HIP(launch_fill_tails(S_out, E_out, nb, W.stride, (uint32_t)std::min<uint64_t>(batch, std::max<uint64_t>(ns, 1)), s));
         auto run = [&](uint64_t first, uint32_t rounds, bool identity, unsigned long long* out) -> int {

@@ -163,7 +163,8 @@ __device__ uint32_t block_scan_u32(uint32_t* h, uint32_t m, uint32_t* wsum) {
     return tot;
 }
 
-// Ranks of every cell's first coordinate in B_S and B_E.
+// Ranks of every cell's first coordinate in B_S and B_E, both bisections in
+// step so that their dependent loads overlap.
 __global__ void __launch_bounds__(256) k_bin_cells(BinGeom g, const uint32_t* __restrict__ bs,
                                                    const uint32_t* __restrict__ be, uint32_t n,
                                                    uint32_t* __restrict__ rs, uint32_t* __restrict__ re) {
@@ -171,60 +172,106 @@ __global__ void __launch_bounds__(256) k_bin_cells(BinGeom g, const uint32_t* __
     for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncells; c += gridDim.x * blockDim.x) {
         const uint32_t k = chrom_of_cell(g, c);
         const uint32_t lo = g.off[k] + ((c - g.cb[k]) << g.shift);
-        rs[c] = rank_in<true>(bs, n, lo);
-        re[c] = rank_in<true>(be, n, lo);
+        uint32_t b0 = 0, b1 = 0, len = n;   // n > 0
+        while (len > 1) {
+            const uint32_t half = len >> 1;
+            const uint32_t k0 = bs[b0 + half], k1 = be[b1 + half];
+            if (k0 < lo) b0 += half;
+            if (k1 < lo) b1 += half;
+            len -= half;
+        }
+        rs[c] = b0 + (bs[b0] < lo);
+        re[c] = b1 + (be[b1] < lo);
     }
 }
 
-// flag[c] = 1 where a region starts: the first cell of a chromosome, or the
-// merged count since the chromosome's start enters a new multiple of kRegionKeys.
-__global__ void __launch_bounds__(256) k_bin_flags(BinGeom g, const uint32_t* __restrict__ rs,
-                                                   const uint32_t* __restrict__ re, uint32_t* __restrict__ flag) {
-    const uint32_t ncells = g.cb[g.n_chrom];
-    for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncells; c += gridDim.x * blockDim.x) {
-        const uint32_t k = chrom_of_cell(g, c), c0 = g.cb[k];
-        uint32_t f = 1u;
-        if (c != c0) {
-            const uint64_t base = (uint64_t)rs[c0] + re[c0];
-            const uint64_t p = (uint64_t)rs[c] + re[c] - base, q = (uint64_t)rs[c - 1] + re[c - 1] - base;
-            f = (p / kRegionKeys) != (q / kRegionKeys) ? 1u : 0u;
-        }
-        flag[c] = f;
+// Regions of one chromosome per workgroup.  A region starts at the
+// chromosome's first cell and wherever the merged count since the chromosome's
+// start enters a new multiple of kRegionKeys.  Chromosome k's regions take the
+// numbers from sum over k' < k of bound(k') on, bound = min(cells, keys /
+// kRegionKeys + 1) being the most it can have, so that no scan over
+// chromosomes is needed; the numbers it leaves unused are empty regions at its
+// end.  Writes cell -> region, the descriptors, and with the last chromosome
+// the sentinel {genome size, n, n} and the number of regions.
+__global__ void __launch_bounds__(kBinThreads) k_bin_regions(BinGeom g, const uint32_t* __restrict__ rs,
+                                                             const uint32_t* __restrict__ re, uint32_t n,
+                                                             uint32_t nreg_max, uint32_t* __restrict__ cell_region,
+                                                             RegionDesc* __restrict__ desc, uint64_t* nreg,
+                                                             uint32_t* status) {
+    constexpr uint32_t kPer = kMaxCells / kBinThreads, kWaves = kBinThreads / kWave;
+    __shared__ uint32_t found[kPer * kWaves], wsum[kWaves], sh_total;
+    const uint32_t k = blockIdx.x, c0 = g.cb[k], nc = g.cb[k + 1] - c0, ncells = g.cb[g.n_chrom];
+    if (nc == 0) return;
+    const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    auto merged = [&](uint32_t c) -> uint64_t { return c < ncells ? (uint64_t)rs[c] + re[c] : 2ull * n; };
+    auto bound = [&](uint32_t q) -> uint32_t {
+        const uint32_t a = g.cb[q], m = g.cb[q + 1] - a;
+        return m ? (uint32_t)min((uint64_t)m, (merged(a + m) - merged(a)) / kRegionKeys + 1u) : 0u;
+    };
+    const uint64_t base = merged(c0);
+    // thread t holds cells t, t + 1024, ...; all loads (indices clamped) are in flight together
+    uint32_t r_s[kPer], r_e[kPer];
+    uint64_t prev[kPer];
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+        const uint32_t c = min(u * kBinThreads + threadIdx.x, nc - 1u);
+        r_s[u] = rs[c0 + c];
+        r_e[u] = re[c0 + c];
+        prev[u] = merged(c0 + (c ? c - 1u : 0u));
     }
-}
-
-// cell -> region (offsets = exclusive scan of the flags), region descriptors,
-// and the sentinel after the last region: {genome size, n, n}.
-__global__ void __launch_bounds__(256) k_bin_regions(BinGeom g, const uint32_t* __restrict__ rs,
-                                                     const uint32_t* __restrict__ re,
-                                                     const uint32_t* __restrict__ flag,
-                                                     const uint64_t* __restrict__ offsets, uint32_t n,
-                                                     uint32_t nreg_max, uint32_t* __restrict__ cell_region,
-                                                     RegionDesc* __restrict__ desc, uint32_t* status) {
-    const uint32_t ncells = g.cb[g.n_chrom];
-    for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncells; c += gridDim.x * blockDim.x) {
-        uint32_t rid = (uint32_t)(offsets[c + 1] - 1u);
-        if (rid >= nreg_max) {          // cannot happen (nreg_max bounds the count); never index past it
-            atomicOr(status, BITS_FLAG_CHROM);
-            rid = nreg_max - 1u;
-        }
-        cell_region[c] = rid;
-        if (flag[c]) {
-            const uint32_t k = chrom_of_cell(g, c);
-            desc[rid] = RegionDesc{g.off[k] + ((c - g.cb[k]) << g.shift), rs[c], re[c], 0u};
-        }
-        if (c == ncells - 1) desc[rid + 1] = RegionDesc{g.off[g.n_chrom], n, n, 0u};   // desc has nreg_max + 1
+    uint32_t before = threadIdx.x < k ? bound(threadIdx.x) : 0u;
+    uint64_t starts[kPer];   // the wave's cells that start a region
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+        const uint32_t c = u * kBinThreads + threadIdx.x;
+        const uint64_t m = ((uint64_t)r_s[u] + r_e[u] - base) / kRegionKeys, q = (prev[u] - base) / kRegionKeys;
+        starts[u] = __ballot(c < nc && (c == 0u || m != q));
+        if (lane == 0) found[u * kWaves + w] = (uint32_t)__popcll(starts[u]);
     }
-}
-
-// The per-query table the binning kernel reads: {input index, length}, the
-// length 0 for a query outside its chromosome (span 0).  A query's legal
-// starts follow from its chromosome's length: span = len_k - L + 1.
-__global__ void __launch_bounds__(256) k_bin_pack(const uint32_t* __restrict__ span, const uint32_t* __restrict__ len,
-                                                  const uint32_t* __restrict__ idx, uint64_t na,
-                                                  uint2* __restrict__ packed) {
-    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < na; p += (uint64_t)gridDim.x * blockDim.x)
-        packed[p] = make_uint2(idx[p], span[p] ? len[p] : 0u);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) before += __shfl_xor(before, o);
+    if (lane == 0) wsum[w] = before;
+    __syncthreads();
+    if (w == 0) {   // exclusive prefix of the 128 counts, two a lane
+        static_assert(kPer * kWaves == 2 * kWave, "one wave scans the counts");
+        const uint32_t a = found[2 * lane], b = found[2 * lane + 1];
+        uint32_t x = a + b;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o);
+            if (lane >= (uint32_t)o) x += y;
+        }
+        found[2 * lane] = x - a - b;
+        found[2 * lane + 1] = x - b;
+        if (lane == kWave - 1) sh_total = x;
+    }
+    __syncthreads();
+    uint32_t first = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) first += wsum[j];   // at most 256 chromosomes before this one
+    const uint32_t total = sh_total, most = bound(k);
+    if ((first + most > nreg_max || total > most) && threadIdx.x == 0)   // only for unsorted arrays;
+        atomicOr(status, BITS_FLAG_CHROM);                               // never index past the table
+#pragma unroll
+    for (uint32_t u = 0; u < kPer; ++u) {
+        const uint32_t c = u * kBinThreads + threadIdx.x;
+        if (c >= nc) continue;
+        // the region of cell c: as many as started up to it, less one
+        const uint32_t rid = first + found[u * kWaves + w] + (uint32_t)__popcll(starts[u] & (~0ull >> (63 - lane))) - 1u;
+        if (((starts[u] >> lane) & 1u) && rid < nreg_max)
+            desc[rid] = RegionDesc{g.off[k] + (c << g.shift), r_s[u], r_e[u], 0u};
+        cell_region[c0 + c] = min(rid, nreg_max - 1u);
+    }
+    // the unused numbers: empty regions where the next chromosome starts
+    const uint32_t next = c0 + nc;
+    const RegionDesc end = next < ncells ? RegionDesc{g.off[k + 1], rs[next], re[next], 0u}
+                                         : RegionDesc{g.off[g.n_chrom], n, n, 0u};
+    for (uint32_t r = first + total + threadIdx.x; r < min(first + most, nreg_max); r += kBinThreads) desc[r] = end;
+    if (next == ncells && threadIdx.x == 0) {
+        const uint32_t all = min(first + most, nreg_max);
+        desc[all] = end;   // desc has nreg_max + 1
+        *nreg = all;
+    }
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave, moving data between lanes
@@ -286,10 +333,15 @@ __device__ __forceinline__ uint32_t half16(const uint32_t* w, uint32_t j) {
 // group that fits one chunk is placed only once: its chunk's region counts
 // are the segment table and the chunk is its final layout.
 // (8 waves per SIMD: two workgroups per CU, at most 64 VGPRs.)
+// LOOKUP, for fewer queries than half the genome's cells: such a group reads a
+// placement's region from memory and leaves the LDS table, a load per cell,
+// out (2000 queries x 100 shuffles: 25.3 -> 22.2 us; as a branch in one kernel
+// it costs 1e5 x 2000 1%).
+template <bool LOOKUP>
 __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     BinGeom g, const uint2* __restrict__ packed, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ cursor,
     uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, const uint32_t* __restrict__ cell_region,
-    const uint64_t* __restrict__ offsets, uint32_t nreg_max, uint32_t* __restrict__ seg_start,
+    const uint64_t* __restrict__ nreg_p, uint32_t nreg_max, uint32_t* __restrict__ seg_start,
     uint32_t* __restrict__ seg_cnt, uint2* __restrict__ recs) {
     __shared__ uint16_t cr[kMaxCells];
     __shared__ uint32_t hs[kStageRegions];          // segment cursors (staged path)
@@ -301,7 +353,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     const uint32_t k = blockIdx.x / nb, s = blockIdx.x - k * nb;
     const uint32_t c0 = g.cb[k], nc = g.cb[k + 1] - c0;
     if (nc == 0) return;
-    const uint32_t nreg = (uint32_t)offsets[g.cb[g.n_chrom]];
+    const uint32_t nreg = (uint32_t)*nreg_p;
     const uint32_t rb = cell_region[c0];
     const uint32_t rl = (k + 1 < g.n_chrom && g.cb[k + 1] < g.cb[g.n_chrom]) ? cell_region[g.cb[k + 1]] : nreg;
     const uint32_t nr = rl > rb ? min(min(rl - rb, nc), nreg_max - rb) : 0u;
@@ -309,10 +361,13 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     // record lines); with few regions the direct writes already merge in L2
     const bool staged = nr >= kStageMinRegions && nr <= kStageRegions;
     uint32_t* h = staged ? hs : reinterpret_cast<uint32_t*>(stage);   // kMaxCells words fit the stage buffer
-    for (uint32_t j = threadIdx.x; j < nc; j += blockDim.x) cr[j] = (uint16_t)(cell_region[c0 + j] - rb);
-    for (uint32_t j = threadIdx.x; j < nr; j += blockDim.x) h[j] = 0u;
-    __syncthreads();
     const uint32_t g1 = cursor[k], g0 = g1 - hist[k];
+    const bool lookup = LOOKUP && g1 - g0 <= kStageRecs && nr <= kStageRegions;
+    if (!lookup) {
+        for (uint32_t j = threadIdx.x; j < nc; j += blockDim.x) cr[j] = (uint16_t)(cell_region[c0 + j] - rb);
+        for (uint32_t j = threadIdx.x; j < nr; j += blockDim.x) h[j] = 0u;
+        __syncthreads();
+    }
     const uint32_t ok = g.off[k], sh = g.shift, clen = g.off[k + 1] - g.off[k];
     const uint64_t gs = (sb + s) * na;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -325,22 +380,28 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
         if (owner) cc[threadIdx.x] = 0u;
         __syncthreads();
         uint32_t st_[kStagePer], len_[kStagePer], key_[kStagePer];   // key = lr << 16 | rank, or ~0
+        auto place = [&](auto region_of) {
 #pragma unroll
-        for (int u = 0; u < kStagePer; ++u) {
-            const uint32_t p = g0 + threadIdx.x + (uint32_t)u * blockDim.x;
-            const uint2 q = p < g1 ? packed[p] : make_uint2(0u, 0u);
-            key_[u] = 0xFFFFFFFFu;
-            st_[u] = 0u;
-            len_[u] = q.y;
-            if (!q.y) continue;
-            const uint32_t st = mc_place(gs + q.x, k0, k1, ok, clen - q.y + 1u);
-            const uint32_t lr = cr[(st - ok) >> sh];
-            if (lr >= nr) continue;
-            const uint32_t sft = 16u * (lr & 1u);
-            const uint32_t old = atomicAdd(&cc[lr >> 1], 1u << sft);
-            st_[u] = st;
-            key_[u] = (lr << 16) | ((old >> sft) & 0xFFFFu);
-        }
+            for (int u = 0; u < kStagePer; ++u) {
+                const uint32_t p = g0 + threadIdx.x + (uint32_t)u * blockDim.x;
+                const uint2 q = p < g1 ? packed[p] : make_uint2(0u, 0u);
+                key_[u] = 0xFFFFFFFFu;
+                st_[u] = 0u;
+                len_[u] = q.y;
+                if (!q.y) continue;
+                const uint32_t st = mc_place(gs + q.x, k0, k1, ok, clen - q.y + 1u);
+                const uint32_t lr = region_of((st - ok) >> sh);
+                if (lr >= nr) continue;
+                const uint32_t sft = 16u * (lr & 1u);
+                const uint32_t old = atomicAdd(&cc[lr >> 1], 1u << sft);
+                st_[u] = st;
+                key_[u] = (lr << 16) | ((old >> sft) & 0xFFFFu);
+            }
+        };
+        if (LOOKUP)
+            place([&](uint32_t cell) { return cell_region[c0 + cell] - rb; });
+        else
+            place([&](uint32_t cell) { return (uint32_t)cr[cell]; });
         __syncthreads();
         {
             const uint32_t wv = owner ? cc[threadIdx.x] : 0u;
@@ -661,6 +722,12 @@ __global__ void __launch_bounds__(kBinThreads) k_bin_search(
         }
         if (threadIdx.x == nb - 1) pre[nb] = before + x;
     }
+    __syncthreads();
+    if (pre[nb] == 0u) {   // no placement starts here (uniform)
+        if (threadIdx.x < nb)
+            partial[(SPLIT ? (uint64_t)r * splits + part : (uint64_t)r) * nb + threadIdx.x] = 0ull;
+        return;
+    }
     const uint32_t eo = ns;   // E's first word
     const bool in_lds = (uint64_t)ns + ne <= kSliceWords;
     // buckets: the least power-of-two width that cuts [key_lo, key_hi) into at most kBuckets
@@ -751,27 +818,16 @@ bool bin_layout(const uint32_t* chrom_len, uint32_t n_chrom, uint64_t n, BinLayo
     return true;
 }
 
-hipError_t launch_bin_pack(const McTable& tab, uint64_t na, const BinWs& w, hipStream_t s) {
-    if (!na) return hipSuccess;
-    const uint32_t gr = (uint32_t)std::min<uint64_t>((na + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_bin_pack, dim3(gr), dim3(256), 0, s, tab.span, tab.len, tab.idx, na,
-                       reinterpret_cast<uint2*>(w.packed));
-    return hipGetLastError();
-}
-
 hipError_t launch_bin_regions(const uint32_t* chrom_len, uint32_t n_chrom, const uint32_t* bs, const uint32_t* be,
                               uint32_t n, const BinWs& w, uint32_t* status, hipStream_t s) {
     BinGeom g;
     if (!bin_geometry(chrom_len, n_chrom, &g)) return hipErrorInvalidValue;
     const uint32_t ncells = g.cb[n_chrom];
-    if (!ncells) return hipErrorInvalidValue;
+    if (!ncells || !n) return hipErrorInvalidValue;
     const uint32_t gr = (uint32_t)std::min<uint64_t>((ncells + 255) / 256, 4096);
     hipLaunchKernelGGL(k_bin_cells, dim3(gr), dim3(256), 0, s, g, bs, be, n, w.rs, w.re);
-    hipLaunchKernelGGL(k_bin_flags, dim3(gr), dim3(256), 0, s, g, w.rs, w.re, w.flag);
-    hipError_t e = launch_scan_counts(w.flag, ncells, w.offsets, w.scan_tiles, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bin_regions, dim3(gr), dim3(256), 0, s, g, w.rs, w.re, w.flag, w.offsets, n, w.nreg_max,
-                       w.cell_region, reinterpret_cast<RegionDesc*>(w.desc), status);
+    hipLaunchKernelGGL(k_bin_regions, dim3(n_chrom), dim3(kBinThreads), 0, s, g, w.rs, w.re, n, w.nreg_max,
+                       w.cell_region, reinterpret_cast<RegionDesc*>(w.desc), w.nreg, status);
     return hipGetLastError();
 }
 
@@ -782,25 +838,25 @@ hipError_t launch_bin_batch(const uint32_t* chrom_len, uint32_t n_chrom, const M
     BinGeom g;
     if (!bin_geometry(chrom_len, n_chrom, &g)) return hipErrorInvalidValue;
     if (nb == 0 || nb > BITS_MC_BIN_MAX_BATCH) return hipErrorInvalidValue;
-    const uint32_t ncells = g.cb[n_chrom];
     hipError_t e;
     if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bin_place, dim3(n_chrom * nb), dim3(kBinThreads), 0, s, g,
+    const auto place = na < g.cb[n_chrom] / 2 ? k_bin_place<true> : k_bin_place<false>;
+    hipLaunchKernelGGL(place, dim3(n_chrom * nb), dim3(kBinThreads), 0, s, g,
                        reinterpret_cast<const uint2*>(w.packed), tab.hist, tab.cursor, na, seed, sb, nb,
-                       w.cell_region, w.offsets, w.nreg_max, w.seg_start, w.seg_cnt, reinterpret_cast<uint2*>(w.recs));
+                       w.cell_region, w.nreg, w.nreg_max, w.seg_start, w.seg_cnt, reinterpret_cast<uint2*>(w.recs));
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
     if (w.splits > 1)
         hipLaunchKernelGGL(k_bin_search<true>, dim3(w.nreg_max * w.splits), dim3(kBinThreads), 0, s, bs, be, n,
-                           reinterpret_cast<const RegionDesc*>(w.desc), w.offsets + ncells, w.seg_start, w.seg_cnt,
+                           reinterpret_cast<const RegionDesc*>(w.desc), w.nreg, w.seg_start, w.seg_cnt,
                            w.nreg_max, nb, reinterpret_cast<const uint2*>(w.recs), na, w.splits, w.partial);
     else
         hipLaunchKernelGGL(k_bin_search<false>, dim3(w.nreg_max), dim3(kBinThreads), 0, s, bs, be, n,
-                           reinterpret_cast<const RegionDesc*>(w.desc), w.offsets + ncells, w.seg_start, w.seg_cnt,
+                           reinterpret_cast<const RegionDesc*>(w.desc), w.nreg, w.seg_start, w.seg_cnt,
                            w.nreg_max, nb, reinterpret_cast<const uint2*>(w.recs), na, 1u, w.partial);
     if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return e;
     // about 8 region shares per thread, at most 512 partial sums per shuffle into the atomics
     const uint32_t gy = (uint32_t)std::min<uint64_t>(std::max<uint64_t>((uint64_t)w.nreg_max * w.splits / 8, 1), 512);
-    hipLaunchKernelGGL(k_bin_reduce, dim3((nb + 255) / 256, gy), dim3(256), 0, s, w.partial, w.offsets + ncells,
+    hipLaunchKernelGGL(k_bin_reduce, dim3((nb + 255) / 256, gy), dim3(256), 0, s, w.partial, w.nreg,
                        w.splits, nb, totals);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev && (e = hipEventRecord(ev[3], s)) != hipSuccess) return e;

@@ -221,8 +221,14 @@ hipError_t launch_count(const SearchArgs& sa, const LaunchCfg& cfg, const uint32
 struct McTable {
     uint32_t *off, *span, *len, *idx, *hist, *cursor;
 };
+// Zeros of the outputs and (tab != nullptr) of the table's histogram and cursors.
+hipError_t launch_mc_zero(unsigned long long* totals, uint64_t ns, unsigned long long* observed, const McTable* tab,
+                          hipStream_t s);
+// Fills the table (after launch_mc_zero).  packed != nullptr: uint2[na] of the
+// binned path in place of off and len.  cursor[c] ends as the first table
+// position past chromosome c, hist[c] as its number of queries.
 hipError_t launch_mc_prepare(const uint32_t* as, const uint32_t* ae, uint64_t na, const uint32_t* chrom_len,
-                             uint32_t n_chrom, const McTable& tab, uint32_t* status, hipStream_t s);
+                             uint32_t n_chrom, const McTable& tab, void* packed, uint32_t* status, hipStream_t s);
 hipError_t launch_mc(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                      const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
                      unsigned long long* totals, unsigned long long* observed, hipStream_t s);
@@ -251,9 +257,8 @@ struct BinLayout {
 // false if the genome cannot be cut (sizes past 2^32).
 bool bin_layout(const uint32_t* chrom_len, uint32_t n_chrom, uint64_t n, BinLayout* L);
 struct BinWs {                    // device buffers, carved from the caller's workspace
-    uint32_t *rs, *re, *flag;     // [ncells]
-    uint64_t* offsets;            // [ncells + 1]: region starts (exclusive scan of flag); offsets[ncells] = regions
-    uint64_t* scan_tiles;         // scan_tiles(ncells)
+    uint32_t *rs, *re;            // [ncells]
+    uint64_t* nreg;               // number of regions
     uint32_t* cell_region;        // [ncells]
     void* desc;                   // [nreg_max + 1] region descriptors (16 bytes)
     uint32_t *seg_start, *seg_cnt;    // [batch][nreg_max]
@@ -262,7 +267,6 @@ struct BinWs {                    // device buffers, carved from the caller's wo
     void* packed;                     // [na] {input index, length or 0}
     uint32_t nreg_max, splits;
 };
-hipError_t launch_bin_pack(const McTable& tab, uint64_t na, const BinWs& w, hipStream_t s);
 hipError_t launch_bin_regions(const uint32_t* chrom_len, uint32_t n_chrom, const uint32_t* bs, const uint32_t* be,
                               uint32_t n, const BinWs& w, uint32_t* status, hipStream_t s);
 // Shuffles [sb, sb + nb) (absolute indices); totals points at shuffle sb's slot.

@@ -1178,28 +1178,56 @@ __device__ __forceinline__ uint32_t chrom_of(const ChromTab& ct, uint32_t s) {
     return lo;
 }
 
-// Per-chromosome query counts (hist zeroed by the caller).
-__global__ void __launch_bounds__(256) k_mc_hist(const uint32_t* __restrict__ a_start, uint64_t na, ChromTab ct,
-                                                 uint32_t* __restrict__ hist) {
-    __shared__ uint32_t h[BITS_MAX_CHROM];
-    for (uint32_t k = threadIdx.x; k < BITS_MAX_CHROM; k += blockDim.x) h[k] = 0u;
+// What a Monte-Carlo call starts from, in one launch: zero totals, observed
+// total, chromosome histogram and cursors.
+__global__ void __launch_bounds__(256) k_mc_zero(unsigned long long* __restrict__ totals, uint64_t ns,
+                                                 unsigned long long* observed, uint32_t* hist, uint32_t* cursor) {
+    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < ns; k += (uint64_t)gridDim.x * blockDim.x)
+        totals[k] = 0ull;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) *observed = 0ull;
+        if (hist) {
+            hist[threadIdx.x] = 0u;
+            cursor[threadIdx.x] = 0u;
+        }
+    }
+}
+static_assert(BITS_MAX_CHROM == 256, "one thread per chromosome");
+
+// Per-chromosome query counts (hist and cursor zeroed by the caller).  The
+// last workgroup to add its counts (counted in cursor[0], which is 0 in the
+// result) turns them into cursor[c] = queries on chromosomes before c.  Each
+// workgroup waits for its additions' return values before it counts itself in,
+// so no cache write-back (a device fence: 30 us for 1e5 queries) is needed; few
+// large workgroups keep the shared counter cheap.
+__global__ void __launch_bounds__(1024) k_mc_hist(const uint32_t* __restrict__ a_start, uint64_t na, ChromTab ct,
+                                                  uint32_t* hist, uint32_t* cursor) {
+    __shared__ uint32_t h[BITS_MAX_CHROM], wsum[4], last;
+    if (threadIdx.x < BITS_MAX_CHROM) h[threadIdx.x] = 0u;
     __syncthreads();
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na; i += (uint64_t)gridDim.x * blockDim.x)
         atomicAdd(&h[chrom_of(ct, a_start[i])], 1u);
     __syncthreads();
-    for (uint32_t k = threadIdx.x; k < ct.n; k += blockDim.x)
-        if (h[k]) atomicAdd(&hist[k], h[k]);
-}
-
-// cursor[c] = queries on chromosomes before c (one lane; at most 256 bins).
-__global__ void k_mc_scan(const uint32_t* __restrict__ hist, uint32_t n, uint32_t* __restrict__ cursor) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        uint32_t acc = 0;
-        for (uint32_t k = 0; k < n; ++k) {
-            cursor[k] = acc;
-            acc += hist[k];
-        }
+    if (threadIdx.x < BITS_MAX_CHROM && h[threadIdx.x]) {
+        const uint32_t old = atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+        asm volatile("" ::"v"(old) : "memory");   // the addition has been made
     }
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&cursor[0], 1u) == gridDim.x - 1u ? 1u : 0u;
+    __syncthreads();
+    if (!last || threadIdx.x >= BITS_MAX_CHROM) return;
+    const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const uint32_t v = __hip_atomic_load(&hist[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t x = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o);
+        if (lane >= (uint32_t)o) x += y;
+    }
+    if (lane == kWave - 1) wsum[w] = x;
+    __syncthreads();   // of the waves that are left
+    for (uint32_t k = 0; k < w; ++k) x += wsum[k];
+    cursor[threadIdx.x] = x - v;
 }
 
 // Per-query (chromosome offset, number of legal starts, length, index),
@@ -1208,12 +1236,15 @@ __global__ void k_mc_scan(const uint32_t* __restrict__ hist, uint32_t n, uint32_
 // `cursor` and places its queries there.  The order inside a chromosome's
 // range depends on scheduling; the totals do not (sums over the queries,
 // each drawing from its own index).  span = 0 marks a query outside its
-// chromosome (or start > end).
+// chromosome (or start > end).  With packed != nullptr (the binned path) the
+// table is span, idx and packed = {index, length, or 0 for such a query}; off
+// and len are not written.
 __global__ void __launch_bounds__(1024) k_mc_prepare(const uint32_t* __restrict__ a_start,
                                                      const uint32_t* __restrict__ a_end, uint64_t na, ChromTab ct,
                                                      uint32_t* __restrict__ cursor, uint32_t* __restrict__ off,
                                                      uint32_t* __restrict__ span, uint32_t* __restrict__ len,
-                                                     uint32_t* __restrict__ idx, uint32_t* status) {
+                                                     uint32_t* __restrict__ idx, uint2* __restrict__ packed,
+                                                     uint32_t* status) {
     __shared__ uint32_t cnt[BITS_MAX_CHROM], base[BITS_MAX_CHROM];
     uint32_t bad = 0;
     for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x; i0 < na; i0 += (uint64_t)gridDim.x * blockDim.x) {
@@ -1235,8 +1266,12 @@ __global__ void __launch_bounds__(1024) k_mc_prepare(const uint32_t* __restrict_
             const bool ok = s <= e && s >= ct.off[c] && (uint64_t)e < (uint64_t)ct.off[c + 1];
             const uint32_t L = e - s + 1u;
             const uint32_t pos = base[c] + r;
-            off[pos] = ct.off[c];
-            len[pos] = ok ? L : 1u;
+            if (packed) {
+                packed[pos] = make_uint2((uint32_t)i, ok ? L : 0u);
+            } else {
+                off[pos] = ct.off[c];
+                len[pos] = ok ? L : 1u;
+            }
             span[pos] = ok ? (ct.off[c + 1] - ct.off[c]) - L + 1u : 0u;
             idx[pos] = (uint32_t)i;
             if (!ok) bad |= (s > e) ? BITS_FLAG_INTERVAL : BITS_FLAG_CHROM;
@@ -1392,45 +1427,115 @@ __global__ void k_mc_tail(const unsigned long long* __restrict__ totals, uint64_
     }
 }
 
-// Order statistics of the per-shuffle totals (the median of Sec. 3.3):
-// out[r] = the k[r]-th smallest (0-based) of v[0..n), by most-significant-
-// digit radix selection over the 8 bytes: each pass histograms the values
-// that match the digits fixed so far and keeps the bucket holding the rank.
-// One workgroup; exact for any n < 2^32.
+// Order statistics of the per-shuffle totals (the median of Sec. 3.3): *out0
+// and *out1 = the k0-th and k1-th smallest (0-based, k0 <= k1 <= k0 + 1) of
+// v[0..n), exact for any n < 2^32, in one workgroup.  Most-significant-digit
+// radix selection of the k0-th: the digits all values share are found first
+// and skipped (totals of one run differ in their low two or three bytes), then
+// each pass histograms the values that match the digits fixed so far, and one
+// wave finds the bucket holding the rank with a prefix sum.  The k1-th is the
+// same value if enough values are not above it, else the least value above.
+// Latency of a pass bounds it; 1000 totals took 49 us with sixteen passes and
+// a serial walk of the histogram, 5 us now.
+__device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const unsigned long long y = __shfl_xor(v, o);
+        v = y < v ? y : v;
+    }
+    return v;
+}
+
 __global__ void __launch_bounds__(1024) k_select_u64(const unsigned long long* __restrict__ v, uint64_t n,
                                                      uint64_t k0, uint64_t k1, unsigned long long* out0,
                                                      unsigned long long* out1) {
     __shared__ uint32_t hist[256];
-    __shared__ unsigned long long sh_prefix, sh_mask;
+    __shared__ unsigned long long red[2][16], sh_prefix, sh_diff;
     __shared__ uint64_t sh_rank;
-    for (int which = 0; which < 2; ++which) {
-        if (threadIdx.x == 0) {
-            sh_prefix = 0ull;
-            sh_mask = 0ull;
-            sh_rank = which ? k1 : k0;
-        }
+    __shared__ uint32_t sh_same;
+    const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    constexpr int kHeld = 4;   // values a thread keeps in registers; the rest are read again each pass
+    unsigned long long held[kHeld];
+    const unsigned long long ref = v[0];
+    unsigned long long diff = 0ull;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) {
+        const uint64_t i = threadIdx.x + (uint64_t)u * 1024;
+        held[u] = i < n ? v[i] : ref;
+        diff |= held[u] ^ ref;
+    }
+    for (uint64_t i = threadIdx.x + kHeld * 1024; i < n; i += 1024) diff |= v[i] ^ ref;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) diff |= __shfl_xor(diff, o);
+    if (lane == 0) red[0][w] = diff;
+    if (threadIdx.x < 256) hist[threadIdx.x] = 0u;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long d = 0ull;
+        for (int k = 0; k < 16; ++k) d |= red[0][k];
+        const int top = d ? (63 - __clzll(d)) / 8 : -1;   // the highest byte in which values differ
+        sh_diff = d;
+        sh_prefix = top == 7 ? 0ull : ref & (~0ull << (8 * (top + 1)));
+        sh_rank = k0;
+        sh_same = 0u;
+    }
+    __syncthreads();
+    const unsigned long long d = sh_diff;
+    for (int p = d ? (63 - __clzll(d)) / 8 : -1; p >= 0; --p) {
+        const unsigned long long mask = p == 7 ? 0ull : ~0ull << (8 * (p + 1)), prefix = sh_prefix;
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u)
+            if (threadIdx.x + (uint64_t)u * 1024 < n && (held[u] & mask) == prefix)
+                atomicAdd(&hist[(uint32_t)(held[u] >> (8 * p)) & 255u], 1u);
+        for (uint64_t i = threadIdx.x + kHeld * 1024; i < n; i += 1024)
+            if ((v[i] & mask) == prefix) atomicAdd(&hist[(uint32_t)(v[i] >> (8 * p)) & 255u], 1u);
         __syncthreads();
-        for (int p = 7; p >= 0; --p) {
-            for (uint32_t d = threadIdx.x; d < 256u; d += blockDim.x) hist[d] = 0u;
-            __syncthreads();
-            const unsigned long long prefix = sh_prefix, mask = sh_mask;
-            for (uint64_t i = threadIdx.x; i < n; i += blockDim.x) {
-                const unsigned long long x = v[i];
-                if ((x & mask) == prefix) atomicAdd(&hist[(uint32_t)(x >> (8 * p)) & 255u], 1u);
+        if (w == 0) {   // lane l owns buckets 4l .. 4l + 3
+            uint32_t c[4], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum += c[k] = hist[4 * lane + k];
+            uint32_t x = sum;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const uint32_t y = __shfl_up(x, o);
+                if (lane >= (uint32_t)o) x += y;
             }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                uint64_t r = sh_rank, cum = 0;
-                uint32_t d = 0;
-                while (d < 255u && cum + hist[d] <= r) cum += hist[d++];
+            const uint64_t r = sh_rank;
+            uint64_t cum = x - sum;
+            if (r >= cum && r < x) {   // the bucket is one of this lane's
+                uint32_t k = 0;
+                while (cum + c[k] <= r) cum += c[k++];
                 sh_rank = r - cum;
-                sh_prefix = prefix | ((unsigned long long)d << (8 * p));
-                sh_mask = mask | (0xFFull << (8 * p));
+                sh_same = c[k];
+                sh_prefix = prefix | ((unsigned long long)(4 * lane + k) << (8 * p));
             }
-            __syncthreads();
         }
-        if (threadIdx.x == 0) *(which ? out1 : out0) = sh_prefix;
         __syncthreads();
+        if (threadIdx.x < 256) hist[threadIdx.x] = 0u;
+        __syncthreads();
+    }
+    // sh_prefix is the k0-th value, sh_rank its rank among its equals (k0 when all are equal)
+    const unsigned long long v0 = sh_prefix;
+    const uint64_t same = d ? sh_same : n;
+    if (threadIdx.x == 0) *out0 = v0;
+    if (sh_rank + (k1 - k0) < same) {
+        if (threadIdx.x == 0) *out1 = v0;
+        return;
+    }
+    unsigned long long m = ~0ull;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u)
+        if (held[u] > v0 && held[u] < m) m = held[u];
+    for (uint64_t i = threadIdx.x + kHeld * 1024; i < n; i += 1024) {
+        const unsigned long long x = v[i];
+        if (x > v0 && x < m) m = x;
+    }
+    m = wave_min_u64(m);
+    if (lane == 0) red[1][w] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 16; ++k) m = red[1][k] < m ? red[1][k] : m;
+        *out1 = m;
     }
 }
 
@@ -1717,21 +1822,25 @@ static int fill_chrom_tab(const uint32_t* chrom_len, uint32_t n_chrom, ChromTab*
     return BITS_OK;
 }
 
+hipError_t launch_mc_zero(unsigned long long* totals, uint64_t ns, unsigned long long* observed, const McTable* tab,
+                          hipStream_t s) {
+    const uint64_t g = (ns + 255) / 256;
+    hipLaunchKernelGGL(k_mc_zero, dim3((uint32_t)(g < 1 ? 1 : g > 4096 ? 4096 : g)), dim3(256), 0, s, totals, ns,
+                       observed, tab ? tab->hist : nullptr, tab ? tab->cursor : nullptr);
+    return hipGetLastError();
+}
+
 hipError_t launch_mc_prepare(const uint32_t* as, const uint32_t* ae, uint64_t na, const uint32_t* chrom_len,
-                             uint32_t n_chrom, const McTable& tab, uint32_t* status, hipStream_t s) {
+                             uint32_t n_chrom, const McTable& tab, void* packed, uint32_t* status, hipStream_t s) {
     ChromTab ct;
     if (fill_chrom_tab(chrom_len, n_chrom, &ct) != BITS_OK) return hipErrorInvalidValue;
     if (!na) return hipSuccess;
-    hipError_t e = launch_fill_u32(tab.hist, n_chrom, 0u, s);
-    if (e != hipSuccess) return e;
-    uint64_t g = (na + 255) / 256;
-    if (g > 2048) g = 2048;
-    hipLaunchKernelGGL(k_mc_hist, dim3((uint32_t)g), dim3(256), 0, s, as, na, ct, tab.hist);
-    hipLaunchKernelGGL(k_mc_scan, dim3(1), dim3(64), 0, s, tab.hist, n_chrom, tab.cursor);
-    g = (na + 1023) / 1024;
+    uint64_t g = (na + 1023) / 1024;
+    hipLaunchKernelGGL(k_mc_hist, dim3((uint32_t)(g < 256 ? g : 256)), dim3(1024), 0, s, as, na, ct, tab.hist,
+                       tab.cursor);
     if (g > 1024) g = 1024;
     hipLaunchKernelGGL(k_mc_prepare, dim3((uint32_t)g), dim3(1024), 0, s, as, ae, na, ct, tab.cursor, tab.off,
-                       tab.span, tab.len, tab.idx, status);
+                       tab.span, tab.len, tab.idx, (uint2*)packed, status);
     return hipGetLastError();
 }
 

@@ -91,6 +91,7 @@ struct SearchArgs {
     uint32_t n;                  // |B|
     uint32_t tree_stride;        // 2^built_depth
     uint32_t depth;              // levels searched from LDS (<= built depth)
+    float mean_len;              // mean_length(), set by the kernels that use it
 };
 
 // Entries of one line-head array for n keys: ceil(n / 32) heads plus at
@@ -128,6 +129,8 @@ __host__ __device__ constexpr size_t search_lds_bytes(bool learned, uint32_t dep
 // 335 and 144 us).
 enum : int { kModePlain = 0, kModeLearned = 1, kModeTiered = 2, kModeDirect = 3 };
 constexpr uint32_t kDirectKeys = 1u << 19;
+// Above this the tiered search looks for a query's second rank next to its first.
+constexpr uint32_t kNearKeys = 1u << 24;
 
 // Copy the first 2^d - 1 nodes of both trees into LDS: lds[0..2^d) starts,
 // lds[2^d..2^(d+1)) ends, 1-based BFS order (slot 0 unused).

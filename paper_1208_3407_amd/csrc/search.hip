@@ -42,6 +42,23 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The sorted arrays a search of several chains runs over, with their line heads
+// and models: even chains take k[0], odd ones k[1].  A search of one array has
+// it in both places.
+struct Arrays {
+    const uint32_t* k[2];
+    const uint32_t* h[2];
+    const bits_rmi_model* m[2];
+    uint32_t n;
+};
+__device__ __forceinline__ Arrays both_arrays(const SearchArgs& sa) {
+    return Arrays{{sa.bs, sa.be}, {sa.hs, sa.he}, {sa.rmi, sa.rmi ? sa.rmi + 1 : nullptr}, sa.n};
+}
+__device__ __forceinline__ Arrays one_array(const SearchArgs& sa, int which) {
+    const Arrays a = both_arrays(sa);
+    return Arrays{{a.k[which], a.k[which]}, {a.h[which], a.h[which]}, {a.m[which], a.m[which]}, a.n};
+}
+
 // ------------------------------------------------------------------ bisection
 // For each chain c: base[c] += #{K_c[base[c] .. base[c] + len[c]) < x[c]};
 // K_c is B_S for even c and B_E for odd c.  Leaves len[c] == 0.  The first
@@ -190,13 +207,16 @@ __device__ __forceinline__ void probe_lines(const uint32_t* __restrict__ ks, con
     wave_lds_sync();
 }
 
-// ------------------------------------------------------------------ quad probe
-// Windows of a sorted array counted by the four lanes of a quad, in
-// registers only: in pass j the quad serves its lane j, whose window start
-// and key the other three read with a quad_perm broadcast.  Each lane takes
-// 16 bytes per 64-byte half window, so one load instruction covers 64
-// contiguous bytes per quad, and two DPP additions leave the count in the
-// owner.  No LDS is touched, so the LDS holds only the top trees.
+// ------------------------------------------------------------------ probes in registers
+// The same counts without LDS memory, for the search that keeps its LDS for
+// the top trees.  A group of lanes serves its own lanes in turn: in pass j the
+// group counts lane j's window, whose start and key the others read by a lane
+// broadcast, each lane taking 16 bytes of it.
+//   quads  windows of WIN words, 64 contiguous bytes per load and quad
+//          (quad_perm broadcasts);
+//   octs   128-byte windows, one load each: a line read by one instruction is
+//          one request, by two it is two (1e7 queries against 1e7: 702 us with
+//          the data lines read by octs, 798 by quads); ds_swizzle broadcasts.
 template <int J>
 __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
     int r = __builtin_amdgcn_update_dpp(0, (int)v, J * 0x55, 0xF, 0xF, true);
@@ -204,17 +224,17 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
     return (uint32_t)r;
 }
 
+template <int J>
+__device__ __forceinline__ uint32_t oct_bcast(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (J << 5) | 0x18);   // lane (l & 24) | J of each 32
+}
+
 // The 16-byte pieces of the windows of the quad's lane J.
-template <int J, int LOADS, bool NT>
+template <int J, int LOADS>
 __device__ __forceinline__ void quad_load(const uint32_t* __restrict__ K, uint32_t start, u32x4 (&v)[LOADS]) {
     const u32x4* P = reinterpret_cast<const u32x4*>(K + quad_bcast<J>(start)) + (threadIdx.x & 3u);
 #pragma unroll
-    for (int k = 0; k < LOADS; ++k) {
-        if constexpr (NT)
-            v[k] = __builtin_nontemporal_load(P + 4 * k);
-        else
-            v[k] = P[4 * k];
-    }
+    for (int k = 0; k < LOADS; ++k) v[k] = P[4 * k];
 }
 
 template <int J, int LOADS>
@@ -231,7 +251,7 @@ __device__ __forceinline__ void quad_sum(const u32x4 (&v)[LOADS], uint32_t x, ui
 // multiple of 4 with the whole window inside K_c; all 64 lanes call it, an
 // idle chain passes any start in bounds.  The loads of all chains are issued
 // before the first count.
-template <int NC, int WIN, bool NT>
+template <int NC, int WIN>
 __device__ __forceinline__ void quad_windows(const uint32_t* __restrict__ ks, const uint32_t* __restrict__ ke,
                                              const uint32_t (&start)[NC], const uint32_t (&x)[NC],
                                              uint32_t (&cnt)[NC]) {
@@ -241,10 +261,10 @@ __device__ __forceinline__ void quad_windows(const uint32_t* __restrict__ ks, co
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const uint32_t* K = (c & 1) ? ke : ks;
-        quad_load<0, kLoads, NT>(K, start[c], v[c][0]);
-        quad_load<1, kLoads, NT>(K, start[c], v[c][1]);
-        quad_load<2, kLoads, NT>(K, start[c], v[c][2]);
-        quad_load<3, kLoads, NT>(K, start[c], v[c][3]);
+        quad_load<0, kLoads>(K, start[c], v[c][0]);
+        quad_load<1, kLoads>(K, start[c], v[c][1]);
+        quad_load<2, kLoads>(K, start[c], v[c][2]);
+        quad_load<3, kLoads>(K, start[c], v[c][3]);
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -257,13 +277,89 @@ __device__ __forceinline__ void quad_windows(const uint32_t* __restrict__ ks, co
     }
 }
 
+template <int J, bool NT>
+__device__ __forceinline__ u32x4 oct_load(const uint32_t* __restrict__ K, uint32_t start) {
+    const u32x4* P = reinterpret_cast<const u32x4*>(K + oct_bcast<J>(start)) + (threadIdx.x & 7u);
+    if constexpr (NT)
+        return __builtin_nontemporal_load(P);
+    else
+        return *P;
+}
+
+template <int J>
+__device__ __forceinline__ void oct_sum(u32x4 v, uint32_t x, uint32_t& res) {
+    const uint32_t t = group_sum<8>(count_lt4(v, oct_bcast<J>(x)));
+    if ((threadIdx.x & 7u) == (uint32_t)J) res = t;
+}
+
+// As quad_windows for 32 words, by octs.
+template <int NC, bool NT>
+__device__ __forceinline__ void oct_windows(const uint32_t* __restrict__ ks, const uint32_t* __restrict__ ke,
+                                            const uint32_t (&start)[NC], const uint32_t (&x)[NC], uint32_t (&cnt)[NC]) {
+    u32x4 v[NC][8];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const uint32_t* K = (c & 1) ? ke : ks;
+        v[c][0] = oct_load<0, NT>(K, start[c]);
+        v[c][1] = oct_load<1, NT>(K, start[c]);
+        v[c][2] = oct_load<2, NT>(K, start[c]);
+        v[c][3] = oct_load<3, NT>(K, start[c]);
+        v[c][4] = oct_load<4, NT>(K, start[c]);
+        v[c][5] = oct_load<5, NT>(K, start[c]);
+        v[c][6] = oct_load<6, NT>(K, start[c]);
+        v[c][7] = oct_load<7, NT>(K, start[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        uint32_t r = 0;
+        oct_sum<0>(v[c][0], x[c], r);
+        oct_sum<1>(v[c][1], x[c], r);
+        oct_sum<2>(v[c][2], x[c], r);
+        oct_sum<3>(v[c][3], x[c], r);
+        oct_sum<4>(v[c][4], x[c], r);
+        oct_sum<5>(v[c][5], x[c], r);
+        oct_sum<6>(v[c][6], x[c], r);
+        oct_sum<7>(v[c][7], x[c], r);
+        cnt[c] = r;
+    }
+}
+
+// Windows of 32 words for the few lanes of `on` (not empty): the lowest eight
+// of them are served at once, the k-th by oct k.  Returns the count in the
+// lanes served, and in `on` the lanes that are.  All 64 lanes call it.
+template <bool NT>
+__device__ __forceinline__ uint32_t few_windows(const uint32_t* __restrict__ K, uint32_t start, uint32_t x, uint64_t& on) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    uint32_t owner = 0;
+    uint64_t m = on, served = 0ull;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {   // m is uniform: the k-th lane of `on`, for oct k
+        const uint32_t i = m ? (uint32_t)__builtin_ctzll(m) : (uint32_t)__builtin_ctzll(on);
+        owner = lane / 8 == k ? i : owner;
+        served |= m & (0ull - m);
+        m &= m - 1;
+    }
+    const uint32_t w = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4 * owner), (int)start);
+    const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4 * owner), (int)x);
+    const u32x4* P = reinterpret_cast<const u32x4*>(K + w) + (lane & 7u);
+    u32x4 v;
+    if constexpr (NT)
+        v = __builtin_nontemporal_load(P);
+    else
+        v = *P;
+    const uint32_t t = group_sum<8>(count_lt4(v, y));
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(on >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)on, 0u));
+    on = served;
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(32 * (rank & 7u)), (int)t);
+}
+
 // Lower bounds by windows: on entry r_c = #{K_c < x[c]} lies in
 // [lo[c], hi[c]] and near g[c]; on return lo[c] = r_c.  The first window sits
 // around the guess, the second next to it on the side its count points to,
 // later ones around the middle of what is left, so a bad guess costs speed
 // only.  K_c is readable (and 0xFFFFFFFF past its keys) up to `lim`, a
 // multiple of 4 and at least WIN.  All 64 lanes call it.
-template <int NC, int WIN, bool NT>
+template <int NC, int WIN>
 __device__ __forceinline__ void window_search(const uint32_t* __restrict__ ks, const uint32_t* __restrict__ ke,
                                               uint32_t lim, uint32_t (&lo)[NC], uint32_t (&hi)[NC],
                                               const uint32_t (&g)[NC], const uint32_t (&x)[NC]) {
@@ -272,12 +368,12 @@ __device__ __forceinline__ void window_search(const uint32_t* __restrict__ ks, c
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         // a range that one window covers needs no guess
-        const uint32_t near = (g[c] > WIN / 2 ? g[c] - WIN / 2 : 0u) & ~3u;
+        const uint32_t near = (g[c] > WIN / 2 - 4 ? g[c] - (WIN / 2 - 4) : 0u) & ~7u;
         w[c] = min(hi[c] - lo[c] <= WIN - 4 ? lo[c] & ~3u : near, lim - WIN);
         any |= lo[c] < hi[c];
     }
     for (uint32_t step = 0; __ballot(any); ++step) {
-        quad_windows<NC, WIN, NT>(ks, ke, w, x, cnt);
+        quad_windows<NC, WIN>(ks, ke, w, x, cnt);
         any = false;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -321,7 +417,7 @@ __device__ __forceinline__ uint32_t dpp_quad(uint32_t v) {
 }
 
 template <int NC>
-__device__ __forceinline__ void quad_leaves(const bits_rmi_model* __restrict__ rmi, const uint32_t (&leaf)[NC],
+__device__ __forceinline__ void quad_leaves(const Arrays& A, const uint32_t (&leaf)[NC],
                                             const uint32_t (&x)[NC], uint32_t* scr) {
     const uint32_t lane = threadIdx.x & (kWave - 1);
 #pragma unroll
@@ -333,8 +429,8 @@ __device__ __forceinline__ void quad_leaves(const bits_rmi_model* __restrict__ r
     const uint32_t quad = lane >> 2, q = lane & 3u;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const bits_rmi_model* M = rmi + (c & 1);
-        uint4 A[4], B[4];
+        const bits_rmi_model* M = A.m[c & 1];
+        uint4 Q[4], B[4];
         uint32_t xo[4];
 #pragma unroll
         for (int pass = 0; pass < 4; ++pass) {
@@ -342,7 +438,7 @@ __device__ __forceinline__ void quad_leaves(const bits_rmi_model* __restrict__ r
             const uint2 lx = *reinterpret_cast<const uint2*>(scr + c * kLeafScr + 2 * owner);
             xo[pass] = lx.y;
             const uint4* rec = reinterpret_cast<const uint4*>(M->leaf + lx.x);
-            A[pass] = rec[q];
+            Q[pass] = rec[q];
             B[pass] = rec[4 + q];
         }
 #pragma unroll
@@ -350,11 +446,11 @@ __device__ __forceinline__ void quad_leaves(const bits_rmi_model* __restrict__ r
             const uint32_t owner = (uint32_t)pass * 16u + quad;
             // kmin from quad lane 0, kinv from quad lane 2 (lane exchanges: a quad_perm
             // broadcast DPP folded into the using instruction gave wrong values here)
-            const uint32_t kmin = (uint32_t)__shfl((int)A[pass].x, (int)(lane & ~3u));
-            const uint32_t kinvb = (uint32_t)__shfl((int)A[pass].x, (int)((lane & ~3u) + 2u));
+            const uint32_t kmin = (uint32_t)__shfl((int)Q[pass].x, (int)(lane & ~3u));
+            const uint32_t kinvb = (uint32_t)__shfl((int)Q[pass].x, (int)((lane & ~3u) + 2u));
             const float u = rmi_u(xo[pass] - kmin, __uint_as_float(kinvb));
-            const float w1[4] = {h2f(A[pass].z & 0xFFFFu), h2f(A[pass].z >> 16), h2f(A[pass].w & 0xFFFFu),
-                                 h2f(A[pass].w >> 16)};
+            const float w1[4] = {h2f(Q[pass].z & 0xFFFFu), h2f(Q[pass].z >> 16), h2f(Q[pass].w & 0xFFFFu),
+                                 h2f(Q[pass].w >> 16)};
             const float b1[4] = {h2f(B[pass].x & 0xFFFFu), h2f(B[pass].x >> 16), h2f(B[pass].y & 0xFFFFu),
                                  h2f(B[pass].y >> 16)};
             const float w2[4] = {h2f(B[pass].z & 0xFFFFu), h2f(B[pass].z >> 16), h2f(B[pass].w & 0xFFFFu),
@@ -370,11 +466,11 @@ __device__ __forceinline__ void quad_leaves(const bits_rmi_model* __restrict__ r
             // lane 0: {kmin, kmax}; 1: {rlo, cnt}; 2: y = b2 + sum; 3: err
             uint32_t* res = scr + c * kLeafScr + 2 * kWave + 6 * owner;
             if (q < 2)
-                *reinterpret_cast<uint2*>(res + 2 * q) = make_uint2(A[pass].x, A[pass].y);
+                *reinterpret_cast<uint2*>(res + 2 * q) = make_uint2(Q[pass].x, Q[pass].y);
             else if (q == 2)
-                res[4] = __float_as_uint(__uint_as_float(A[pass].y) + t);
+                res[4] = __float_as_uint(__uint_as_float(Q[pass].y) + t);
             else
-                res[5] = A[pass].x;
+                res[5] = Q[pass].x;
         }
     }
     wave_lds_sync();
@@ -392,6 +488,19 @@ __device__ __forceinline__ void quad_leaves(const bits_rmi_model* __restrict__ r
 // single probe.  (An idle [0, 0] would search B_S for 1, which a reference
 // with many intervals starting at 0 turns into a fallback bisection.)
 constexpr uint32_t kIdleEnd = 0xFFFFFFFFu;
+
+// Mean length of B's intervals less one, for predictions only: the mean
+// distance of equal ranks of B_E and B_S at four places.
+__device__ __forceinline__ float mean_length(const SearchArgs& sa) {
+    float m = 0.0f;
+#pragma unroll
+    for (uint32_t k = 1; k < 8; k += 2) {
+        const uint32_t i = (uint32_t)((uint64_t)sa.n * k / 8);
+        const uint32_t a = sa.bs[i], b = sa.be[i];
+        m += b > a ? (float)(b - a) : 0.0f;
+    }
+    return 0.25f * m;
+}
 
 // Bisection probes kept in L2 on the plain path: the first few probes of a
 // bucket are shared by every query landing in it.
@@ -454,19 +563,19 @@ __device__ __forceinline__ void icount_plain(const SearchArgs& sa, const uint32_
 // the leaf's rank range [rlo, rhi]; inside = (kmin < x <= kmax); pred = the
 // model's rank for an inside key, else the resolved rank (rhi if x > kmax,
 // rlo if x <= kmin: routing is monotone, so no key of another leaf lies
-// between); err = the leaf's packed error bounds.  Must be called by all 64
-// lanes.
+// between); err = the leaf's packed error bounds; dens = the leaf's keys per
+// coordinate.  Must be called by all 64 lanes.
 template <int NC>
-__device__ __forceinline__ void leaf_stage(const SearchArgs& sa, uint32_t* scr, const uint32_t (&x)[NC],
+__device__ __forceinline__ void leaf_stage(const Arrays& A, uint32_t* scr, const uint32_t (&x)[NC],
                                            uint32_t (&rlo)[NC], uint32_t (&rhi)[NC], uint32_t (&pred)[NC],
-                                           uint32_t (&err)[NC], bool (&inside)[NC]) {
+                                           uint32_t (&err)[NC], bool (&inside)[NC], float (&dens)[NC]) {
     uint32_t leaf[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const bits_rmi_model* M = sa.rmi + (c & 1);
+        const bits_rmi_model* M = A.m[c & 1];
         leaf[c] = rmi_route(M->root_a, M->root_b, x[c]);
     }
-    quad_leaves<NC>(sa.rmi, leaf, x, scr);
+    quad_leaves<NC>(A, leaf, x, scr);
     const uint32_t lane = threadIdx.x & (kWave - 1);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -475,9 +584,10 @@ __device__ __forceinline__ void leaf_stage(const SearchArgs& sa, uint32_t* scr, 
                     rc = *reinterpret_cast<const uint2*>(res + 4);
         // ra = {kmin, kmax}, rb = {rlo, cnt}, rc = {y, err}
         // clamped to [0, n] so that no header value can send a search out of bounds
-        rhi[c] = min(rb.x + rb.y, sa.n);
+        rhi[c] = min(rb.x + rb.y, A.n);
         rlo[c] = min(rb.x, rhi[c]);
         err[c] = rc.y;
+        dens[c] = (float)rb.y * __builtin_amdgcn_rcpf((float)(ra.y - ra.x));
         inside[c] = x[c] > ra.x && x[c] <= ra.y;
         if (inside[c])
             pred[c] = min(rlo[c] + (uint32_t)rmi_offset_from_y(__uint_as_float(rc.x), rb.y), rhi[c]);
@@ -490,11 +600,12 @@ __device__ __forceinline__ void leaf_stage(const SearchArgs& sa, uint32_t* scr, 
 // the recorded error window [wl, wr] around the prediction (base = wl).  Must
 // be called by all 64 lanes.
 template <int NC>
-__device__ __forceinline__ void learned_windows(const SearchArgs& sa, uint32_t* scr, const uint32_t (&x)[NC],
+__device__ __forceinline__ void learned_windows(const Arrays& A, uint32_t* scr, const uint32_t (&x)[NC],
                                                 uint32_t (&base)[NC], uint32_t (&wl)[NC], uint32_t (&wr)[NC],
-                                                uint32_t (&rlo)[NC], uint32_t (&rhi)[NC], bool (&win)[NC]) {
+                                                uint32_t (&rlo)[NC], uint32_t (&rhi)[NC], bool (&win)[NC],
+                                                float (&dens)[NC]) {
     uint32_t pred[NC], err[NC];
-    leaf_stage<NC>(sa, scr, x, rlo, rhi, pred, err, win);
+    leaf_stage<NC>(A, scr, x, rlo, rhi, pred, err, win, dens);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         base[c] = pred[c];
@@ -554,7 +665,7 @@ __device__ __forceinline__ uint32_t head_outcome(uint32_t w, uint32_t cnt) {
     return (cnt == 0u && w != 0u) ? kHeadLeft : kHeadHit;
 }
 
-// Learned count: the leaf's recorded error window [wl, wr] holds the lower
+// Learned rank: the leaf's recorded error window [wl, wr] holds the lower
 // bound r = #{K < x}, so j = #{H < x} = ceil(r / 32) over the line heads
 // (H[j] = K[32 j], kept in L2 / the Infinity Cache) lies in [ceil(wl / 32),
 // ceil(wr / 32)].  One cooperative probe of the kHeadWin heads starting at
@@ -564,20 +675,13 @@ __device__ __forceinline__ uint32_t head_outcome(uint32_t w, uint32_t cnt) {
 // recorded error) falls back to that bisection too, and is counted.  One
 // cooperative probe of line j - 1 then gives r (r = 0 when j = 0).  Must be
 // called by all 64 lanes.
-template <int QPL>
-__device__ __forceinline__ void icount_learned(const SearchArgs& sa, uint32_t* scr, const uint32_t (&as)[QPL],
-                                               const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL],
-                                               uint32_t (&fst)[QPL]) {
-    constexpr int NC = 2 * QPL;
-    uint32_t x[NC], base[NC], wl[NC], wr[NC], rlo[NC], rhi[NC];
+template <int NC>
+__device__ __forceinline__ void rank_learned(const Arrays& A, unsigned long long* fallbacks, uint32_t* scr,
+                                             const uint32_t (&x)[NC], uint32_t (&r)[NC], float (&dens)[NC]) {
+    uint32_t wl[NC], wr[NC], rlo[NC], rhi[NC];
     bool win[NC];
-#pragma unroll
-    for (int q = 0; q < QPL; ++q) {
-        x[2 * q] = ae[q] + 1u;
-        x[2 * q + 1] = as[q];
-    }
-    learned_windows<NC>(sa, scr, x, base, wl, wr, rlo, rhi, win);
-    const uint32_t m = (sa.n + 31u) >> 5;     // heads in use
+    learned_windows<NC>(A, scr, x, r, wl, wr, rlo, rhi, win, dens);
+    const uint32_t m = (A.n + 31u) >> 5;     // heads in use
     uint32_t w[NC], pc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -585,7 +689,7 @@ __device__ __forceinline__ void icount_learned(const SearchArgs& sa, uint32_t* s
         const uint32_t w0 = (jlo > 0u ? jlo - 1u : 0u) & ~(kHeadAlign - 1u);
         w[c] = (win[c] && jhi < w0 + kHeadWin) ? w0 : kNoLine;
     }
-    probe_lines<NC, false, kHeadWin, kHeadLanes>(sa.hs, sa.he, w, x, pc, scr);
+    probe_lines<NC, false, kHeadWin, kHeadLanes>(A.h[0], A.h[1], w, x, pc, scr);
     uint32_t j[NC], jl[NC];
     bool again = false;
 #pragma unroll
@@ -597,25 +701,19 @@ __device__ __forceinline__ void icount_learned(const SearchArgs& sa, uint32_t* s
             j[c] = w[c] + pc[c];
             continue;
         }
-        if (w[c] != kNoLine) atomicAdd(sa.fallbacks, 1ull);   // the window missed
+        if (w[c] != kNoLine) atomicAdd(fallbacks, 1ull);   // the window missed
         j[c] = min((rlo[c] + 31u) >> 5, m);
         jl[c] = min((rhi[c] + 31u) >> 5, m) - j[c];
         again = true;
     }
-    if (__ballot(again)) bisect_multi<NC>(sa.hs, sa.he, j, jl, x, 32u);
+    if (__ballot(again)) bisect_multi<NC>(A.h[0], A.h[1], j, jl, x, 32u);
     uint32_t dw[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) dw[c] = (win[c] && j[c] != 0u) ? (min(j[c], m) - 1u) * 32u : kNoLine;
-    probe_lines<NC, true>(sa.bs, sa.be, dw, x, pc, scr);
+    probe_lines<NC, true>(A.k[0], A.k[1], dw, x, pc, scr);
 #pragma unroll
     for (int c = 0; c < NC; ++c)
-        if (win[c]) base[c] = dw[c] == kNoLine ? 0u : dw[c] + pc[c];
-#pragma unroll
-    for (int q = 0; q < QPL; ++q) {
-        const uint32_t first = (ae[q] == 0xFFFFFFFFu) ? sa.n : base[2 * q];
-        cnt[q] = first - base[2 * q + 1];
-        fst[q] = first;
-    }
+        if (win[c]) r[c] = dw[c] == kNoLine ? 0u : dw[c] + pc[c];
 }
 
 template <int QPL>
@@ -630,7 +728,8 @@ __device__ __forceinline__ void icount_heads(const SearchArgs& sa, uint32_t* scr
         x[2 * q] = ae[q] + 1u;
         x[2 * q + 1] = as[q];
     }
-    leaf_stage<NC>(sa, scr, x, rlo, rhi, pred, err, inside);
+    float dens[NC];
+    leaf_stage<NC>(both_arrays(sa), scr, x, rlo, rhi, pred, err, inside, dens);
     const uint32_t m = (sa.n + 31u) >> 5;     // heads in use
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -706,23 +805,26 @@ __device__ __forceinline__ void icount_heads(const SearchArgs& sa, uint32_t* scr
 //                      bucket of at most 28 keys is covered whole.
 //   larger n           j = #{H < x} = ceil(r / 32) over the line heads
 //                      H[j] = K[32 j] (1/32 of the array, kept in L2 / the
-//                      Infinity Cache) by a window of 16 heads around the
-//                      predicted line, then one window over line j - 1
-//                      (r = 0 when j = 0): one data line per search.
-// Exact whatever the prediction (window_search).  All 64 lanes call it.
-// Bound by random reads: one 64-byte window of heads (L2) and one data line
-// per search.  1e7 queries against 1e7 (half clustered): 0.79 ms, against
+//                      Infinity Cache) by windows of 32 heads around the
+//                      predicted line (the median error is 2 heads at 1e7
+//                      half-clustered keys and 8 at 5e7; windows of 16 miss more
+//                      often: 702 us against 647 for 1e7 queries), then one window
+//                      over line j - 1 (r = 0 when j = 0): one data line per search.
+// dens = the bucket's keys per coordinate.  Exact whatever the prediction
+// (window_search).  All 64 lanes call it.
+// Bound by random reads: one window of heads (L2) and one data line per
+// search.  1e7 queries against 1e7 (half clustered): 0.60 ms, against
 // 3.85 ms for the bisection of the bucket in HBM and about 0.35 ms for the
-// data lines alone; 5e7 against 5e7: 6.5 against 18.5 ms.  A whole bisection
-// of the heads costs one L2 request per step where the window costs one.
+// data lines alone; 5e7 against 5e7: 4.0 against 18.5 ms.  A whole bisection
+// of the heads costs one L2 request per step where the window costs two.
 template <int NC, bool DIRECT>
-__device__ __forceinline__ void rank_tiered(const SearchArgs& sa, const uint32_t* lds, const uint32_t (&x)[NC],
-                                            uint32_t (&r)[NC]) {
-    const uint32_t d = sa.depth, n = sa.n, m = 1u << d;
+__device__ __forceinline__ void rank_tiered(const Arrays& A, const uint32_t* tree0, const uint32_t* tree1, uint32_t d,
+                                            const uint32_t (&x)[NC], uint32_t (&r)[NC], float (&dens)[NC]) {
+    const uint32_t n = A.n, m = 1u << d;
     uint32_t k[NC], klo[NC], khi[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        const uint32_t* K = (c & 1) ? sa.be : sa.bs;
+        const uint32_t* K = A.k[c & 1];
         k[c] = 1u;
         klo[c] = K[0];
         khi[c] = K[n - 1];
@@ -730,7 +832,7 @@ __device__ __forceinline__ void rank_tiered(const SearchArgs& sa, const uint32_t
     for (uint32_t l = 0; l < d; ++l) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const uint32_t v = lds[(c & 1) * m + k[c]];
+            const uint32_t v = ((c & 1) ? tree1 : tree0)[k[c]];
             const bool right = v < x[c];
             klo[c] = right ? v : klo[c];
             khi[c] = right ? khi[c] : v;
@@ -742,40 +844,185 @@ __device__ __forceinline__ void rank_tiered(const SearchArgs& sa, const uint32_t
     for (int c = 0; c < NC; ++c) {
         const uint64_t qb = k[c] - m;
         const uint32_t base = (uint32_t)((qb * n) >> d), len = (uint32_t)(((qb + 1) * n) >> d) - base;
-        const float f = x[c] > klo[c] ? (float)(x[c] - klo[c]) * __builtin_amdgcn_rcpf((float)(khi[c] - klo[c])) : 0.0f;
+        const float inv = __builtin_amdgcn_rcpf((float)(khi[c] - klo[c]));
+        const float f = x[c] > klo[c] ? (float)(x[c] - klo[c]) * inv : 0.0f;
+        dens[c] = (float)len * inv;
         const uint32_t pos = base + (uint32_t)(fminf(f, 1.0f) * (float)len);   // equal bounding keys give f = inf
         lo[c] = DIRECT ? base : (uint32_t)(((uint64_t)base + 31u) >> 5);
         hi[c] = DIRECT ? base + len : (uint32_t)(((uint64_t)base + len + 31u) >> 5);
         g[c] = DIRECT ? pos : (uint32_t)(((uint64_t)pos + 31u) >> 5);
     }
     if constexpr (DIRECT) {
-        window_search<NC, 32, false>(sa.bs, sa.be, (n + 31u) & ~31u, lo, hi, g, x);
+        window_search<NC, 32>(A.k[0], A.k[1], (n + 31u) & ~31u, lo, hi, g, x);
 #pragma unroll
         for (int c = 0; c < NC; ++c) r[c] = lo[c];
     } else {
-        window_search<NC, 16, false>(sa.hs, sa.he, (uint32_t)heads_len(n), lo, hi, g, x);
+        window_search<NC, 32>(A.h[0], A.h[1], (uint32_t)heads_len(n), lo, hi, g, x);
         uint32_t w[NC], pc[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) w[c] = lo[c] ? (lo[c] - 1u) * 32u : 0u;
-        quad_windows<NC, 32, true>(sa.bs, sa.be, w, x, pc);
+        oct_windows<NC, true>(A.k[0], A.k[1], w, x, pc);
 #pragma unroll
         for (int c = 0; c < NC; ++c) r[c] = lo[c] ? w[c] + pc[c] : 0u;
     }
 }
 
-// One query (two chains) at a time: the windows of more would not fit the registers.
+// ------------------------------------------------------------------ last from first
+// #{B_E < a.start} is first = #{B_S <= a.end} less the count, so it is looked
+// for next to rank `first` of B_E instead of by a search of its own: with the
+// local density of starts, est = dens (length of a + mean length of B)
+// intervals are expected, and the 128-byte line of rank first - 1 - est, or
+// its neighbour on the side the count of the line points to, holds the answer
+// for all but long queries.  Nothing is assumed about the count: a key range
+// that the two lines do not decide, an interval set whose starts and ends do
+// not belong together, or a query with more than kNearCount expected hits
+// takes the full search.
+// That halves the requests (9.5 -> 4.2 L2 requests per query at 1e7) but makes
+// one chain of waits of two, so it pays where reads miss the caches: 5e7
+// queries against 5e7 through the model 3.34 ms, 3.71 with both searches in
+// full; without a model 4.0 against 5.2 ms there, 1.37 against 1.49 ms at 2e7,
+// but 635 against 600 us at 1e7, and the Monte-Carlo search of a reference of
+// 1e6 613 against 463 us.
+constexpr float kNearCount = 256.0f;
+constexpr int kNearSteps = 4;   // rounds of up to eight lanes
+
+// One step: the count of the line at w; on return either r is known (true) or
+// w is the neighbouring line to look at.
+__device__ __forceinline__ bool near_step(uint32_t n, uint32_t cnt, uint32_t& w, uint32_t& r) {
+    if (cnt == 0u) {                       // r <= w
+        r = 0u;
+        if (w == 0u) return true;
+        w -= 32u;
+        return false;
+    }
+    r = w + cnt;
+    if (cnt < 32u) return true;
+    w += 32u;                              // r >= w
+    if (w >= n) return true;               // the array ends here: r = n
+    return false;
+}
+
+// first, the starts' density and the query -> the first line to look at, or
+// kNoLine for the full search; `done` when #{B_E < s} is 0 without a look.
+__device__ __forceinline__ uint32_t near_line(uint32_t n, uint32_t first, float dens, float mean, uint32_t s, uint32_t e,
+                                              bool& done) {
+    done = s == 0u;
+    const float est = dens * ((float)(e - s) + mean);
+    if (done || e == 0xFFFFFFFFu || !(est <= kNearCount)) return kNoLine;
+    const uint32_t back = 1u + (uint32_t)est;
+    return (first > back ? min(first - back, n - 1u) : 0u) & ~31u;
+}
+
+// RANK(array, 0 = B_S or 1 = B_E, x[NC], r[NC], dens[NC]) is the full search of
+// NC chains, LINE(K, w[NC], x[NC], cnt[NC]) counts lines (kNoLine: idle).
+template <int QPL, class RANK, class LINE>
+__device__ __forceinline__ void icount_near(const SearchArgs& sa, const uint32_t (&as)[QPL], const uint32_t (&ae)[QPL],
+                                            uint32_t (&cnt)[QPL], uint32_t (&fst)[QPL], RANK rank, LINE line) {
+    uint32_t x[QPL], r[QPL], w[QPL], c[QPL];
+    float dens[QPL];
+    bool open[QPL];
+#pragma unroll
+    for (int q = 0; q < QPL; ++q) x[q] = ae[q] + 1u;
+    rank(one_array(sa, 0), 0, x, r, dens);
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < QPL; ++q) {
+        fst[q] = (ae[q] == 0xFFFFFFFFu) ? sa.n : r[q];
+        x[q] = as[q];
+        bool done;
+        w[q] = near_line(sa.n, fst[q], dens[q], sa.mean_len, as[q], ae[q], done);
+        r[q] = 0u;
+        open[q] = !done;
+        any |= w[q] != kNoLine;
+    }
+    if (__ballot(any)) {
+        line(sa.be, w, x, c);
+#pragma unroll
+        for (int q = 0; q < QPL; ++q) {
+            if (w[q] != kNoLine && near_step(sa.n, c[q], w[q], r[q])) {
+                open[q] = false;
+                w[q] = kNoLine;
+            }
+        }
+    }
+    // the few lanes whose line did not decide
+#pragma unroll
+    for (int q = 0; q < QPL; ++q) {
+#pragma unroll 1
+        for (int step = 0; step < kNearSteps; ++step) {
+            uint64_t on = __ballot(w[q] != kNoLine);
+            if (!on) break;
+            const uint32_t k = few_windows<true>(sa.be, w[q], x[q], on);
+            if (((on >> (threadIdx.x & (kWave - 1))) & 1u) && near_step(sa.n, k, w[q], r[q])) {
+                open[q] = false;
+                w[q] = kNoLine;
+            }
+        }
+    }
+    any = false;
+#pragma unroll
+    for (int q = 0; q < QPL; ++q) any |= open[q];
+    if (__ballot(any)) {
+        uint32_t r2[QPL];
+#pragma unroll
+        for (int q = 0; q < QPL; ++q) x[q] = open[q] ? as[q] : 0u;   // 0 is below every key of a leaf
+        rank(one_array(sa, 1), 1, x, r2, dens);
+#pragma unroll
+        for (int q = 0; q < QPL; ++q)
+            if (open[q]) r[q] = r2[q];
+    }
+#pragma unroll
+    for (int q = 0; q < QPL; ++q) cnt[q] = fst[q] - r[q];
+}
+
+// The count through the model: the recorded error windows searched.
+template <int QPL>
+__device__ __forceinline__ void icount_learned(const SearchArgs& sa, uint32_t* scr, const uint32_t (&as)[QPL],
+                                               const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL], uint32_t (&fst)[QPL]) {
+    icount_near<QPL>(
+        sa, as, ae, cnt, fst,
+        [&](const Arrays& A, int, const uint32_t (&x)[QPL], uint32_t (&r)[QPL], float (&dens)[QPL]) {
+            rank_learned<QPL>(A, sa.fallbacks, scr, x, r, dens);
+        },
+        [&](const uint32_t* K, const uint32_t (&w)[QPL], const uint32_t (&x)[QPL], uint32_t (&c)[QPL]) {
+            probe_lines<QPL, true>(K, K, w, x, c, scr);
+        });
+}
+
+// One query at a time: the windows of more would not fit the registers.  Up to
+// kNearKeys keys both searches of a query run in step, which hides their waits
+// in each other's; above, the second search starts from the first one's rank.
 template <int QPL, bool DIRECT>
 __device__ __forceinline__ void icount_tiered(const SearchArgs& sa, const uint32_t* lds, const uint32_t (&as)[QPL],
                                               const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL],
                                               uint32_t (&fst)[QPL]) {
+    const uint32_t* tree_e = lds + (1u << sa.depth);
 #pragma unroll 1
     for (int q = 0; q < QPL; ++q) {
-        const uint32_t x[2] = {ae[q] + 1u, as[q]};
-        uint32_t r[2];
-        rank_tiered<2, DIRECT>(sa, lds, x, r);
-        const uint32_t first = (ae[q] == 0xFFFFFFFFu) ? sa.n : r[0];
-        cnt[q] = first - r[1];
-        fst[q] = first;
+        if (DIRECT || sa.n <= kNearKeys) {
+            const uint32_t x[2] = {ae[q] + 1u, as[q]};
+            uint32_t r[2];
+            float dens[2];
+            rank_tiered<2, DIRECT>(both_arrays(sa), lds, tree_e, sa.depth, x, r, dens);
+            const uint32_t first = (ae[q] == 0xFFFFFFFFu) ? sa.n : r[0];
+            cnt[q] = first - r[1];
+            fst[q] = first;
+        } else {
+            const uint32_t s1[1] = {as[q]}, e1[1] = {ae[q]};
+            uint32_t c1[1], f1[1];
+            icount_near<1>(
+                sa, s1, e1, c1, f1,
+                [&](const Arrays& A, int which, const uint32_t (&x)[1], uint32_t (&r)[1], float (&dens)[1]) {
+                    const uint32_t* tree = which ? tree_e : lds;
+                    rank_tiered<1, false>(A, tree, tree, sa.depth, x, r, dens);
+                },
+                [&](const uint32_t* K, const uint32_t (&w)[1], const uint32_t (&x)[1], uint32_t (&c)[1]) {
+                    const uint32_t at[1] = {w[0] == kNoLine ? 0u : w[0]};
+                    oct_windows<1, true>(K, K, at, x, c);
+                });
+            cnt[q] = c1[0];
+            fst[q] = f1[0];
+        }
     }
 }
 
@@ -791,10 +1038,25 @@ __device__ __forceinline__ void icount(const SearchArgs& sa, uint32_t* lds, cons
 }
 
 
+// Adds the workgroup's sum of v to *out with one atomic: all workgroups add to
+// one word, and thousands of such additions take longer than a small count
+// (1e6 queries against 3e5 with 8192 waves: 129 us with an atomic per wave,
+// 52 us with one per workgroup).  All threads call it.
+__device__ __forceinline__ void add_block_sum(uint64_t v, unsigned long long* out) {
+    __shared__ unsigned long long part[1024 / kWave];
+    v = wave_sum_u64(v);
+    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (uint32_t k = 1; k < blockDim.x / kWave; ++k) v += part[k];
+        if (v) atomicAdd(out, (unsigned long long)v);
+    }
+}
+
 // ------------------------------------------------------------------ counting kernel
 // Persistent grid over tiles of blockDim*QPL queries; query i of a tile is
 // loaded by lane (i mod blockDim), so every load of a query round is
-// coalesced.  Totals: uint64 wave sum, one atomic per wave.
+// coalesced.  Totals: uint64 sums, one atomic per workgroup.
 
 // MODE: kModePlain (LDS tree + bisection), kModeLearned (learned index,
 // error-window head probe + one line), kModeTiered (LDS tree + line-head
@@ -809,6 +1071,7 @@ BITS_SEARCH_KERNEL k_count(SearchArgs sa, const uint32_t* __restrict__ a_start,
         stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
         __syncthreads();
     }
+    if (MODE == kModeLearned || MODE == kModeTiered) sa.mean_len = mean_length(sa);
     const uint64_t tile = (uint64_t)blockDim.x * QPL;
     const uint64_t ntiles = (na + tile - 1) / tile;
     uint64_t acc = 0;
@@ -840,10 +1103,7 @@ BITS_SEARCH_KERNEL k_count(SearchArgs sa, const uint32_t* __restrict__ a_start,
         }
     }
     if (bad) atomicOr(sa.status, BITS_FLAG_INTERVAL);
-    if (total) {
-        acc = wave_sum_u64(acc);
-        if ((threadIdx.x & (kWave - 1)) == 0 && acc) atomicAdd(total, (unsigned long long)acc);
-    }
+    if (total) add_block_sum(acc, total);
 }
 
 // ------------------------------------------------------------------ decision
@@ -859,6 +1119,7 @@ BITS_SEARCH_KERNEL k_decide(SearchArgs sa, const uint32_t* __restrict__ a_start,
     __shared__ uint32_t stop;
     if (MODE != kModeLearned) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
     __syncthreads();
+    if (MODE == kModeLearned || MODE == kModeTiered) sa.mean_len = mean_length(sa);
     const uint64_t tile = (uint64_t)blockDim.x * QPL;
     const uint64_t ntiles = (na + tile - 1) / tile;
     uint32_t bad = 0;
@@ -937,6 +1198,7 @@ BITS_SEARCH_KERNEL k_mc(SearchArgs sa, const uint32_t* __restrict__ a_start, con
     if (MODE != kModeLearned) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
     for (uint32_t k = threadIdx.x; k < kMaxChunk; k += blockDim.x) acc[k] = 0ull;
     __syncthreads();
+    if (MODE == kModeTiered) sa.mean_len = mean_length(sa);
     const uint64_t tile = (uint64_t)blockDim.x * QPL;
     const uint64_t nchunks = (nshuf + chunk - 1) / chunk;
     const uint32_t ng = (gridDim.x >= kXcds && tiles >= kXcds) ? kXcds : 1u;
@@ -1377,6 +1639,7 @@ BITS_SEARCH_KERNEL k_count_rounds(SearchArgs sa0, uint64_t stride, uint32_t roun
     sa.hs += r * stride;
     sa.he += r * stride;
     stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
+    if (MODE == kModeTiered) sa.mean_len = mean_length(sa);
     __syncthreads();
     const uint64_t tiles = (na + blockDim.x - 1) / blockDim.x;
     uint32_t bad = 0;
@@ -1393,8 +1656,7 @@ BITS_SEARCH_KERNEL k_count_rounds(SearchArgs sa0, uint64_t stride, uint32_t roun
         icount<1, MODE>(sa, lds, as, ae, cnt, fst);
         sum += valid ? cnt[0] : 0u;
     }
-    sum = wave_sum_u64(sum);
-    if ((threadIdx.x & (kWave - 1)) == 0 && sum) atomicAdd(totals + r, (unsigned long long)sum);
+    add_block_sum(sum, totals + r);
     if (bad && sa.status) atomicOr(sa.status, BITS_FLAG_INTERVAL);
 }
 
@@ -1596,6 +1858,7 @@ __global__ void __launch_bounds__(1024)
             sa.n = R.n;
             sa.tree_stride = R.tree_stride;
             sa.depth = LEARNED ? 0u : min(R.depth, max_depth);
+            sa.mean_len = MODE != kModePlain && R.n ? mean_length(sa) : 0.0f;
             if (!LEARNED) {
                 __syncthreads();
                 stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
@@ -1651,8 +1914,9 @@ __global__ void __launch_bounds__(256) k_rmi_window(SearchArgs sa, uint32_t whic
         const uint64_t i = t * blockDim.x + threadIdx.x;
         const uint32_t xi = i < n ? xs[i] : 0u;
         uint32_t x[2] = {xi, xi}, base[2], wl[2], wr[2], rlo[2], rhi[2];
+        float dens[2];
         bool win[2];
-        learned_windows<2>(sa, scr, x, base, wl, wr, rlo, rhi, win);
+        learned_windows<2>(both_arrays(sa), scr, x, base, wl, wr, rlo, rhi, win, dens);
         if (i < n) {
             lo[i] = win[which] ? wl[which] : base[which];
             hi[i] = win[which] ? wr[which] : base[which];

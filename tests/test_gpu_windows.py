@@ -97,3 +97,43 @@ def test_resort_rounds(nb, rounds, batch):
     for name in ("totals", "observed", "n_ge", "n_le"):
         assert torch.equal(getattr(got, name).view(torch.int64), getattr(exp, name).view(torch.int64)), name
     assert int(status.item()) == (bits.BITS_FLAG_CHROM if nb > 50 else 0)
+
+
+def near_sets(n, rng):
+    """References and queries that the second search's start near the first one's rank does not fit: long
+    intervals on either side, many equal keys, intervals with start > end in B (not checked there: the
+    difference of the two ranks then wraps), the first and last coordinates."""
+    s = np.concatenate([rng.integers(0, 2_900_000_000, n - n // 2),
+                        rng.normal(1_000_000_000, 40_000, n // 2).astype(np.int64)])
+    e = s + np.where(rng.random(n) < 0.01, rng.integers(0, 3_000_000, n), rng.integers(0, 900, n))
+    swap = rng.random(n) < 0.02
+    s[swap], e[swap] = e[swap], s[swap]
+    s[: n // 50] = 1_000_000_100
+    m = 20_000
+    a = rng.integers(0, 2_950_000_000, m)
+    a[: m // 2] = rng.normal(1_000_000_000, 60_000, m // 2).astype(np.int64)
+    z = a + np.where(rng.random(m) < 0.1, rng.integers(0, 100_000_000, m), rng.integers(0, 700, m))
+    z[:3], a[1:4] = TOP, 0
+    a[4:8], z[4:8] = 1_000_000_100, 1_000_000_100
+    return s, e, a, np.minimum(z, TOP)
+
+
+@pytest.mark.parametrize("n", [1, 33, 5_000, 300_007])
+def test_second_rank_next_to_the_first(n):
+    print("case: near", n, flush=True)
+    s, e, a, z = near_sets(n, np.random.default_rng(n))
+    exp = (np.searchsorted(np.sort(s), z, "right") - np.searchsorted(np.sort(e), a, "left")) % 2**32
+    ref = bits.bits_sort_ref(up(s), up(e), learned=True, train={"epochs": 10})
+    for launch in (None, {"path": 2, "block": 256, "qpl": 1}, {"path": 2, "qpl": 4}, {"path": 3}, {"path": 1}):
+        counts, _ = bits.bits_count_per_query(ref, up(a), up(z), launch=launch)
+        assert np.array_equal(counts.cpu().numpy().astype(np.int64), exp), launch
+
+
+def test_second_rank_next_to_the_first_large():
+    n = (1 << 24) + 77
+    s, e, a, z = near_sets(n, np.random.default_rng(9))
+    exp = (np.searchsorted(np.sort(s), z, "right") - np.searchsorted(np.sort(e), a, "left")) % 2**32
+    ref = bits.bits_sort_ref(up(s), up(e))
+    for launch in (None, {"path": 3, "depth": 0, "block": 256, "qpl": 2}, {"path": 3, "depth": 7}):
+        counts, _ = bits.bits_count_per_query(ref, up(a), up(z), launch=launch)
+        assert np.array_equal(counts.cpu().numpy().astype(np.int64), exp), launch

@@ -22,7 +22,7 @@
 //            slice ranks at equally spaced coordinates (a piecewise-constant
 //            CDF of the slice), and each placement of each shuffle of the
 //            batch is counted by two table lookups, each followed by a
-//            bisection of the few keys of its bucket, all in LDS; the
+//            comparison with the few keys of its bucket, all in LDS; the
 //            per-shuffle sums are written out;
 //   reduce   per shuffle: the sums over regions (and shares) are added to the
 //            totals.
@@ -42,11 +42,21 @@ constexpr uint32_t kMinShift = 10;         // cells are at least 1 kbp
 constexpr uint32_t kRegionKeys = 8192;     // merged B_S + B_E keys per region (target)
 constexpr uint32_t kMargin = 256;          // B_S keys staged past a region's end
 constexpr uint32_t kSliceWords = 12800;    // LDS slice capacity of the search kernel (50 KiB)
-// Bucket tables of the search kernel: a region's coordinate range is cut
-// into at most kBuckets equal power-of-two buckets; word b of a table is the
-// slice rank of bucket b's first coordinate (b = 0 .. buckets, the last one
-// closing the final bucket).
-constexpr uint32_t kBuckets = 1536;
+// Bucket tables of the search kernel: a region's coordinate range is cut into
+// at most kBuckets equal buckets; entry b of a table (16 bits: a slice has
+// fewer than 2^16 keys) is the number of slice keys in the buckets before b
+// (b = 0 .. buckets, the last one closing the final bucket).
+constexpr uint32_t kBuckets = 3072;
+// Keys compared from a bucket's first on: kFirstKeys by every lane, the others
+// by the lanes whose first ones all count, and past kBucketKeys (as many words
+// of 0xFFFFFFFF follow each slice) a bisection.  LDS bank conflicts price each
+// word a full wave reads: six by every lane took 1.5 times the LDS cycles.
+constexpr uint32_t kFirstKeys = 2, kBucketKeys = 5;
+// Record loads a wave of the search keeps in flight.  One is too few: 29 waves
+// a CU x 512 B x 256 CUs in about 2 us is what the search then read per second.
+// 1e9 records, all passes: 1, 2, 3, 4, 6 loads 3860, 3470, 3360, 3310, 3280 us.
+constexpr uint32_t kAhead = 4;
+static_assert(kSliceWords < (1u << 16), "slice ranks are 16-bit");
 constexpr uint32_t kBinThreads = 1024;
 constexpr int ILP = 4;   // table entries each binning thread loads before it places them
 // A reference with few regions (a small B) would leave most of the chip idle
@@ -564,113 +574,158 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     }
 }
 
-// Wave-level segmented sum: lanes carry (key, value) with the keys of the
-// valid lanes non-decreasing in lane order; each run of equal keys adds its
-// sum to acc[key] with at most two LDS atomics (the run's inclusive prefix at
-// its last lane, minus the prefix before its first lane, which is that lane's
-// inclusive prefix minus its own value).  T = uint32_t only when 64 values
-// cannot reach 2^32.
-template <typename T>
-__device__ __forceinline__ void wave_segment_add(uint32_t key, T v, bool valid, unsigned long long* acc) {
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    const T x = wave_inclusive_scan<T>(v);
-    // the neighbours' keys by whole-wave DPP shifts (wave_shr:1, wave_shl:1); lane 0's kp and
-    // lane 63's kn are never used
-    const uint32_t kp = dpp_in0<0x138, 0xF>(key), kn = dpp_in0<0x130, 0xF>(key);
-    if (!valid) return;
-    if (lane == kWave - 1 || kn != key) atomicAdd(&acc[key], (unsigned long long)x);
-    if (lane != 0 && kp != key) atomicAdd(&acc[key], 0ull - (unsigned long long)(x - v));
+// Lane i's value in every lane of the wave (i uniform).
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t i) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)i);
 }
 
-// R[b] = #{K[0..m) < key_lo + b 2^sh} for b = 0 .. nb, K sorted with
-// K[0] >= key_lo.  With F(x) = (x - key_lo) >> sh, the largest b whose
-// coordinate is <= x, key j writes j to the buckets in (F(K[j - 1]), F(K[j])]
-// and a final step j = m fills the rest up to nb: every bucket is written
-// once, in one pass over the keys.
-__device__ void bucket_ranks(const uint32_t* K, uint32_t m, uint32_t key_lo, uint32_t sh, uint32_t nb, uint32_t* R) {
+__device__ __forceinline__ uint64_t lane_value(uint64_t x, uint32_t i) {
+    return ((uint64_t)lane_value((uint32_t)(x >> 32), i) << 32) | lane_value((uint32_t)x, i);
+}
+
+// A wave-uniform word read from LDS, in a scalar register.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+
+// Buckets over the coordinates [lo, lo + span): bucket of x = (x - lo) scale >> 32.
+// T[b] = #{keys of the slice in the buckets before b}; the keys of bucket b
+// are ranks [T[b], T[b + 1]).
+struct Buckets {
+    const uint16_t* T;
+    uint32_t lo, scale;
+    __device__ __forceinline__ uint32_t of(uint32_t x) const { return __umulhi(x - lo, scale); }
+};
+
+// The number of buckets over `span` > 0 coordinates for m keys (three for four
+// keys: a small slice is not worth a long table), and the scale.  The
+// factor 1 - 2^-20 covers the float roundings (3 x 2^-24), so that
+// scale <= 2^32 nb / span and the last coordinate's bucket is below nb.
+__device__ __forceinline__ uint32_t bucket_scale(uint32_t m, uint32_t span, uint32_t* scale) {
+    const uint32_t nb = min(min(kBuckets, m - m / 4u + 1u), span);
+    *scale = (uint32_t)((float)nb * 4294967296.f / (float)span * (1.f - 0x1p-20f));
+    return nb;
+}
+
+// T[b] for b = 0 .. nb, K[0..m) sorted with K[0] >= bk.lo.  With F(x) the
+// bucket of x, or nb past the last, key j writes j to the buckets in
+// (F(K[j - 1]), F(K[j])] and a final step j = m fills the rest up to nb: every
+// bucket is written once, in one pass over the keys.
+__device__ void bucket_ranks(const uint32_t* K, uint32_t m, const Buckets& bk, uint32_t nb, uint16_t* T) {
     for (uint32_t j = threadIdx.x; j <= m; j += blockDim.x) {
-        const uint32_t lo = j == 0 ? 0u : min((K[j - 1] - key_lo) >> sh, nb) + 1u;
-        const uint32_t hi = j == m ? nb : min((K[j] - key_lo) >> sh, nb);
-        for (uint32_t b = lo; b <= hi; ++b) R[b] = j;
+        const uint32_t lo = j == 0 ? 0u : min(bk.of(K[j - 1]), nb) + 1u;
+        const uint32_t hi = j == m ? nb : min(bk.of(K[j]), nb);
+        for (uint32_t b = lo; b <= hi; ++b) T[b] = (uint16_t)j;
     }
+}
+
+// #{K < x} (STRICT) or #{K <= x} in a slice, x inside the buckets: the keys
+// before x's bucket, and those of its first kBucketKeys keys that count.  Keys
+// of later buckets are above x, and so is the padding (x < 0xFFFFFFFF), so no
+// bound is looked up; only a bucket with more keys below x is bisected on.
+template <bool STRICT>
+__device__ __forceinline__ uint32_t rank_buckets(const uint32_t* K, const Buckets& bk, uint32_t x) {
+    const uint32_t b = bk.of(x), lo = bk.T[b];
+    const uint32_t* k = K + lo;
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kFirstKeys; ++i) c += STRICT ? (k[i] < x) : (k[i] <= x);
+    if (c != kFirstKeys) return lo + c;
+#pragma unroll
+    for (uint32_t i = kFirstKeys; i < kBucketKeys; ++i) c += STRICT ? (k[i] < x) : (k[i] <= x);
+    if (c == kBucketKeys) c += rank_bucket<STRICT>(k + kBucketKeys, bk.T[b + 1] - lo - kBucketKeys, x);
+    return lo + c;
 }
 
 // The placements of one region, counted against slices S = B_S[s_lo, s_lo + ns)
 // and E = B_E[e_lo, e_lo + ne) (in LDS, or in HBM for an oversize region):
 // the workgroup's share [q0, q1) of the region's records.  Each wave takes a
-// contiguous range of it, 64 records per step; records are grouped by
-// shuffle (pre[s] = first record of shuffle s), so a wave tracks its shuffle
-// by a forward scan and adds per-shuffle sums with wave_segment_add.
-// Bucket geometry of a region [key_lo, key_hi): bucket of x = (x - key_lo) >> sh.
-// On the LDS path, TS / TE hold word b = rank(v_b), v_b = key_lo + b 2^sh,
-// the ranks being #{S < v} and #{E < v} in the slices; bucket b's keys are
-// ranks [TS[b], TS[b + 1]).
-struct Buckets {
-    const uint32_t* TS;
-    const uint32_t* TE;
-    uint32_t key_lo, key_hi, sh;
-};
-
+// contiguous range of it, 64 records per step; record p of the pass
+// (p < pre[nb] < 2^32) is recs[base[s] + p], s its shuffle, pre[s] <= p <
+// pre[s + 1].  The wave walks the shuffles with scalars: a step's counts are
+// summed up to every lane, and where a shuffle ends its part of the sums, read
+// from its last lane, goes to acc[s].
+// Vector issue (75% of the cycles) and the LDS (58%) bound this loop, 81 vector
+// instructions per 64 records.  Half as many buckets of power-of-two widths,
+// bisected, shuffles tracked by each lane, a segmented sum with two LDS atomics
+// a run and one load ahead took 124 (1e9 records against 5e7 keys: 3700 -> 3310
+// us; 2e8 against 1e6: 775 -> 684 us).
 template <bool LDS, typename T>
 __device__ __forceinline__ void bin_count_region(const uint32_t* S, uint32_t ns, const uint32_t* E, uint32_t ne,
                                                  const uint32_t* __restrict__ bs, uint32_t n, uint32_t s_lo,
-                                                 uint32_t e_lo, const Buckets& bk, const uint2* __restrict__ recs,
+                                                 uint32_t e_lo, const Buckets& bks, const Buckets& bke,
+                                                 uint32_t key_top, const uint2* __restrict__ recs,
                                                  const uint32_t* pre, const uint32_t* base, uint32_t nb,
                                                  uint64_t q0, uint64_t q1, unsigned long long* acc) {
-    const uint32_t lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    const uint32_t lane = threadIdx.x & (kWave - 1), wv = uniform(threadIdx.x / kWave), nw = blockDim.x / kWave;
     const uint64_t steps = (q1 - q0 + kWave - 1) / kWave, per = (steps + nw - 1) / nw;
     const uint64_t p0 = q0 + (uint64_t)wv * per * kWave, p1 = min(q1, p0 + per * kWave);
     if (p0 >= p1) return;
-    // record p of the pass (p < pre[nb] < 2^32) is recs[base[s] + p], s its shuffle
     const uint32_t s_end = s_lo + ns;
     // shuffle of the wave's first record: the last s with pre[s] <= p0
-    uint32_t sw = 0, hi = nb;
-    while (hi - sw > 1) {
-        const uint32_t mid = (sw + hi) >> 1;
-        if (pre[mid] <= p0) sw = mid; else hi = mid;
+    uint32_t sc = 0, hi = nb;
+    while (hi - sc > 1) {
+        const uint32_t mid = (sc + hi) >> 1;
+        if (uniform(pre[mid]) <= p0) sc = mid; else hi = mid;
     }
-    // Software pipeline: the record of the next step is loaded before this
-    // step's searches, so a wave has two record loads in flight.  A lane's
-    // shuffle only moves forward, as its record index grows by 64 a step.
-    uint32_t sl = sw;
-    uint2 rn = make_uint2(0u, 0u);
-    if (p0 + lane < p1) {
-        const uint32_t p = (uint32_t)p0 + lane;
-        while (pre[sl + 1] <= p) ++sl;   // ends at sl < nb: p < pre[nb]
-        rn = recs[base[sl] + p];
-    }
-    for (uint64_t b = p0; b < p1; b += kWave) {
-        const bool valid = b + lane < p1;
-        const uint32_t slc = sl;
-        const uint2 r = rn;
-        if (b + kWave + lane < p1) {
-            const uint32_t p = (uint32_t)(b + kWave) + lane;
-            while (pre[sl + 1] <= p) ++sl;
-            rn = recs[base[sl] + p];
+    uint32_t end_c = uniform(pre[sc + 1]);   // the end of the counted step's shuffle
+    // the shuffle of the records being loaded, a step ahead, so that a wave has
+    // two record loads in flight
+    uint32_t sn = sc, end_n = end_c, base_n = uniform(base[sc]);
+    auto load = [&](uint64_t b) {   // records [b, min(b + 64, p1)), b < p1
+        const uint32_t e = (uint32_t)min(p1, b + kWave), p = (uint32_t)b + lane;
+        uint32_t at = base_n + p;
+        while (end_n < e) {   // ends at sn < nb: e <= pre[nb]
+            const uint32_t from = end_n;
+            ++sn;
+            end_n = uniform(pre[sn + 1]);
+            base_n = uniform(base[sn]);
+            if (p >= from) at = base_n + p;
         }
-        T v = 0;
-        if (valid) {
-            uint32_t first, last;
-            if (LDS && r.y < bk.key_hi) {
-                // every key <= r.y is below key_hi, so inside the slice: the bucket's keys decide
-                const uint32_t b = (r.y - bk.key_lo) >> bk.sh, lo = bk.TS[b];
-                first = s_lo + lo + rank_bucket<false>(S + lo, bk.TS[b + 1] - lo, r.y);
-            } else if (r.y == 0xFFFFFFFFu) {
-                first = n;
-            } else {
-                const uint32_t c = rank_in<false>(S, ns, r.y);
-                first = (c == ns && s_end < n) ? gallop_le(bs, n, s_end, r.y) : s_lo + c;
-            }
-            if (LDS) {   // key_lo <= r.x < key_hi: the start lies in the region
-                const uint32_t b = (r.x - bk.key_lo) >> bk.sh, lo = bk.TE[b];
-                last = e_lo + lo + rank_bucket<true>(E + lo, bk.TE[b + 1] - lo, r.x);
-            } else {
-                last = e_lo + rank_in<true>(E, ne, r.x);
-            }
-            v = (T)(first - last);
+        return lane < e - (uint32_t)b ? recs[at] : make_uint2(bke.lo, bke.lo);
+    };
+    unsigned long long run = 0ull;   // of shuffle sc, in the steps so far
+    auto count = [&](uint64_t b, uint2 r) {   // the step of records [b, min(b + 64, p1))
+        uint32_t first, last;
+        if (LDS && r.y < key_top) {   // every key <= r.y is inside the slice
+            first = s_lo + rank_buckets<false>(S, bks, r.y);
+        } else if (r.y == 0xFFFFFFFFu) {
+            first = n;
+        } else {
+            const uint32_t c = rank_in<false>(S, ns, r.y);
+            first = (c == ns && s_end < n) ? gallop_le(bs, n, s_end, r.y) : s_lo + c;
         }
-        wave_segment_add<T>(valid ? slc : 0xFFFFFFFFu, v, valid, acc);
+        if (LDS)   // the start lies in the region
+            last = e_lo + rank_buckets<true>(E, bke, r.x);
+        else
+            last = e_lo + rank_in<true>(E, ne, r.x);
+        const uint32_t e = (uint32_t)min(p1, b + kWave), got = e - (uint32_t)b;
+        const T x = wave_inclusive_scan<T>(lane < got ? (T)(first - last) : (T)0);
+        T before = 0;
+        while (end_c <= e) {   // end_c > b: shuffle sc ends in this step
+            const T upto = lane_value(x, end_c - 1u - (uint32_t)b);
+            run += (T)(upto - before);
+            before = upto;
+            if (lane == 0) atomicAdd(&acc[sc], run);
+            run = 0ull;
+            if (++sc == nb) break;
+            end_c = uniform(pre[sc + 1]);
+        }
+        run += (T)(lane_value(x, kWave - 1) - before);
+    };
+    uint2 rn[kAhead];
+#pragma unroll
+    for (uint32_t u = 0; u < kAhead; ++u)
+        if (p0 + u * kWave < p1) rn[u] = load(p0 + u * kWave);
+    for (uint64_t b0 = p0; b0 < p1; b0 += kAhead * kWave) {
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u) {
+            const uint64_t b = b0 + u * kWave;
+            if (b >= p1) break;
+            const uint2 r = rn[u];
+            if (b + kAhead * kWave < p1) rn[u] = load(b + kAhead * kWave);
+            count(b, r);
+        }
     }
+    if (lane == 0 && run) atomicAdd(&acc[sc], run);   // run = 0 once sc = nb
 }
 
 // `splits` workgroups per region r < nreg (nreg on the device; workgroups past
@@ -683,8 +738,8 @@ __global__ void __launch_bounds__(kBinThreads) k_bin_search(
     const RegionDesc* __restrict__ desc, const uint64_t* __restrict__ nreg_p, const uint32_t* __restrict__ seg_start,
     const uint32_t* __restrict__ seg_cnt, uint32_t nreg_max, uint32_t nb, const uint2* __restrict__ recs,
     uint64_t na, uint32_t splits, unsigned long long* __restrict__ partial) {
-    __shared__ uint32_t slice[kSliceWords + 1];   // + 1: the word an empty last bucket reads
-    __shared__ uint32_t tabs[2 * (kBuckets + 1)];
+    __shared__ uint32_t slice[kSliceWords + 2 * kBucketKeys];   // both slices, each with its padding
+    __shared__ uint16_t tabs[2][kBuckets + 1];
     __shared__ uint32_t pre[BITS_MC_BIN_MAX_BATCH + 1];
     __shared__ uint32_t base[BITS_MC_BIN_MAX_BATCH];
     __shared__ unsigned long long acc[BITS_MC_BIN_MAX_BATCH];
@@ -728,19 +783,22 @@ __global__ void __launch_bounds__(kBinThreads) k_bin_search(
             partial[(SPLIT ? (uint64_t)r * splits + part : (uint64_t)r) * nb + threadIdx.x] = 0ull;
         return;
     }
-    const uint32_t eo = ns;   // E's first word
+    const uint32_t eo = ns + kBucketKeys;   // E's first word
     const bool in_lds = (uint64_t)ns + ne <= kSliceWords;
-    // buckets: the least power-of-two width that cuts [key_lo, key_hi) into at most kBuckets
-    Buckets bk{tabs, tabs + kBuckets + 1, d0.key_lo, d1.key_lo, 0u};
-    const uint32_t span = bk.key_hi - bk.key_lo;   // > 0: a region holds at least one cell
-    while (((span - 1u) >> bk.sh) >= kBuckets) ++bk.sh;
-    const uint32_t nbk = ((span - 1u) >> bk.sh) + 1u;
+    // E's buckets cover the region, S's an eighth more, for the ends that cross
+    // the region's end (not past the last staged key: up to it, every key is staged)
+    const uint32_t key_lo = d0.key_lo, span = d1.key_lo - key_lo;   // > 0: a region holds at least one cell
+    uint32_t key_top = d1.key_lo + min(span / 8u, 0xFFFFFFFFu - d1.key_lo);
+    Buckets bks{tabs[0], key_lo, 0u}, bke{tabs[1], key_lo, 0u};
     if (in_lds) {
         for (uint32_t j = threadIdx.x; j < ns; j += blockDim.x) slice[j] = bs[s_lo + j];
         for (uint32_t j = threadIdx.x; j < ne; j += blockDim.x) slice[eo + j] = be[e_lo + j];
+        if (threadIdx.x < kBucketKeys) slice[ns + threadIdx.x] = slice[eo + ne + threadIdx.x] = 0xFFFFFFFFu;
         __syncthreads();
-        bucket_ranks(slice, ns, bk.key_lo, bk.sh, nbk, tabs);
-        bucket_ranks(slice + eo, ne, bk.key_lo, bk.sh, nbk, tabs + kBuckets + 1);
+        if (s_end < n) key_top = min(key_top, max(slice[ns - 1], d1.key_lo));
+        const uint32_t nbs = bucket_scale(ns, key_top - key_lo, &bks.scale), nbe = bucket_scale(ne, span, &bke.scale);
+        bucket_ranks(slice, ns, bks, nbs, tabs[0]);
+        bucket_ranks(slice + eo, ne, bke, nbe, tabs[1]);
     }
     __syncthreads();
     // this workgroup's share of the region's records
@@ -749,17 +807,17 @@ __global__ void __launch_bounds__(kBinThreads) k_bin_search(
     // per-step sums fit 32 bits when 64 counts of at most n cannot reach 2^32
     const bool narrow = n < (1u << 26);
     if (in_lds && narrow)
-        bin_count_region<true, uint32_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bk, recs, pre, base, nb,
-                                         q0, q1, acc);
+        bin_count_region<true, uint32_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                         recs, pre, base, nb, q0, q1, acc);
     else if (in_lds)
-        bin_count_region<true, uint64_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bk, recs, pre, base, nb,
-                                         q0, q1, acc);
+        bin_count_region<true, uint64_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                         recs, pre, base, nb, q0, q1, acc);
     else if (narrow)
-        bin_count_region<false, uint32_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bk, recs, pre, base,
-                                          nb, q0, q1, acc);
+        bin_count_region<false, uint32_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                          recs, pre, base, nb, q0, q1, acc);
     else
-        bin_count_region<false, uint64_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bk, recs, pre, base,
-                                          nb, q0, q1, acc);
+        bin_count_region<false, uint64_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                          recs, pre, base, nb, q0, q1, acc);
     __syncthreads();
     if (threadIdx.x < nb)
         partial[(SPLIT ? (uint64_t)r * splits + part : (uint64_t)r) * nb + threadIdx.x] = acc[threadIdx.x];

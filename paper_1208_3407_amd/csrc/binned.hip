@@ -325,6 +325,10 @@ constexpr uint32_t kStageRegions = 2048;
 constexpr uint32_t kStageMinRegions = 128;
 constexpr uint32_t kStageRecs = 5632;      // 44 KB
 constexpr int kStagePer = (kStageRecs + kBinThreads - 1) / kBinThreads;
+// A group of at most kGroupRecs entries is placed once and held in registers.
+constexpr int kGroupPer = 8;
+constexpr uint32_t kGroupRecs = kGroupPer * kBinThreads;
+static_assert(kGroupRecs < (1u << 16), "places in a group are 16-bit");
 static_assert(kStageRegions <= 2 * kBinThreads, "one thread owns two regions' chunk counters");
 static_assert(kStageRecs < (1u << 16), "chunk counts and offsets are 16-bit");
 static_assert(kMaxCells <= (1u << 16), "cell-to-region table entries are 16-bit");
@@ -334,23 +338,25 @@ __device__ __forceinline__ uint32_t half16(const uint32_t* w, uint32_t j) {
     return (w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
 }
 
-// Binning of shuffles [sb, sb + nb): workgroup (k, s) makes the placements of
-// chromosome k's queries (table positions [cursor[k] - hist[k], cursor[k]))
-// in shuffle sb + s, counts them per region, writes the segment table of
-// (s, every region of k), and writes the records {start, end} in region
-// order to recs[s * na + table position range], either one by one (few
-// regions, or more than kStageRegions) or chunk by chunk through LDS.  A
-// group that fits one chunk is placed only once: its chunk's region counts
-// are the segment table and the chunk is its final layout.
+// Binning of shuffles [sb, sb + nb): a workgroup makes the placements of one
+// chromosome k's queries (table positions [cursor[k] - hist[k], cursor[k])) in
+// one shuffle s, or in `per` shuffles in turn (MANY), counts them per region,
+// writes the segment table of (s, every region of k), and writes the records
+// {start, end} in region order to recs[s * na + table position range].  A group
+// of at most kGroupRecs entries is placed once and held in registers; a larger
+// one is placed twice, to count and to write, either one by one (few regions,
+// or more than kStageRegions) or chunk by chunk through LDS.
 // (8 waves per SIMD: two workgroups per CU, at most 64 VGPRs.)
-// LOOKUP, for fewer queries than half the genome's cells: such a group reads a
-// placement's region from memory and leaves the LDS table, a load per cell,
-// out (2000 queries x 100 shuffles: 25.3 -> 22.2 us; as a branch in one kernel
-// it costs 1e5 x 2000 1%).
-template <bool LOOKUP>
+// Vector instructions, the Philox rounds above all, bound large groups (1e9
+// placements 5240 us, 1600 of them the counting sweep).  A workgroup of 4000
+// entries spends half its time on its start, the region table and the chain
+// of loads and barriers before its first store, so it takes several shuffles
+// (1e5 entries in 24 chromosomes x 2000 shuffles: 800 -> 648 us; 2000 x 100:
+// 21.3 -> 18.9 us).
+template <bool MANY>
 __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     BinGeom g, const uint2* __restrict__ packed, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ cursor,
-    uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, const uint32_t* __restrict__ cell_region,
+    uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, uint32_t per, const uint32_t* __restrict__ cell_region,
     const uint64_t* __restrict__ nreg_p, uint32_t nreg_max, uint32_t* __restrict__ seg_start,
     uint32_t* __restrict__ seg_cnt, uint2* __restrict__ recs) {
     __shared__ uint16_t cr[kMaxCells];
@@ -360,7 +366,8 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     __shared__ uint2 stage[kStageRecs];             // the chunk's records in region order; h of the direct path
     __shared__ uint32_t wsum[kBinThreads / kWave];
     __shared__ uint32_t staged_total;
-    const uint32_t k = blockIdx.x / nb, s = blockIdx.x - k * nb;
+    const uint32_t wgs = MANY ? (nb + per - 1u) / per : nb, k = blockIdx.x / wgs;
+    const uint32_t s0 = (blockIdx.x - k * wgs) * (MANY ? per : 1u), s1 = MANY ? min(nb, s0 + per) : s0 + 1u;
     const uint32_t c0 = g.cb[k], nc = g.cb[k + 1] - c0;
     if (nc == 0) return;
     const uint32_t nreg = (uint32_t)*nreg_p;
@@ -372,64 +379,71 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     const bool staged = nr >= kStageMinRegions && nr <= kStageRegions;
     uint32_t* h = staged ? hs : reinterpret_cast<uint32_t*>(stage);   // kMaxCells words fit the stage buffer
     const uint32_t g1 = cursor[k], g0 = g1 - hist[k];
-    const bool lookup = LOOKUP && g1 - g0 <= kStageRecs && nr <= kStageRegions;
-    if (!lookup) {
-        for (uint32_t j = threadIdx.x; j < nc; j += blockDim.x) cr[j] = (uint16_t)(cell_region[c0 + j] - rb);
-        for (uint32_t j = threadIdx.x; j < nr; j += blockDim.x) h[j] = 0u;
-        __syncthreads();
-    }
+    const bool whole = g1 - g0 <= kGroupRecs && nr <= kStageRegions;
+    for (uint32_t j = threadIdx.x; j < nc; j += kBinThreads) cr[j] = (uint16_t)(cell_region[c0 + j] - rb);
     const uint32_t ok = g.off[k], sh = g.shift, clen = g.off[k + 1] - g.off[k];
-    const uint64_t gs = (sb + s) * na;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-    if (g1 - g0 <= kStageRecs && nr <= kStageRegions) {
-        // The group fits one LDS chunk: every entry is placed once and ranked in its
-        // region, the counts give the segment table directly, and the chunk in region
-        // order is the group's final layout (written out sequentially).
-        const uint32_t nw2 = (nr + 1) >> 1;
-        const bool owner = threadIdx.x < nw2;
+    const uint32_t nw2 = (nr + 1) >> 1;
+    const bool owner = threadIdx.x < nw2;
+    if (whole) {
+        // Every entry is placed once and kept, with its rank in its region, in registers;
+        // the counts give the segment table directly, and the records in region order are
+        // the group's final layout, written out sequentially in windows of kStageRecs.  The
+        // next shuffle's ranking touches only the counters, so it may overlap the write-out.
         if (owner) cc[threadIdx.x] = 0u;
         __syncthreads();
-        uint32_t st_[kStagePer], len_[kStagePer], key_[kStagePer];   // key = lr << 16 | rank, or ~0
-        auto place = [&](auto region_of) {
+        for (uint32_t s = s0; s < s1; ++s) {
+            const uint64_t gs = (sb + s) * na;
+            uint32_t st_[kGroupPer], len[kGroupPer], key[kGroupPer];   // key: region << 16 | rank in it, or ~0
+            // the entries are read again for every shuffle (they stay in L2): held, they and
+            // what the compiler derives from them spill
+            uint32_t from = g0 + threadIdx.x;
+            if (MANY) asm volatile("" : "+v"(from));
 #pragma unroll
-            for (int u = 0; u < kStagePer; ++u) {
-                const uint32_t p = g0 + threadIdx.x + (uint32_t)u * blockDim.x;
+            for (int u = 0; u < kGroupPer; ++u) {
+                key[u] = 0xFFFFFFFFu;
+                st_[u] = len[u] = 0u;
+                if (g0 + (uint32_t)u * kBinThreads >= g1) continue;   // uniform
+                const uint32_t p = from + (uint32_t)u * kBinThreads;
                 const uint2 q = p < g1 ? packed[p] : make_uint2(0u, 0u);
-                key_[u] = 0xFFFFFFFFu;
-                st_[u] = 0u;
-                len_[u] = q.y;
+                len[u] = q.y;
                 if (!q.y) continue;
                 const uint32_t st = mc_place(gs + q.x, k0, k1, ok, clen - q.y + 1u);
-                const uint32_t lr = region_of((st - ok) >> sh);
+                const uint32_t lr = cr[(st - ok) >> sh];
                 if (lr >= nr) continue;
                 const uint32_t sft = 16u * (lr & 1u);
                 const uint32_t old = atomicAdd(&cc[lr >> 1], 1u << sft);
                 st_[u] = st;
-                key_[u] = (lr << 16) | ((old >> sft) & 0xFFFFu);
+                key[u] = (lr << 16) | ((old >> sft) & 0xFFFFu);
             }
-        };
-        if (LOOKUP)
-            place([&](uint32_t cell) { return cell_region[c0 + cell] - rb; });
-        else
-            place([&](uint32_t cell) { return (uint32_t)cr[cell]; });
-        __syncthreads();
-        {
+            __syncthreads();   // counts complete; the previous shuffle is written out
             const uint32_t wv = owner ? cc[threadIdx.x] : 0u;
             const uint32_t a0 = wv & 0xFFFFu, a1 = wv >> 16, tsum = a0 + a1;
             const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-            const uint32_t x = wave_inclusive_scan<uint32_t>(tsum);
-            if (lane == kWave - 1) wsum[w] = x;
-            __syncthreads();
-            uint32_t pre = 0, tot = 0;
-            for (uint32_t j = 0; j < kBinThreads / kWave; ++j) {
-                if (j < w) pre += wsum[j];
-                tot += wsum[j];
+            uint32_t pre = 0;
+            if (nw2 <= kWave) {   // the first wave owns all the counters
+                if (w == 0) {
+                    const uint32_t x = wave_inclusive_scan<uint32_t>(tsum);
+                    if (lane == kWave - 1) staged_total = x;
+                    pre = x - tsum;
+                }
+            } else {
+                const uint32_t x = wave_inclusive_scan<uint32_t>(tsum);
+                if (lane == kWave - 1) wsum[w] = x;
+                __syncthreads();
+                uint32_t tot = 0;
+                for (uint32_t j = 0; j < kBinThreads / kWave; ++j) {
+                    if (j < w) pre += wsum[j];
+                    tot += wsum[j];
+                }
+                pre += x - tsum;
+                if (threadIdx.x == 0) staged_total = tot;
             }
-            pre += x - tsum;
             if (owner) {
                 uint32_t* ss = seg_start + (uint64_t)s * nreg_max + rb;
                 uint32_t* sc = seg_cnt + (uint64_t)s * nreg_max + rb;
                 const uint32_t r0 = 2u * threadIdx.x, lo1 = pre + a0;
+                cc[threadIdx.x] = 0u;   // ready for the next shuffle
                 co[threadIdx.x] = pre | (lo1 << 16);
                 ss[r0] = g0 + pre;
                 sc[r0] = a0;
@@ -438,51 +452,34 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
                     sc[r0 + 1u] = a1;
                 }
             }
-            if (threadIdx.x == 0) staged_total = tot;
-        }
-        __syncthreads();
+            __syncthreads();
+            const uint32_t tot = staged_total;
 #pragma unroll
-        for (int u = 0; u < kStagePer; ++u) {
-            if (key_[u] == 0xFFFFFFFFu) continue;
-            const uint32_t lr = key_[u] >> 16;
-            stage[half16(co, lr) + (key_[u] & 0xFFFFu)] = make_uint2(st_[u], st_[u] + (len_[u] - 1u));
+            for (int u = 0; u < kGroupPer; ++u)   // now the place in the group, or ~0
+                if (key[u] != 0xFFFFFFFFu) key[u] = half16(co, key[u] >> 16) + (key[u] & 0xFFFFu);
+            uint2* out = recs + (uint64_t)s * na + g0;
+            for (uint32_t w0 = 0; w0 < tot; w0 += kStageRecs) {
+                if (w0) __syncthreads();   // the last window is written out
+#pragma unroll
+                for (int u = 0; u < kGroupPer; ++u)
+                    if (key[u] - w0 < kStageRecs) stage[key[u] - w0] = make_uint2(st_[u], st_[u] + (len[u] - 1u));
+                __syncthreads();
+                const uint32_t m = min(kStageRecs, tot - w0);
+                for (uint32_t j = threadIdx.x; j < m; j += kBinThreads) out[w0 + j] = stage[j];
+            }
         }
-        __syncthreads();
-        uint2* out = recs + (uint64_t)s * na + g0;
-        const uint32_t tot = staged_total;
-        for (uint32_t j = threadIdx.x; j < tot; j += blockDim.x) out[j] = stage[j];
         return;
     }
-    for (uint32_t p0 = g0 + threadIdx.x; p0 < g1; p0 += ILP * blockDim.x) {
-        uint2 q[ILP];
-#pragma unroll
-        for (int u = 0; u < ILP; ++u) {
-            const uint32_t p = p0 + u * blockDim.x;
-            q[u] = p < g1 ? packed[p] : make_uint2(0u, 0u);
-        }
-#pragma unroll
-        for (int u = 0; u < ILP; ++u) {
-            if (!q[u].y) continue;
-            const uint32_t st = mc_place(gs + q[u].x, k0, k1, ok, clen - q[u].y + 1u);
-            const uint32_t lr = cr[(st - ok) >> sh];
-            if (lr < nr) atomicAdd(&h[lr], 1u);
-        }
-    }
-    __syncthreads();
-    uint32_t* ss = seg_start + (uint64_t)s * nreg_max + rb;
-    uint32_t* sc = seg_cnt + (uint64_t)s * nreg_max + rb;
-    for (uint32_t j = threadIdx.x; j < nr; j += blockDim.x) sc[j] = h[j];
-    __syncthreads();
-    block_scan_u32(h, nr, wsum);
-    for (uint32_t j = threadIdx.x; j < nr; j += blockDim.x) ss[j] = g0 + h[j];
-    __syncthreads();
-    uint2* out = recs + (uint64_t)s * na;
-    if (!staged) {
-        for (uint32_t p0 = g0 + threadIdx.x; p0 < g1; p0 += ILP * blockDim.x) {
+    for (uint32_t s = s0; s < s1; ++s) {
+        const uint64_t gs = (sb + s) * na;
+        if (MANY) __syncthreads();   // the last shuffle's counters are read
+        for (uint32_t j = threadIdx.x; j < nr; j += kBinThreads) h[j] = 0u;
+        __syncthreads();
+        for (uint32_t p0 = g0 + threadIdx.x; p0 < g1; p0 += ILP * kBinThreads) {
             uint2 q[ILP];
 #pragma unroll
             for (int u = 0; u < ILP; ++u) {
-                const uint32_t p = p0 + u * blockDim.x;
+                const uint32_t p = p0 + u * kBinThreads;
                 q[u] = p < g1 ? packed[p] : make_uint2(0u, 0u);
             }
 #pragma unroll
@@ -490,86 +487,110 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
                 if (!q[u].y) continue;
                 const uint32_t st = mc_place(gs + q[u].x, k0, k1, ok, clen - q[u].y + 1u);
                 const uint32_t lr = cr[(st - ok) >> sh];
-                if (lr >= nr) continue;
-                const uint32_t at = atomicAdd(&h[lr], 1u);
-                out[g0 + at] = make_uint2(st, st + (q[u].y - 1u));
+                if (lr < nr) atomicAdd(&h[lr], 1u);
             }
         }
-        return;
-    }
-    // staged: chunks of kStageRecs table entries are placed, counting-sorted by region in
-    // LDS, and written out in region runs.  Thread t < nw2 owns regions 2t and 2t + 1
-    // (counter word t) for the whole loop.  During a chunk, hs[r] holds region r's cursor
-    // minus the offset of r's run in the chunk, so the chunk's record j goes to
-    // g0 + hs[r] + j; the next chunk's scan adds back the end of that run (kept in the
-    // owner's registers) to get the cursor again.  Four barriers a chunk: the next
-    // chunk's ranking touches only the counters, so it may overlap this write-out.
-    const uint32_t nw2 = (nr + 1) >> 1;
-    const bool owner = threadIdx.x < nw2;
-    if (owner) cc[threadIdx.x] = 0u;
-    uint32_t end0 = 0u, end1 = 0u;   // the owner's run ends in the previous chunk
-    __syncthreads();
-    for (uint32_t cb = g0; cb < g1; cb += kStageRecs) {
-        const uint32_t ce = min(g1, cb + kStageRecs);
-        uint32_t st_[kStagePer], len_[kStagePer], key_[kStagePer];   // key = lr << 16 | rank, or ~0
+        __syncthreads();
+        uint32_t* ss = seg_start + (uint64_t)s * nreg_max + rb;
+        uint32_t* sc = seg_cnt + (uint64_t)s * nreg_max + rb;
+        for (uint32_t j = threadIdx.x; j < nr; j += kBinThreads) sc[j] = h[j];
+        __syncthreads();
+        block_scan_u32(h, nr, wsum);
+        for (uint32_t j = threadIdx.x; j < nr; j += kBinThreads) ss[j] = g0 + h[j];
+        __syncthreads();
+        uint2* out = recs + (uint64_t)s * na;
+        if (!staged) {
+            for (uint32_t p0 = g0 + threadIdx.x; p0 < g1; p0 += ILP * kBinThreads) {
+                uint2 q[ILP];
 #pragma unroll
-        for (int u = 0; u < kStagePer; ++u) {
-            const uint32_t p = cb + threadIdx.x + (uint32_t)u * blockDim.x;
-            const uint2 q = p < ce ? packed[p] : make_uint2(0u, 0u);
-            key_[u] = 0xFFFFFFFFu;
-            st_[u] = 0u;
-            len_[u] = q.y;
-            if (!q.y) continue;
-            const uint32_t st = mc_place(gs + q.x, k0, k1, ok, clen - q.y + 1u);
-            const uint32_t lr = cr[(st - ok) >> sh];
-            if (lr >= nr) continue;
-            const uint32_t sft = 16u * (lr & 1u);
-            const uint32_t old = atomicAdd(&cc[lr >> 1], 1u << sft);
-            st_[u] = st;
-            key_[u] = (lr << 16) | ((old >> sft) & 0xFFFFu);
-        }
-        __syncthreads();   // counts complete; the previous chunk is written out
-        // exclusive offsets of the chunk's region counts (two per word) into co, and the
-        // owners' cursors turned into this chunk's deltas
-        {
-            const uint32_t wv = owner ? cc[threadIdx.x] : 0u;
-            if (owner) cc[threadIdx.x] = 0u;   // ready for the next chunk
-            const uint32_t a0 = wv & 0xFFFFu, a1 = wv >> 16, tsum = a0 + a1;
-            const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-            const uint32_t x = wave_inclusive_scan<uint32_t>(tsum);
-            if (lane == kWave - 1) wsum[w] = x;
-            __syncthreads();
-            uint32_t pre = 0, tot = 0;
-            for (uint32_t j = 0; j < kBinThreads / kWave; ++j) {
-                if (j < w) pre += wsum[j];
-                tot += wsum[j];
-            }
-            pre += x - tsum;
-            if (owner) {
-                const uint32_t r0 = 2u * threadIdx.x, lo1 = pre + a0;
-                co[threadIdx.x] = pre | (lo1 << 16);
-                hs[r0] = hs[r0] + end0 - pre;
-                end0 = lo1;
-                if (r0 + 1u < nr) {
-                    hs[r0 + 1u] = hs[r0 + 1u] + end1 - lo1;
-                    end1 = lo1 + a1;
+                for (int u = 0; u < ILP; ++u) {
+                    const uint32_t p = p0 + u * kBinThreads;
+                    q[u] = p < g1 ? packed[p] : make_uint2(0u, 0u);
+                }
+#pragma unroll
+                for (int u = 0; u < ILP; ++u) {
+                    if (!q[u].y) continue;
+                    const uint32_t st = mc_place(gs + q[u].x, k0, k1, ok, clen - q[u].y + 1u);
+                    const uint32_t lr = cr[(st - ok) >> sh];
+                    if (lr >= nr) continue;
+                    const uint32_t at = atomicAdd(&h[lr], 1u);
+                    out[g0 + at] = make_uint2(st, st + (q[u].y - 1u));
                 }
             }
-            if (threadIdx.x == 0) staged_total = tot;
+            continue;
         }
+        // staged: chunks of kStageRecs table entries are placed, counting-sorted by region in
+        // LDS, and written out in region runs.  Thread t < nw2 owns regions 2t and 2t + 1
+        // (counter word t) for the whole loop.  During a chunk, hs[r] holds region r's cursor
+        // minus the offset of r's run in the chunk, so the chunk's record j goes to
+        // g0 + hs[r] + j; the next chunk's scan adds back the end of that run (kept in the
+        // owner's registers) to get the cursor again.  Four barriers a chunk: the next
+        // chunk's ranking touches only the counters, so it may overlap this write-out.
+        if (owner) cc[threadIdx.x] = 0u;
+        uint32_t end0 = 0u, end1 = 0u;   // the owner's run ends in the previous chunk
         __syncthreads();
+        for (uint32_t cb = g0; cb < g1; cb += kStageRecs) {
+            const uint32_t ce = min(g1, cb + kStageRecs);
+            uint32_t st_[kStagePer], len_[kStagePer], key_[kStagePer];   // key = lr << 16 | rank, or ~0
 #pragma unroll
-        for (int u = 0; u < kStagePer; ++u) {
-            if (key_[u] == 0xFFFFFFFFu) continue;
-            const uint32_t lr = key_[u] >> 16;
-            stage[half16(co, lr) + (key_[u] & 0xFFFFu)] = make_uint2(st_[u], st_[u] + (len_[u] - 1u));
-        }
-        __syncthreads();
-        const uint32_t tot = staged_total;
-        for (uint32_t j = threadIdx.x; j < tot; j += blockDim.x) {
-            const uint2 rec = stage[j];
-            const uint32_t lr = cr[(rec.x - ok) >> sh];
-            out[g0 + hs[lr] + j] = rec;
+            for (int u = 0; u < kStagePer; ++u) {
+                const uint32_t p = cb + threadIdx.x + (uint32_t)u * kBinThreads;
+                const uint2 q = p < ce ? packed[p] : make_uint2(0u, 0u);
+                key_[u] = 0xFFFFFFFFu;
+                st_[u] = 0u;
+                len_[u] = q.y;
+                if (!q.y) continue;
+                const uint32_t st = mc_place(gs + q.x, k0, k1, ok, clen - q.y + 1u);
+                const uint32_t lr = cr[(st - ok) >> sh];
+                if (lr >= nr) continue;
+                const uint32_t sft = 16u * (lr & 1u);
+                const uint32_t old = atomicAdd(&cc[lr >> 1], 1u << sft);
+                st_[u] = st;
+                key_[u] = (lr << 16) | ((old >> sft) & 0xFFFFu);
+            }
+            __syncthreads();   // counts complete; the previous chunk is written out
+            // exclusive offsets of the chunk's region counts (two per word) into co, and the
+            // owners' cursors turned into this chunk's deltas
+            {
+                const uint32_t wv = owner ? cc[threadIdx.x] : 0u;
+                if (owner) cc[threadIdx.x] = 0u;   // ready for the next chunk
+                const uint32_t a0 = wv & 0xFFFFu, a1 = wv >> 16, tsum = a0 + a1;
+                const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+                const uint32_t x = wave_inclusive_scan<uint32_t>(tsum);
+                if (lane == kWave - 1) wsum[w] = x;
+                __syncthreads();
+                uint32_t pre = 0, tot = 0;
+                for (uint32_t j = 0; j < kBinThreads / kWave; ++j) {
+                    if (j < w) pre += wsum[j];
+                    tot += wsum[j];
+                }
+                pre += x - tsum;
+                if (owner) {
+                    const uint32_t r0 = 2u * threadIdx.x, lo1 = pre + a0;
+                    co[threadIdx.x] = pre | (lo1 << 16);
+                    hs[r0] = hs[r0] + end0 - pre;
+                    end0 = lo1;
+                    if (r0 + 1u < nr) {
+                        hs[r0 + 1u] = hs[r0 + 1u] + end1 - lo1;
+                        end1 = lo1 + a1;
+                    }
+                }
+                if (threadIdx.x == 0) staged_total = tot;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kStagePer; ++u) {
+                if (key_[u] == 0xFFFFFFFFu) continue;
+                const uint32_t lr = key_[u] >> 16;
+                stage[half16(co, lr) + (key_[u] & 0xFFFFu)] = make_uint2(st_[u], st_[u] + (len_[u] - 1u));
+            }
+            __syncthreads();
+            const uint32_t tot = staged_total;
+            for (uint32_t j = threadIdx.x; j < tot; j += kBinThreads) {
+                const uint2 rec = stage[j];
+                const uint32_t lr = cr[(rec.x - ok) >> sh];
+                out[g0 + hs[lr] + j] = rec;
+            }
         }
     }
 }
@@ -898,9 +919,17 @@ hipError_t launch_bin_batch(const uint32_t* chrom_len, uint32_t n_chrom, const M
     if (nb == 0 || nb > BITS_MC_BIN_MAX_BATCH) return hipErrorInvalidValue;
     hipError_t e;
     if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-    const auto place = na < g.cb[n_chrom] / 2 ? k_bin_place<true> : k_bin_place<false>;
-    hipLaunchKernelGGL(place, dim3(n_chrom * nb), dim3(kBinThreads), 0, s, g,
-                       reinterpret_cast<const uint2*>(w.packed), tab.hist, tab.cursor, na, seed, sb, nb,
+    // Shuffles per workgroup: groups of more than kGroupRecs entries take long enough
+    // by themselves; of the others, as many as leave `rounds` workgroups for each of the
+    // two slots a CU has, one when a shuffle's work is mostly latency, up to 6 so that
+    // the last round costs little (1e5 entries x 2000: 3, 6, 10 rounds 671, 648, 658 us).
+    const uint64_t groups = (uint64_t)n_chrom * nb, mean = na / n_chrom;
+    const uint64_t rounds = std::min<uint64_t>(std::max<uint64_t>(mean / 512, 1), 6);
+    const uint64_t slots = 2u * rounds * (uint64_t)device_cu_count();
+    const uint32_t per = mean > kGroupRecs ? 1u : (uint32_t)std::min<uint64_t>((groups + slots - 1) / slots, nb);
+    const auto place = per == 1 ? k_bin_place<false> : k_bin_place<true>;
+    hipLaunchKernelGGL(place, dim3(n_chrom * ((nb + per - 1) / per)), dim3(kBinThreads), 0, s, g,
+                       reinterpret_cast<const uint2*>(w.packed), tab.hist, tab.cursor, na, seed, sb, nb, per,
                        w.cell_region, w.nreg, w.nreg_max, w.seg_start, w.seg_cnt, reinterpret_cast<uint2*>(w.recs));
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
     if (w.splits > 1)

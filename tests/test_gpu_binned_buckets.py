@@ -82,3 +82,19 @@ def test_top_of_the_coordinate_range():
     b_s, b_e = intervals(rng, size - 90_000, size, 30_000, 3000)
     a_s, a_e = intervals(rng, size - 70_000, size, 5000, 4000)
     check(lengths, a_s, a_e, b_s, b_e, 6, 6)
+
+
+@pytest.mark.parametrize("na", [1, 1023, 5632, 5633, 8191, 8192, 8193, 11_265, 20_000])
+@pytest.mark.parametrize("n_b", [3_000, 1_300_000])
+def test_groups_of_several_shuffles(na, n_b):
+    """One chromosome holds nearly all entries and 23 few or none, so that workgroups take several
+    shuffles of a group held in registers (at most 8192 entries) and of one placed chunk by chunk (many
+    regions) or entry by entry (few)."""
+    rng = np.random.default_rng(na + n_b)
+    lengths = [9_000_000] + [40_000] * 22 + [0]
+    b_s, b_e = intervals(rng, 0, 9_000_000 + 22 * 40_000, n_b, 40)
+    a_s, a_e = intervals(rng, 0, 9_000_000, na, 3000)
+    b = [intervals(rng, 9_000_000 + 40_000 * k, 9_040_000 + 40_000 * k, k % 3, 100) for k in range(22)]
+    a_s = np.concatenate([a_s] + [x[0] for x in b])
+    a_e = np.concatenate([a_e] + [x[1] for x in b])
+    check(lengths, a_s, a_e, b_s, b_e, 131, 128)

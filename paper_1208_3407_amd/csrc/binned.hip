@@ -319,18 +319,16 @@ __device__ __forceinline__ T wave_inclusive_scan(T x) {
 }
 
 // Staged binning (second sweep): chromosomes with kStageMinRegions..kStageRegions
-// regions; kStageRecs records per chunk, so that the workgroup's LDS (about 76 KB)
-// still lets two workgroups share a CU.
+// regions; kStageRecs records staged at a time, so that the workgroup's LDS (about
+// 76 KB) still lets two workgroups share a CU.
 constexpr uint32_t kStageRegions = 2048;
 constexpr uint32_t kStageMinRegions = 128;
 constexpr uint32_t kStageRecs = 5632;      // 44 KB
-constexpr int kStagePer = (kStageRecs + kBinThreads - 1) / kBinThreads;
 // A group of at most kGroupRecs entries is placed once and held in registers.
 constexpr int kGroupPer = 8;
 constexpr uint32_t kGroupRecs = kGroupPer * kBinThreads;
 static_assert(kGroupRecs < (1u << 16), "places in a group are 16-bit");
 static_assert(kStageRegions <= 2 * kBinThreads, "one thread owns two regions' chunk counters");
-static_assert(kStageRecs < (1u << 16), "chunk counts and offsets are 16-bit");
 static_assert(kMaxCells <= (1u << 16), "cell-to-region table entries are 16-bit");
 
 // Entry j of an array of 16-bit values packed two per word.
@@ -347,18 +345,22 @@ __device__ __forceinline__ uint32_t half16(const uint32_t* w, uint32_t j) {
 // one is placed twice, to count and to write, either one by one (few regions,
 // or more than kStageRegions) or chunk by chunk through LDS.
 // (8 waves per SIMD: two workgroups per CU, at most 64 VGPRs.)
-// Vector instructions, the Philox rounds above all, bound large groups (1e9
-// placements 5240 us, 1600 of them the counting sweep).  A workgroup of 4000
-// entries spends half its time on its start, the region table and the chain
-// of loads and barriers before its first store, so it takes several shuffles
-// (1e5 entries in 24 chromosomes x 2000 shuffles: 800 -> 648 us; 2000 x 100:
-// 21.3 -> 18.9 us).
+// The scattered write-out bounds large groups: with 3 Philox rounds for 10 the
+// 4920 us of 1e9 placements become 4560, and without the counting sweep, every
+// region having slots for five standard deviations more than its mean, 5600.
+// A workgroup of 4000 entries spends half its time on its start, the region
+// table and the chain of loads and barriers before its first store, so it takes
+// several shuffles (1e5 entries in 24 chromosomes x 2000 shuffles: 800 -> 648 us;
+// 2000 x 100: 21.3 -> 18.9 us).
 template <bool MANY>
 __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     BinGeom g, const uint2* __restrict__ packed, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ cursor,
     uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, uint32_t per, const uint32_t* __restrict__ cell_region,
     const uint64_t* __restrict__ nreg_p, uint32_t nreg_max, uint32_t* __restrict__ seg_start,
     uint32_t* __restrict__ seg_cnt, uint2* __restrict__ recs) {
+    constexpr int kChunkPer = MANY ? 6 : 10;   // a chunk's entries per thread
+    constexpr uint32_t kChunkRecs = kChunkPer * kBinThreads;
+    static_assert(kChunkRecs < (1u << 16), "chunk counts and offsets are 16-bit");
     __shared__ uint16_t cr[kMaxCells];
     __shared__ uint32_t hs[kStageRegions];          // segment cursors (staged path)
     __shared__ uint32_t cc[kStageRegions / 2];      // chunk counts, 16 bits each
@@ -519,21 +521,23 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
             }
             continue;
         }
-        // staged: chunks of kStageRecs table entries are placed, counting-sorted by region in
-        // LDS, and written out in region runs.  Thread t < nw2 owns regions 2t and 2t + 1
+        // staged: chunks of kChunkRecs table entries are placed into registers, counting-sorted
+        // by region in LDS, in windows of kStageRecs, and written out in region runs.  The runs
+        // are the longer the larger the chunk (1e9 placements, 82 a region and shuffle: 6, 8,
+        // 10, 11 entries a thread 5240, 5030, 4920, 4940 us; 14 spill: 6100).  Thread t < nw2 owns regions 2t and 2t + 1
         // (counter word t) for the whole loop.  During a chunk, hs[r] holds region r's cursor
         // minus the offset of r's run in the chunk, so the chunk's record j goes to
         // g0 + hs[r] + j; the next chunk's scan adds back the end of that run (kept in the
-        // owner's registers) to get the cursor again.  Four barriers a chunk: the next
-        // chunk's ranking touches only the counters, so it may overlap this write-out.
+        // owner's registers) to get the cursor again.  The next chunk's ranking touches only
+        // the counters, so it may overlap the last write-out.
         if (owner) cc[threadIdx.x] = 0u;
         uint32_t end0 = 0u, end1 = 0u;   // the owner's run ends in the previous chunk
         __syncthreads();
-        for (uint32_t cb = g0; cb < g1; cb += kStageRecs) {
-            const uint32_t ce = min(g1, cb + kStageRecs);
-            uint32_t st_[kStagePer], len_[kStagePer], key_[kStagePer];   // key = lr << 16 | rank, or ~0
+        for (uint32_t cb = g0; cb < g1; cb += kChunkRecs) {
+            const uint32_t ce = min(g1, cb + kChunkRecs);
+            uint32_t st_[kChunkPer], len_[kChunkPer], key_[kChunkPer];   // key = lr << 16 | rank, or ~0
 #pragma unroll
-            for (int u = 0; u < kStagePer; ++u) {
+            for (int u = 0; u < kChunkPer; ++u) {
                 const uint32_t p = cb + threadIdx.x + (uint32_t)u * kBinThreads;
                 const uint2 q = p < ce ? packed[p] : make_uint2(0u, 0u);
                 key_[u] = 0xFFFFFFFFu;
@@ -578,18 +582,22 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
                 if (threadIdx.x == 0) staged_total = tot;
             }
             __syncthreads();
-#pragma unroll
-            for (int u = 0; u < kStagePer; ++u) {
-                if (key_[u] == 0xFFFFFFFFu) continue;
-                const uint32_t lr = key_[u] >> 16;
-                stage[half16(co, lr) + (key_[u] & 0xFFFFu)] = make_uint2(st_[u], st_[u] + (len_[u] - 1u));
-            }
-            __syncthreads();
             const uint32_t tot = staged_total;
-            for (uint32_t j = threadIdx.x; j < tot; j += kBinThreads) {
-                const uint2 rec = stage[j];
-                const uint32_t lr = cr[(rec.x - ok) >> sh];
-                out[g0 + hs[lr] + j] = rec;
+#pragma unroll
+            for (int u = 0; u < kChunkPer; ++u)   // now the place in the chunk, or ~0
+                if (key_[u] != 0xFFFFFFFFu) key_[u] = half16(co, key_[u] >> 16) + (key_[u] & 0xFFFFu);
+            for (uint32_t w0 = 0; w0 < tot; w0 += kStageRecs) {
+                if (w0) __syncthreads();   // the last window is written out
+#pragma unroll
+                for (int u = 0; u < kChunkPer; ++u)
+                    if (key_[u] - w0 < kStageRecs) stage[key_[u] - w0] = make_uint2(st_[u], st_[u] + (len_[u] - 1u));
+                __syncthreads();
+                const uint32_t m = min(kStageRecs, tot - w0);
+                for (uint32_t j = threadIdx.x; j < m; j += kBinThreads) {
+                    const uint2 rec = stage[j];
+                    const uint32_t lr = cr[(rec.x - ok) >> sh];
+                    out[g0 + hs[lr] + w0 + j] = rec;
+                }
             }
         }
     }

@@ -98,3 +98,13 @@ def test_groups_of_several_shuffles(na, n_b):
     a_s = np.concatenate([a_s] + [x[0] for x in b])
     a_e = np.concatenate([a_e] + [x[1] for x in b])
     check(lengths, a_s, a_e, b_s, b_e, 131, 128)
+
+
+@pytest.mark.parametrize("na", [9_216, 10_240, 10_241, 15_872, 20_480, 20_481, 31_000])
+def test_chunks_of_large_groups(na):
+    """A single chromosome of more than 128 regions: chunks of 10240 entries, each staged in two windows
+    of 5632, around whole chunks and windows."""
+    rng = np.random.default_rng(na)
+    b_s, b_e = intervals(rng, 0, 9_000_000, 700_000, 40)
+    a_s, a_e = intervals(rng, 0, 9_000_000, na, 3000)
+    check([9_000_000], a_s, a_e, b_s, b_e, 5, 3)

@@ -76,7 +76,9 @@ typedef enum bits_status {
                                      no model (the index the learned path is measured against) */
 
 /* Launch shape of the search kernels.  A NULL bits_launch* means the
- * library defaults; bits_autotune_count picks one by timing. */
+ * library defaults, and so do block and qpl both 0 with path AUTO, LEARNED or
+ * TIERED: counting, decisions and Monte-Carlo then choose both by the path and
+ * the number of searches.  bits_autotune_count picks one by timing. */
 typedef struct bits_launch {
     uint32_t block;   /* threads per workgroup: 256, 512 or 1024 (0 = default 1024); the learned
                          path uses a smaller one when its LDS scratch would not fit */

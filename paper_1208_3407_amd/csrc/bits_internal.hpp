@@ -84,7 +84,7 @@ struct SearchArgs {
     const uint32_t* be;          // sorted ends
     const uint32_t* tree;        // [2][tree_stride] Eytzinger splitters
     const bits_rmi_model* rmi;   // [2] learned models or nullptr
-    const uint32_t* hs;          // line heads of B_S (learned only): hs[j] = bs[32 j], 0xFFFFFFFF past the end
+    const uint32_t* hs;          // line heads of B_S: hs[j] = bs[32 j], 0xFFFFFFFF past the end
     const uint32_t* he;          // line heads of B_E
     uint32_t* status;            // device status word
     unsigned long long* fallbacks;

@@ -66,7 +66,8 @@ typedef enum bits_status {
 #define BITS_RMI_MAX_POINTS 2048u /* training points per leaf */
 
 /* Search path selection for a call (bits_launch.path). */
-#define BITS_PATH_AUTO    0u      /* learned index if the reference has one, else the tiered search
+#define BITS_PATH_AUTO    0u      /* learned index if the reference has one, else the tiered search,
+                                     or the plain one up to 2^14 intervals
                                      (the batch plan: all references learned, else as bits_batch_create says) */
 #define BITS_PATH_PLAIN   1u      /* LDS Eytzinger top tree + bisection in HBM */
 #define BITS_PATH_LEARNED 2u      /* learned CDF index + error-window search over the line heads (needs learned ref) */

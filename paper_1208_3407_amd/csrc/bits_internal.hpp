@@ -127,7 +127,14 @@ __host__ __device__ constexpr size_t search_lds_bytes(bool learned, uint32_t dep
 // small reference (1e6 queries against 3e5: 63 against 71 us through the line
 // heads), but misses as buckets grow (against 1e6: 88 and 86 us, against 2e6:
 // 335 and 144 us).
-enum : int { kModePlain = 0, kModeLearned = 1, kModeTiered = 2, kModeDirect = 3 };
+// AUTO takes the plain path up to kPlainKeys: the LDS tree then resolves all but
+// a step or two (1.5e7 queries against 1e3 keys 81 us, 206 with windows; 8e3
+// 155, 223; 1.6e4 205, 236; 6.4e4 455, 271).  Counting through the models takes
+// kModePaired up to kPairedKeys keys, kModeLearned above.
+enum : int { kModePlain = 0, kModeLearned = 1, kModeTiered = 2, kModeDirect = 3, kModePaired = 4 };
+__host__ __device__ constexpr bool learned_mode(int mode) { return mode == kModeLearned || mode == kModePaired; }
+constexpr uint32_t kPlainKeys = 1u << 14;
+constexpr uint32_t kPairedKeys = 1u << 16;
 constexpr uint32_t kDirectKeys = 1u << 19;
 // Above this the tiered search looks for a query's second rank next to its first.
 constexpr uint32_t kNearKeys = 1u << 24;

@@ -989,6 +989,28 @@ __device__ __forceinline__ void icount_learned(const SearchArgs& sa, uint32_t* s
         });
 }
 
+// The same with both searches of a query in step, for references up to
+// kPairedKeys keys: their lines are in L2, where a second wait costs more than
+// the requests it saves (1.5e7 queries against 2e3 keys 350 us, 510 near; 2e4
+// 455, 560; 1e5 737, 689).
+template <int QPL>
+__device__ __forceinline__ void icount_paired(const SearchArgs& sa, uint32_t* scr, const uint32_t (&as)[QPL],
+                                              const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL], uint32_t (&fst)[QPL]) {
+    uint32_t x[2 * QPL], r[2 * QPL];
+    float dens[2 * QPL];
+#pragma unroll
+    for (int q = 0; q < QPL; ++q) {
+        x[2 * q] = ae[q] + 1u;
+        x[2 * q + 1] = as[q];
+    }
+    rank_learned<2 * QPL>(both_arrays(sa), sa.fallbacks, scr, x, r, dens);
+#pragma unroll
+    for (int q = 0; q < QPL; ++q) {
+        fst[q] = (ae[q] == 0xFFFFFFFFu) ? sa.n : r[2 * q];
+        cnt[q] = fst[q] - r[2 * q + 1];
+    }
+}
+
 // One query at a time: the windows of more would not fit the registers.  Up to
 // kNearKeys keys both searches of a query run in step, which hides their waits
 // in each other's; above, the second search starts from the first one's rank.
@@ -1031,6 +1053,8 @@ __device__ __forceinline__ void icount(const SearchArgs& sa, uint32_t* lds, cons
                                        const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL], uint32_t (&fst)[QPL]) {
     if constexpr (MODE == kModeLearned)
         icount_learned<QPL>(sa, lds + (threadIdx.x / kWave) * probe_scratch_words(QPL), as, ae, cnt, fst);
+    else if constexpr (MODE == kModePaired)
+        icount_paired<QPL>(sa, lds + (threadIdx.x / kWave) * probe_scratch_words(QPL), as, ae, cnt, fst);
     else if constexpr (MODE == kModePlain)
         icount_plain<QPL>(sa, lds, as, ae, cnt, fst);
     else
@@ -1058,8 +1082,8 @@ __device__ __forceinline__ void add_block_sum(uint64_t v, unsigned long long* ou
 // loaded by lane (i mod blockDim), so every load of a query round is
 // coalesced.  Totals: uint64 sums, one atomic per workgroup.
 
-// MODE: kModePlain (LDS tree + bisection), kModeLearned (learned index,
-// error-window head probe + one line), kModeTiered (LDS tree + line-head
+// MODE: kModePlain (LDS tree + bisection), kModeLearned and kModePaired (learned
+// index, error-window head probe + one line), kModeTiered (LDS tree + line-head
 // window + one line) or kModeDirect (LDS tree + one window of keys).
 template <int QPL, int MODE>
 BITS_SEARCH_KERNEL k_count(SearchArgs sa, const uint32_t* __restrict__ a_start,
@@ -1067,7 +1091,7 @@ BITS_SEARCH_KERNEL k_count(SearchArgs sa, const uint32_t* __restrict__ a_start,
                                                 uint32_t* __restrict__ counts, uint32_t* __restrict__ firsts,
                                                 unsigned long long* total) {
     extern __shared__ __align__(16) uint32_t lds[];
-    if (MODE != kModeLearned) {
+    if (!learned_mode(MODE)) {
         stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
         __syncthreads();
     }
@@ -1117,7 +1141,7 @@ BITS_SEARCH_KERNEL k_decide(SearchArgs sa, const uint32_t* __restrict__ a_start,
                             uint64_t na, uint32_t* found, unsigned long long* witness) {
     extern __shared__ __align__(16) uint32_t lds[];
     __shared__ uint32_t stop;
-    if (MODE != kModeLearned) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
+    if (!learned_mode(MODE)) stage_tree(lds, sa.tree, sa.tree_stride, sa.depth);
     __syncthreads();
     if (MODE == kModeLearned || MODE == kModeTiered) sa.mean_len = mean_length(sa);
     const uint64_t tile = (uint64_t)blockDim.x * QPL;
@@ -2014,8 +2038,8 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s) {
 }
 
 // The kernel mode of a launch's path (the tiered path has one form per size).
-static int search_mode(const SearchArgs& sa, const LaunchCfg& cfg) {
-    if (cfg.path == BITS_PATH_LEARNED) return kModeLearned;
+static int search_mode(const SearchArgs& sa, const LaunchCfg& cfg, bool counting = false) {
+    if (cfg.path == BITS_PATH_LEARNED) return counting && sa.n <= kPairedKeys ? kModePaired : kModeLearned;
     if (cfg.path == BITS_PATH_TIERED) return sa.n <= kDirectKeys ? kModeDirect : kModeTiered;
     return kModePlain;
 }
@@ -2024,7 +2048,7 @@ template <int QPL, int MODE>
 static hipError_t launch_count_t(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                                  uint64_t na, uint32_t* counts, uint32_t* firsts, unsigned long long* total,
                                  hipStream_t s) {
-    const size_t lds = search_lds_bytes(MODE == kModeLearned, sa.depth, QPL, cfg.block);
+    const size_t lds = search_lds_bytes(learned_mode(MODE), sa.depth, QPL, cfg.block);
     const uint64_t tile = (uint64_t)cfg.block * QPL;
     const void* kern = (const void*)k_count<QPL, MODE>;
     const uint32_t grid = persistent_grid(kern, cfg, lds, (na + tile - 1) / tile);
@@ -2037,9 +2061,11 @@ template <int QPL>
 static hipError_t launch_count_q(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                                  uint64_t na, uint32_t* counts, uint32_t* firsts, unsigned long long* total,
                                  hipStream_t s) {
-    switch (search_mode(sa, cfg)) {
+    switch (search_mode(sa, cfg, true)) {
         case kModeLearned:
             return launch_count_t<QPL, kModeLearned>(sa, cfg, as, ae, na, counts, firsts, total, s);
+        case kModePaired:
+            return launch_count_t<QPL, kModePaired>(sa, cfg, as, ae, na, counts, firsts, total, s);
         case kModeTiered:
             return launch_count_t<QPL, kModeTiered>(sa, cfg, as, ae, na, counts, firsts, total, s);
         case kModeDirect:
@@ -2056,12 +2082,14 @@ static hipError_t launch_count_q(const SearchArgs& sa, const LaunchCfg& cfg, con
 // shuffles of a large set (1024 threads lowered to what the LDS scratch of two
 // queries per lane allows, before: counting 1e4 queries in 1e4 23.6 -> 14.3 us,
 // 1e5 in 5e6 34.0 -> 17.5, 5e7 in 5e7 3180 -> 3050; 1e5 x 100 shuffles in 1e6
-// one query 392, two 382, before 478 us; 1e4 x 100 in 1e5 200, 215, 258).
-static LaunchCfg open_shape(const LaunchCfg& cfg, uint64_t na, bool shuffles = false) {
+// one query 392, two 382, before 478 us; 1e4 x 100 in 1e5 200, 215, 258), and
+// in large counts against small references, whose two searches go in step
+// (1.5e7 in 2e4 455 and 439 us).
+static LaunchCfg open_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na, bool shuffles = false) {
     LaunchCfg c = cfg;
     if (!c.open) return c;
     if (c.path == BITS_PATH_LEARNED) {
-        c.qpl = shuffles && na >= (1u << 22) ? 2u : 1u;
+        c.qpl = (shuffles ? na >= (1u << 22) : n <= kPairedKeys && na >= (1u << 20)) ? 2u : 1u;
         c.block = 256u;
     }
     if (c.path != BITS_PATH_TIERED) return c;
@@ -2074,7 +2102,7 @@ static LaunchCfg open_shape(const LaunchCfg& cfg, uint64_t na, bool shuffles = f
 hipError_t launch_count(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t* as, const uint32_t* ae,
                         uint64_t na, uint32_t* counts, unsigned long long* total, hipStream_t s, uint32_t* firsts) {
     if (!na) return hipSuccess;
-    const LaunchCfg cfg = open_shape(cfg0, na);
+    const LaunchCfg cfg = open_shape(cfg0, sa.n, na);
     switch (cfg.qpl) {
         case 1: return launch_count_q<1>(sa, cfg, as, ae, na, counts, firsts, total, s);
         case 4: return launch_count_q<4>(sa, cfg, as, ae, na, counts, firsts, total, s);
@@ -2174,7 +2202,7 @@ hipError_t launch_mc(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t
                      const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
                      unsigned long long* totals, unsigned long long* observed, hipStream_t s) {
     if (!na) return hipSuccess;
-    const LaunchCfg cfg = open_shape(cfg0, na * (nshuf ? nshuf : 1), nshuf != 0);
+    const LaunchCfg cfg = open_shape(cfg0, sa.n, na * (nshuf ? nshuf : 1), nshuf != 0);
     switch (cfg.qpl) {
         case 1: return launch_mc_q<1>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
         case 4: return launch_mc_q<4>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
@@ -2185,7 +2213,7 @@ hipError_t launch_mc(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t
 template <int QPL, int MODE>
 static hipError_t launch_decide_t(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                                   uint64_t na, uint32_t* found, unsigned long long* witness, hipStream_t s) {
-    const size_t lds = search_lds_bytes(MODE == kModeLearned, sa.depth, QPL, cfg.block);
+    const size_t lds = search_lds_bytes(learned_mode(MODE), sa.depth, QPL, cfg.block);
     const uint64_t tile = (uint64_t)cfg.block * QPL;
     const void* kern = (const void*)k_decide<QPL, MODE>;
     const uint32_t grid = persistent_grid(kern, cfg, lds, (na + tile - 1) / tile);
@@ -2196,8 +2224,9 @@ static hipError_t launch_decide_t(const SearchArgs& sa, const LaunchCfg& cfg, co
 template <int QPL>
 static hipError_t launch_decide_q(const SearchArgs& sa, const LaunchCfg& cfg, const uint32_t* as, const uint32_t* ae,
                                   uint64_t na, uint32_t* found, unsigned long long* witness, hipStream_t s) {
-    switch (search_mode(sa, cfg)) {
+    switch (search_mode(sa, cfg, true)) {
         case kModeLearned: return launch_decide_t<QPL, kModeLearned>(sa, cfg, as, ae, na, found, witness, s);
+        case kModePaired: return launch_decide_t<QPL, kModePaired>(sa, cfg, as, ae, na, found, witness, s);
         case kModeTiered: return launch_decide_t<QPL, kModeTiered>(sa, cfg, as, ae, na, found, witness, s);
         case kModeDirect: return launch_decide_t<QPL, kModeDirect>(sa, cfg, as, ae, na, found, witness, s);
         default: return launch_decide_t<QPL, kModePlain>(sa, cfg, as, ae, na, found, witness, s);
@@ -2207,7 +2236,7 @@ static hipError_t launch_decide_q(const SearchArgs& sa, const LaunchCfg& cfg, co
 hipError_t launch_decide(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t* as, const uint32_t* ae,
                          uint64_t na, uint32_t* found, unsigned long long* witness, hipStream_t s) {
     if (!na) return hipSuccess;
-    const LaunchCfg cfg = open_shape(cfg0, na);
+    const LaunchCfg cfg = open_shape(cfg0, sa.n, na);
     switch (cfg.qpl) {
         case 1: return launch_decide_q<1>(sa, cfg, as, ae, na, found, witness, s);
         case 4: return launch_decide_q<4>(sa, cfg, as, ae, na, found, witness, s);

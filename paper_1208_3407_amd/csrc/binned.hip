@@ -56,6 +56,11 @@ constexpr uint32_t kFirstKeys = 2, kBucketKeys = 5;
 // a CU x 512 B x 256 CUs in about 2 us is what the search then read per second.
 // 1e9 records, all passes: 1, 2, 3, 4, 6 loads 3860, 3470, 3360, 3310, 3280 us.
 constexpr uint32_t kAhead = 4;
+// Records per shuffle of a region from which a wave walks the shuffles with
+// scalars, each end costing it an LDS read's wait; with fewer, every lane looks
+// for itself (1000 queries x 2200 against 2.3e6, two a region and shuffle: 453
+// and 264 us; at 82 both take 3.31 ms for 1e9).
+constexpr uint32_t kWalkRecords = 64;
 static_assert(kSliceWords < (1u << 16), "slice ranks are 16-bit");
 constexpr uint32_t kBinThreads = 1024;
 constexpr int ILP = 4;   // table entries each binning thread loads before it places them
@@ -664,6 +669,24 @@ __device__ __forceinline__ uint32_t rank_buckets(const uint32_t* K, const Bucket
     return lo + c;
 }
 
+// Wave-level segmented sum: lanes carry (key, value) with the keys of the
+// valid lanes non-decreasing in lane order; each run of equal keys adds its
+// sum to acc[key] with at most two LDS atomics (the run's inclusive prefix at
+// its last lane, minus the prefix before its first lane, which is that lane's
+// inclusive prefix minus its own value).  T = uint32_t only when 64 values
+// cannot reach 2^32.
+template <typename T>
+__device__ __forceinline__ void wave_segment_add(uint32_t key, T v, bool valid, unsigned long long* acc) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const T x = wave_inclusive_scan<T>(v);
+    // the neighbours' keys by whole-wave DPP shifts (wave_shr:1, wave_shl:1); lane 0's kp and
+    // lane 63's kn are never used
+    const uint32_t kp = dpp_in0<0x138, 0xF>(key), kn = dpp_in0<0x130, 0xF>(key);
+    if (!valid) return;
+    if (lane == kWave - 1 || kn != key) atomicAdd(&acc[key], (unsigned long long)x);
+    if (lane != 0 && kp != key) atomicAdd(&acc[key], 0ull - (unsigned long long)(x - v));
+}
+
 // The placements of one region, counted against slices S = B_S[s_lo, s_lo + ns)
 // and E = B_E[e_lo, e_lo + ne) (in LDS, or in HBM for an oversize region):
 // the workgroup's share [q0, q1) of the region's records.  Each wave takes a
@@ -677,7 +700,9 @@ __device__ __forceinline__ uint32_t rank_buckets(const uint32_t* K, const Bucket
 // bisected, shuffles tracked by each lane, a segmented sum with two LDS atomics
 // a run and one load ahead took 124 (1e9 records against 5e7 keys: 3700 -> 3310
 // us; 2e8 against 1e6: 775 -> 684 us).
-template <bool LDS, typename T>
+// LANES, for few records a shuffle (many shuffles end in a step): every lane
+// finds its own record's shuffle, moving forward, and a segmented sum adds up.
+template <bool LDS, bool LANES, typename T>
 __device__ __forceinline__ void bin_count_region(const uint32_t* S, uint32_t ns, const uint32_t* E, uint32_t ne,
                                                  const uint32_t* __restrict__ bs, uint32_t n, uint32_t s_lo,
                                                  uint32_t e_lo, const Buckets& bks, const Buckets& bke,
@@ -698,9 +723,15 @@ __device__ __forceinline__ void bin_count_region(const uint32_t* S, uint32_t ns,
     uint32_t end_c = uniform(pre[sc + 1]);   // the end of the counted step's shuffle
     // the shuffle of the records being loaded, a step ahead, so that a wave has
     // two record loads in flight
-    uint32_t sn = sc, end_n = end_c, base_n = uniform(base[sc]);
-    auto load = [&](uint64_t b) {   // records [b, min(b + 64, p1)), b < p1
+    uint32_t sn = sc, end_n = end_c, base_n = uniform(base[sc]), lane_s = sc;
+    auto load = [&](uint64_t b, uint32_t& of) {   // records [b, min(b + 64, p1)), b < p1
         const uint32_t e = (uint32_t)min(p1, b + kWave), p = (uint32_t)b + lane;
+        if (LANES) {
+            if (lane >= e - (uint32_t)b) return make_uint2(bke.lo, bke.lo);
+            while (pre[lane_s + 1] <= p) ++lane_s;   // ends at lane_s < nb: p < pre[nb]
+            of = lane_s;
+            return recs[base[lane_s] + p];
+        }
         uint32_t at = base_n + p;
         while (end_n < e) {   // ends at sn < nb: e <= pre[nb]
             const uint32_t from = end_n;
@@ -712,7 +743,7 @@ __device__ __forceinline__ void bin_count_region(const uint32_t* S, uint32_t ns,
         return lane < e - (uint32_t)b ? recs[at] : make_uint2(bke.lo, bke.lo);
     };
     unsigned long long run = 0ull;   // of shuffle sc, in the steps so far
-    auto count = [&](uint64_t b, uint2 r) {   // the step of records [b, min(b + 64, p1))
+    auto count = [&](uint64_t b, uint2 r, uint32_t of) {   // the step of records [b, min(b + 64, p1))
         uint32_t first, last;
         if (LDS && r.y < key_top) {   // every key <= r.y is inside the slice
             first = s_lo + rank_buckets<false>(S, bks, r.y);
@@ -727,6 +758,11 @@ __device__ __forceinline__ void bin_count_region(const uint32_t* S, uint32_t ns,
         else
             last = e_lo + rank_in<true>(E, ne, r.x);
         const uint32_t e = (uint32_t)min(p1, b + kWave), got = e - (uint32_t)b;
+        if (LANES) {
+            const bool valid = lane < got;
+            wave_segment_add<T>(valid ? of : 0xFFFFFFFFu, valid ? (T)(first - last) : (T)0, valid, acc);
+            return;
+        }
         const T x = wave_inclusive_scan<T>(lane < got ? (T)(first - last) : (T)0);
         T before = 0;
         while (end_c <= e) {   // end_c > b: shuffle sc ends in this step
@@ -741,17 +777,19 @@ __device__ __forceinline__ void bin_count_region(const uint32_t* S, uint32_t ns,
         run += (T)(lane_value(x, kWave - 1) - before);
     };
     uint2 rn[kAhead];
+    uint32_t of[kAhead];   // the lanes' shuffles
 #pragma unroll
     for (uint32_t u = 0; u < kAhead; ++u)
-        if (p0 + u * kWave < p1) rn[u] = load(p0 + u * kWave);
+        if (p0 + u * kWave < p1) rn[u] = load(p0 + u * kWave, of[u]);
     for (uint64_t b0 = p0; b0 < p1; b0 += kAhead * kWave) {
 #pragma unroll
         for (uint32_t u = 0; u < kAhead; ++u) {
             const uint64_t b = b0 + u * kWave;
             if (b >= p1) break;
             const uint2 r = rn[u];
-            if (b + kAhead * kWave < p1) rn[u] = load(b + kAhead * kWave);
-            count(b, r);
+            const uint32_t s = LANES ? of[u] : 0u;
+            if (b + kAhead * kWave < p1) rn[u] = load(b + kAhead * kWave, of[u]);
+            count(b, r, s);
         }
     }
     if (lane == 0 && run) atomicAdd(&acc[sc], run);   // run = 0 once sc = nb
@@ -835,18 +873,25 @@ __global__ void __launch_bounds__(kBinThreads) k_bin_search(
     const uint64_t q0 = SPLIT ? total * part / splits : 0ull, q1 = SPLIT ? total * (part + 1) / splits : total;
     // per-step sums fit 32 bits when 64 counts of at most n cannot reach 2^32
     const bool narrow = n < (1u << 26);
-    if (in_lds && narrow)
-        bin_count_region<true, uint32_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
-                                         recs, pre, base, nb, q0, q1, acc);
+    const bool lanes = total < (uint64_t)kWalkRecords * nb;
+    if (in_lds && lanes && narrow)
+        bin_count_region<true, true, uint32_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                               recs, pre, base, nb, q0, q1, acc);
+    else if (in_lds && lanes)
+        bin_count_region<true, true, uint64_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                               recs, pre, base, nb, q0, q1, acc);
+    else if (in_lds && narrow)
+        bin_count_region<true, false, uint32_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                               recs, pre, base, nb, q0, q1, acc);
     else if (in_lds)
-        bin_count_region<true, uint64_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
-                                         recs, pre, base, nb, q0, q1, acc);
+        bin_count_region<true, false, uint64_t>(slice, ns, slice + eo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                               recs, pre, base, nb, q0, q1, acc);
     else if (narrow)
-        bin_count_region<false, uint32_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
-                                          recs, pre, base, nb, q0, q1, acc);
+        bin_count_region<false, false, uint32_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                                 recs, pre, base, nb, q0, q1, acc);
     else
-        bin_count_region<false, uint64_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
-                                          recs, pre, base, nb, q0, q1, acc);
+        bin_count_region<false, false, uint64_t>(bs + s_lo, ns, be + e_lo, ne, bs, n, s_lo, e_lo, bks, bke, key_top,
+                                                 recs, pre, base, nb, q0, q1, acc);
     __syncthreads();
     if (threadIdx.x < nb)
         partial[(SPLIT ? (uint64_t)r * splits + part : (uint64_t)r) * nb + threadIdx.x] = acc[threadIdx.x];

@@ -108,3 +108,13 @@ def test_chunks_of_large_groups(na):
     b_s, b_e = intervals(rng, 0, 9_000_000, 700_000, 40)
     a_s, a_e = intervals(rng, 0, 9_000_000, na, 3000)
     check([9_000_000], a_s, a_e, b_s, b_e, 5, 3)
+
+
+@pytest.mark.parametrize("na", [5, 63 * 40, 64 * 40, 65 * 40, 200 * 40])
+@pytest.mark.parametrize("n_b", [30_000, 300_000])
+def test_few_records_a_shuffle(na, n_b):
+    """Around 64 records per region and shuffle, where a wave's walk over the shuffles changes form."""
+    rng = np.random.default_rng(na + n_b)
+    b_s, b_e = intervals(rng, 0, 4_000_000, n_b, 300)
+    a_s, a_e = intervals(rng, 0, 4_000_000, na, 3000)
+    check([4_000_000], a_s, a_e, b_s, b_e, 40, 33)

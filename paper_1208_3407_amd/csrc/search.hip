@@ -16,6 +16,7 @@
 #include <unordered_map>
 
 #include "bits_internal.hpp"
+#include "near.hpp"
 
 // Waves per SIMD the search kernels are compiled for (caps their VGPRs).
 #ifndef BITS_SEARCH_WAVES_PER_EU
@@ -123,7 +124,6 @@ __device__ __forceinline__ void bisect_multi(const uint32_t* __restrict__ ks, co
 // selects non-temporal loads (data lines, no reuse) over cached ones (line
 // heads, kept in L2).  `scr` is this wave's LDS scratch of 4 * NC * 64
 // words.  Must be called by all 64 lanes.
-constexpr uint32_t kNoLine = 0xFFFFFFFFu;
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
@@ -873,45 +873,18 @@ __device__ __forceinline__ void rank_tiered(const Arrays& A, const uint32_t* tre
 // local density of starts, est = dens (length of a + mean length of B)
 // intervals are expected, and the 128-byte line of rank first - 1 - est, or
 // its neighbour on the side the count of the line points to, holds the answer
-// for all but long queries.  Nothing is assumed about the count: a key range
+// for all but long queries (near_step; a rank on the boundary of two lines is
+// decided by the two together: 3% of the queries, in 88% of the waves, took
+// the full search when it was not, 1e7 queries against 5e6 through the model
+// 617 us, 555 now).  Nothing is assumed about the count: a key range
 // that the two lines do not decide, an interval set whose starts and ends do
 // not belong together, or a query with more than kNearCount expected hits
 // takes the full search.
 // That halves the requests (9.5 -> 4.2 L2 requests per query at 1e7) but makes
-// one chain of waits of two, so it pays where reads miss the caches: 5e7
-// queries against 5e7 through the model 3.34 ms, 3.71 with both searches in
-// full; without a model 4.0 against 5.2 ms there, 1.37 against 1.49 ms at 2e7,
-// but 635 against 600 us at 1e7, and the Monte-Carlo search of a reference of
-// 1e6 613 against 463 us.
-constexpr float kNearCount = 256.0f;
+// one chain of waits of two, so it pays where reads miss the caches: 1e7
+// queries against 5e7 through the model 615 us, 760 with both searches in
+// full; without a model 754 and 1050 us there.
 constexpr int kNearSteps = 4;   // rounds of up to eight lanes
-
-// One step: the count of the line at w; on return either r is known (true) or
-// w is the neighbouring line to look at.
-__device__ __forceinline__ bool near_step(uint32_t n, uint32_t cnt, uint32_t& w, uint32_t& r) {
-    if (cnt == 0u) {                       // r <= w
-        r = 0u;
-        if (w == 0u) return true;
-        w -= 32u;
-        return false;
-    }
-    r = w + cnt;
-    if (cnt < 32u) return true;
-    w += 32u;                              // r >= w
-    if (w >= n) return true;               // the array ends here: r = n
-    return false;
-}
-
-// first, the starts' density and the query -> the first line to look at, or
-// kNoLine for the full search; `done` when #{B_E < s} is 0 without a look.
-__device__ __forceinline__ uint32_t near_line(uint32_t n, uint32_t first, float dens, float mean, uint32_t s, uint32_t e,
-                                              bool& done) {
-    done = s == 0u;
-    const float est = dens * ((float)(e - s) + mean);
-    if (done || e == 0xFFFFFFFFu || !(est <= kNearCount)) return kNoLine;
-    const uint32_t back = 1u + (uint32_t)est;
-    return (first > back ? min(first - back, n - 1u) : 0u) & ~31u;
-}
 
 // RANK(array, 0 = B_S or 1 = B_E, x[NC], r[NC], dens[NC]) is the full search of
 // NC chains, LINE(K, w[NC], x[NC], cnt[NC]) counts lines (kNoLine: idle).
@@ -931,7 +904,7 @@ __device__ __forceinline__ void icount_near(const SearchArgs& sa, const uint32_t
         x[q] = as[q];
         bool done;
         w[q] = near_line(sa.n, fst[q], dens[q], sa.mean_len, as[q], ae[q], done);
-        r[q] = 0u;
+        r[q] = done ? 0u : kNoLine;
         open[q] = !done;
         any |= w[q] != kNoLine;
     }

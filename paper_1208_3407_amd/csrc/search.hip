@@ -884,7 +884,12 @@ __device__ __forceinline__ void rank_tiered(const Arrays& A, const uint32_t* tre
 // one chain of waits of two, so it pays where reads miss the caches: 1e7
 // queries against 5e7 through the model 615 us, 760 with both searches in
 // full; without a model 754 and 1050 us there.
-constexpr int kNearSteps = 4;   // rounds of up to eight lanes
+// Lines after the first: 2% of the queries with 40 expected hits need the
+// second, 0.02% a third.
+constexpr int kNearLooks = 2;
+// Lanes served eight at a time, more by a probe of the whole wave (1e7 queries
+// with 110 expected hits: 8, 16, 24 lanes 429, 422, 398 us).
+constexpr uint32_t kNearFew = 24;
 
 // RANK(array, 0 = B_S or 1 = B_E, x[NC], r[NC], dens[NC]) is the full search of
 // NC chains, LINE(K, w[NC], x[NC], cnt[NC]) counts lines (kNoLine: idle).
@@ -918,17 +923,37 @@ __device__ __forceinline__ void icount_near(const SearchArgs& sa, const uint32_t
             }
         }
     }
-    // the few lanes whose line did not decide
-#pragma unroll
-    for (int q = 0; q < QPL; ++q) {
+    // the neighbouring line for lanes that the first did not decide: as many looks for
+    // each of them, whatever the other lanes need
 #pragma unroll 1
-        for (int step = 0; step < kNearSteps; ++step) {
-            uint64_t on = __ballot(w[q] != kNoLine);
-            if (!on) break;
-            const uint32_t k = few_windows<true>(sa.be, w[q], x[q], on);
-            if (((on >> (threadIdx.x & (kWave - 1))) & 1u) && near_step(sa.n, k, w[q], r[q])) {
-                open[q] = false;
-                w[q] = kNoLine;
+    for (int look = 0; look < kNearLooks; ++look) {
+        uint32_t most = 0;
+#pragma unroll
+        for (int q = 0; q < QPL; ++q) most = max(most, (uint32_t)__popcll(__ballot(w[q] != kNoLine)));
+        if (!most) break;
+        if (most > kNearFew) {
+            line(sa.be, w, x, c);
+#pragma unroll
+            for (int q = 0; q < QPL; ++q) {
+                if (w[q] != kNoLine && near_step(sa.n, c[q], w[q], r[q])) {
+                    open[q] = false;
+                    w[q] = kNoLine;
+                }
+            }
+            continue;
+        }
+#pragma unroll
+        for (int q = 0; q < QPL; ++q) {
+            uint64_t left = __ballot(w[q] != kNoLine);
+#pragma unroll 1
+            while (left) {
+                uint64_t on = left;
+                const uint32_t k = few_windows<true>(sa.be, w[q], x[q], on);
+                left &= ~on;
+                if (((on >> (threadIdx.x & (kWave - 1))) & 1u) && near_step(sa.n, k, w[q], r[q])) {
+                    open[q] = false;
+                    w[q] = kNoLine;
+                }
             }
         }
     }

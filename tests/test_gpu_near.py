@@ -55,3 +55,13 @@ def test_ranks_on_line_boundaries(ref):
     got = [run(ref, edge, s) for s in SHAPES]
     # the first search of a moved query can change leaves, the second must not run
     assert abs(got[0] - mid[0]) <= 100, (got, mid)
+
+
+def test_looks_do_not_depend_on_the_wave(ref):
+    """All ranks on line boundaries, so that every lane needs its second look: the searches that run in full
+    are those of a mid-line set, at every launch shape."""
+    rng = np.random.default_rng(4)
+    rank = rng.integers(1, N // 32 - 1, 20_000) * 32
+    mid = run(ref, rank + 5, None)
+    got = [run(ref, rank, s) for s in SHAPES]
+    assert len(set(got)) == 1 and abs(got[0] - mid) <= 600, (got, mid)   # 600: 3% of the first searches in other leaves

@@ -10,7 +10,12 @@
 namespace bits {
 
 constexpr uint32_t kNoLine = 0xFFFFFFFFu;
-constexpr float kNearCount = 256.0f;
+// Expected hits up to which a line is looked at: with more the line is missed
+// too often and the look comes on top of the full search.  1e7 queries against
+// 5e6 keys through the model with 30, 50, 80, 130, 180 hits each: at 64 in
+// every lane of the wave 624, 650, 649, 648, 648 us; at 160 622, 686, 758, 649, 649;
+// at 64 lane by lane 620, 717, 712, 650, 647; both searches in full 648.
+constexpr float kNearCount = 64.0f;
 
 // One step towards r = #{K < x}: cnt = #{keys < x} of the line at w.  On
 // return either r is known (true), or w is the neighbouring line to look at

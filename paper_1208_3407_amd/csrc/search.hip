@@ -911,6 +911,8 @@ __device__ __forceinline__ void icount_near(const SearchArgs& sa, const uint32_t
         w[q] = near_line(sa.n, fst[q], dens[q], sa.mean_len, as[q], ae[q], done);
         r[q] = done ? 0u : kNoLine;
         open[q] = !done;
+        // one lane's full search is the whole wave's work: no line is then looked at for the others
+        if (__ballot(open[q] && w[q] == kNoLine)) w[q] = kNoLine;
         any |= w[q] != kNoLine;
     }
     if (__ballot(any)) {

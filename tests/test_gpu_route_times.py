@@ -1,0 +1,64 @@
+"""Rules that choose between two forms of a call must not choose one that is
+clearly the slower: times of the chosen form and of a yardstick that does the
+same work, taken in turn, the least of several.  The bounds lie between the
+ratio of a right choice and the ratio of the wrong one, both measured."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+from paper_1208_3407_amd import bits, datagen  # noqa: E402
+
+DEV = torch.device("cuda", 0)
+
+
+def up(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.uint32)).to(DEV)
+
+
+def once(fn, inner):
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    for _ in range(inner):
+        fn()
+    e1.record()
+    e1.synchronize()
+    return e0.elapsed_time(e1) / inner
+
+
+def ratio(fn, yardstick, inner=4, rounds=8):
+    for f in (fn, yardstick):
+        f()
+        f()
+    torch.cuda.synchronize()
+    t = [(once(fn, inner), once(yardstick, inner)) for _ in range(rounds)]
+    r = min(a for a, _ in t) / min(b for _, b in t)
+    print("ratio %.3f (%.1f us)" % (r, 1e3 * min(a for a, _ in t)), flush=True)
+    return r
+
+
+def project(lengths, local):
+    return bits.bits_project(lengths, up(local.chrom), up(local.start), up(local.end))
+
+
+def fixed_length(lengths, n, L, seed):
+    s = np.random.default_rng(seed).integers(0, int(np.sum(lengths)) - L, n)
+    return up(s), up(s + L - 1)
+
+
+def count_into(ref, q, launch=None):
+    counts = torch.empty(q[0].numel(), dtype=torch.uint32, device=DEV)
+    total = torch.empty(1, dtype=torch.uint64, device=DEV)
+    return lambda: bits.bits_count_per_query(ref, *q, launch=launch, counts=counts, total=total)
+
+
+def test_learned_count_of_long_queries():
+    """Queries with some 170 expected hits against ones with thousands, which take both searches in full
+    (right 1.0, wrong 1.25)."""
+    lengths, _, B = datagen.w2_sets(seed=11, n_a=10, n_b=5_000_000)
+    ref = bits.bits_sort_ref(*project(lengths, B), learned=True, train={"epochs": 20, "max_points": 64})
+    long, longer = (fixed_length(lengths, 5_000_000, L, 12) for L in (100_000, 1_000_000))
+    assert ratio(count_into(ref, long), count_into(ref, longer)) < 1.12

@@ -134,10 +134,8 @@ __host__ __device__ constexpr size_t search_lds_bytes(bool learned, uint32_t dep
 enum : int { kModePlain = 0, kModeLearned = 1, kModeTiered = 2, kModeDirect = 3, kModePaired = 4 };
 __host__ __device__ constexpr bool learned_mode(int mode) { return mode == kModeLearned || mode == kModePaired; }
 constexpr uint32_t kPlainKeys = 1u << 14;
-constexpr uint32_t kPairedKeys = 1u << 16;
+constexpr uint32_t kPairedKeys = 1u << 15;
 constexpr uint32_t kDirectKeys = 1u << 19;
-// Above this the tiered search looks for a query's second rank next to its first.
-constexpr uint32_t kNearKeys = 1u << 24;
 
 // Copy the first 2^d - 1 nodes of both trees into LDS: lds[0..2^d) starts,
 // lds[2^d..2^(d+1)) ends, 1-based BFS order (slot 0 unused).

@@ -881,9 +881,11 @@ __device__ __forceinline__ void rank_tiered(const Arrays& A, const uint32_t* tre
 // not belong together, or a query with more than kNearCount expected hits
 // takes the full search.
 // That halves the requests (9.5 -> 4.2 L2 requests per query at 1e7) but makes
-// one chain of waits of two, so it pays where reads miss the caches: 1e7
-// queries against 5e7 through the model 615 us, 760 with both searches in
-// full; without a model 754 and 1050 us there.
+// one chain of waits of two, so it pays where reads miss the nearest caches.
+// 1e7 queries with both searches in step and so: through the model against 2e4
+// keys 316 and 339 us, 5e4 371 and 297, 1e5 485 and 379, 1e6 601 and 510, 5e6
+// 632 and 556, 5e7 766 and 615; without a model (line heads) against 1e6 560
+// and 484, 5e6 603 and 533, 2e7 775 and 633, 5e7 1225 and 761.
 // Lines after the first: 2% of the queries with 40 expected hits need the
 // second, 0.02% a third.
 constexpr int kNearLooks = 2;
@@ -991,8 +993,7 @@ __device__ __forceinline__ void icount_learned(const SearchArgs& sa, uint32_t* s
 
 // The same with both searches of a query in step, for references up to
 // kPairedKeys keys: their lines are in L2, where a second wait costs more than
-// the requests it saves (1.5e7 queries against 2e3 keys 350 us, 510 near; 2e4
-// 455, 560; 1e5 737, 689).
+// the requests it saves (measured at icount_near).
 template <int QPL>
 __device__ __forceinline__ void icount_paired(const SearchArgs& sa, uint32_t* scr, const uint32_t (&as)[QPL],
                                               const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL], uint32_t (&fst)[QPL]) {
@@ -1011,9 +1012,9 @@ __device__ __forceinline__ void icount_paired(const SearchArgs& sa, uint32_t* sc
     }
 }
 
-// One query at a time: the windows of more would not fit the registers.  Up to
-// kNearKeys keys both searches of a query run in step, which hides their waits
-// in each other's; above, the second search starts from the first one's rank.
+// One query at a time: the windows of more would not fit the registers.  In
+// windows of keys both searches of a query run in step, which hides their waits
+// in each other's; through the line heads the second starts from the first one's rank.
 template <int QPL, bool DIRECT>
 __device__ __forceinline__ void icount_tiered(const SearchArgs& sa, const uint32_t* lds, const uint32_t (&as)[QPL],
                                               const uint32_t (&ae)[QPL], uint32_t (&cnt)[QPL],
@@ -1021,11 +1022,11 @@ __device__ __forceinline__ void icount_tiered(const SearchArgs& sa, const uint32
     const uint32_t* tree_e = lds + (1u << sa.depth);
 #pragma unroll 1
     for (int q = 0; q < QPL; ++q) {
-        if (DIRECT || sa.n <= kNearKeys) {
+        if constexpr (DIRECT) {
             const uint32_t x[2] = {ae[q] + 1u, as[q]};
             uint32_t r[2];
             float dens[2];
-            rank_tiered<2, DIRECT>(both_arrays(sa), lds, tree_e, sa.depth, x, r, dens);
+            rank_tiered<2, true>(both_arrays(sa), lds, tree_e, sa.depth, x, r, dens);
             const uint32_t first = (ae[q] == 0xFFFFFFFFu) ? sa.n : r[0];
             cnt[q] = first - r[1];
             fst[q] = first;

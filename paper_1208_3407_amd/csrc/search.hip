@@ -1868,8 +1868,19 @@ __global__ void __launch_bounds__(1024)
     uint32_t cur = 0xFFFFFFFFu;
     SearchArgs sa{};
     uint32_t bad = 0;
+    // The lane's sum for the pair of the last items: one addition to a total per wave and run
+    // of its items (with one per item, 2 x 2 pairs of 1e6 queries against 3e4 keys 295 us, 119 so).
+    uint64_t acc = 0, pair = 0;
+    auto flush = [&] {
+        acc = wave_sum_u64(acc);
+        if ((threadIdx.x & (kWave - 1)) == 0 && acc) atomicAdd(pair_totals + pair, (unsigned long long)acc);
+        acc = 0;
+    };
     for (uint32_t it = i0; it < i1; ++it) {
         const BatchItem item = items[it];
+        const uint64_t p = (uint64_t)item.q * n_ref + item.r;
+        if (p != pair) flush();
+        pair = p;
         if (item.r != cur) {
             const BatchRef R = refs[item.r];
             sa.bs = R.bs;
@@ -1917,13 +1928,10 @@ __global__ void __launch_bounds__(1024)
 #pragma unroll
             for (int q = 0; q < QPL; ++q) cnt[q] = 0;
         }
-        uint64_t acc = 0;
 #pragma unroll
         for (int q = 0; q < QPL; ++q) acc += valid[q] ? cnt[q] : 0u;
-        acc = wave_sum_u64(acc);
-        if ((threadIdx.x & (kWave - 1)) == 0 && acc)
-            atomicAdd(pair_totals + (uint64_t)item.q * n_ref + item.r, (unsigned long long)acc);
     }
+    flush();
     if (bad) atomicOr(status, BITS_FLAG_INTERVAL);
 }
 

@@ -65,3 +65,26 @@ def test_looks_do_not_depend_on_the_wave(ref):
     mid = run(ref, rank + 5, None)
     got = [run(ref, rank, s) for s in SHAPES]
     assert len(set(got)) == 1 and abs(got[0] - mid) <= 600, (got, mid)   # 600: 3% of the first searches in other leaves
+
+
+def test_batch_searches_as_the_count(ref):
+    """A batch plan over references with models takes the same searches as a count of each pair: totals and
+    fallbacks agree, references around the size where both searches of a query go in step among them."""
+    rng = np.random.default_rng(5)
+    q = [(up(s), up(s + 100)) for s in (rng.integers(0, N * STEP, n) for n in (1, 900, 5000))]
+    refs = [ref]
+    for n in (1, 32_767, 32_768, 32_769, 65_537):
+        s = rng.integers(0, N * STEP, n)
+        refs.append(bits.bits_sort_ref(up(s), up(s + LEN), learned=True, train={"epochs": 5, "max_points": 64}))
+
+    def fallbacks():
+        return [bits.bits_rmi_info(r)["fallbacks"] for r in refs]
+
+    f0 = fallbacks()
+    exp = torch.stack([torch.cat([bits.bits_count(r, *a).view(torch.int64) for r in refs]) for a in q])
+    f1 = fallbacks()
+    plan = bits.bits_batch_create(refs, q)
+    assert torch.equal(bits.bits_batch_run(plan).view(torch.int64).view(len(q), len(refs)), exp)
+    f2 = fallbacks()
+    bits.bits_batch_destroy(plan)
+    assert [b - a for a, b in zip(f0, f1)] == [c - b for b, c in zip(f1, f2)] and f2[0] > f1[0] > f0[0]

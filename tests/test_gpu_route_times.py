@@ -62,3 +62,16 @@ def test_learned_count_of_long_queries():
     ref = bits.bits_sort_ref(*project(lengths, B), learned=True, train={"epochs": 20, "max_points": 64})
     long, longer = (fixed_length(lengths, 5_000_000, L, 12) for L in (100_000, 1_000_000))
     assert ratio(count_into(ref, long), count_into(ref, longer)) < 1.12
+
+
+def test_batch_of_few_large_pairs():
+    """A plan of 2 x 2 pairs, searched pair by pair, against a count of each pair (right 1.2, with an atomic
+    addition for every wave and work item 2.9)."""
+    lengths = datagen.genome_g24()
+    sets = [datagen.w1_sets(seed=s, n_a=1_000_000, n_b=30_000)[1:] for s in (13, 14)]
+    q = [project(lengths, a) for a, _ in sets]
+    refs = [bits.bits_sort_ref(*project(lengths, b)) for _, b in sets]
+    plan = bits.bits_batch_create(refs, q)
+    total = torch.empty(1, dtype=torch.uint64, device=DEV)
+    assert ratio(lambda: bits.bits_batch_run(plan), lambda: [bits.bits_count(r, *a, total=total) for a in q for r in refs]) < 2.0
+    bits.bits_batch_destroy(plan)

@@ -323,6 +323,15 @@ __device__ __forceinline__ T wave_inclusive_scan(T x) {
     return x;
 }
 
+// Lane i's value in every lane of the wave (i uniform).
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t i) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)i);
+}
+
+__device__ __forceinline__ uint64_t lane_value(uint64_t x, uint32_t i) {
+    return ((uint64_t)lane_value((uint32_t)(x >> 32), i) << 32) | lane_value((uint32_t)x, i);
+}
+
 // Staged binning (second sweep): chromosomes with kStageMinRegions..kStageRegions
 // regions; kStageRecs records staged at a time, so that the workgroup's LDS (about
 // 76 KB) still lets two workgroups share a CU.
@@ -343,7 +352,7 @@ __device__ __forceinline__ uint32_t half16(const uint32_t* w, uint32_t j) {
 
 // Binning of shuffles [sb, sb + nb): a workgroup makes the placements of one
 // chromosome k's queries (table positions [cursor[k] - hist[k], cursor[k])) in
-// one shuffle s, or in `per` shuffles in turn (MANY), counts them per region,
+// one shuffle s, or in several in turn (MANY, place_share), counts them per region,
 // writes the segment table of (s, every region of k), and writes the records
 // {start, end} in region order to recs[s * na + table position range].  A group
 // of at most kGroupRecs entries is placed once and held in registers; a larger
@@ -356,11 +365,50 @@ __device__ __forceinline__ uint32_t half16(const uint32_t* w, uint32_t j) {
 // A workgroup of 4000 entries spends half its time on its start, the region
 // table and the chain of loads and barriers before its first store, so it takes
 // several shuffles (1e5 entries in 24 chromosomes x 2000 shuffles: 800 -> 648 us;
-// 2000 x 100: 21.3 -> 18.9 us).
+// 2000 x 100: 21.3 -> 18.9 us): as many as place_share gives it.
+
+// A (shuffle, chromosome)'s work in entries, counting what it takes besides
+// them: about 1.8 us with none, 3.9 with 830, 6.9 with 4200, 0.9 ns for each
+// further one.  Concave, so no spread of the entries over the chromosomes makes
+// the sum larger than the even one does.
+__host__ __device__ __forceinline__ float group_cost(float h) {
+    const float more = 4.0f * h;
+    return h + 2048.0f + (more < 6144.0f ? more : 6144.0f);
+}
+
+// The chromosome and the shuffles [s0, s1) of workgroup b when workgroups take
+// several: chromosome k has group_cost(hist[k]) inv workgroups, rounded, at
+// least 1 and at most nb, which split the shuffles evenly, so that a workgroup's
+// work does not depend on how the queries lie over the chromosomes (1e5
+// queries x 1000 shuffles on 24 of 256 chromosomes, 65 shuffles for each
+// workgroup: 5140 us; 1310 so, 2250 with one).  False past the last share.  All lanes call it.
+__device__ __forceinline__ bool place_share(const BinGeom& g, const uint32_t* __restrict__ hist, uint32_t nb, float inv,
+                                            uint32_t b, uint32_t& k, uint32_t& s0, uint32_t& s1) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    uint32_t before = 0;
+    for (uint32_t j = 0; j < g.n_chrom; j += kWave) {
+        const uint32_t c = j + lane;
+        const uint32_t h = hist[min(c, g.n_chrom - 1u)];
+        const uint32_t v = c < g.n_chrom ? min(nb, max(1u, (uint32_t)(group_cost((float)h) * inv + 0.5f))) : 0u;
+        const uint32_t x = wave_inclusive_scan<uint32_t>(v);
+        const uint64_t past = __ballot(before + x > b);
+        if (past) {
+            const uint32_t l = (uint32_t)__builtin_ctzll(past), n = lane_value(v, l);
+            const uint32_t i = b - (before + lane_value(x, l) - n);
+            k = j + l;
+            s0 = nb * i / n;
+            s1 = nb * (i + 1u) / n;
+            return true;
+        }
+        before += lane_value(x, kWave - 1);
+    }
+    return false;
+}
+
 template <bool MANY>
 __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     BinGeom g, const uint2* __restrict__ packed, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ cursor,
-    uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, uint32_t per, const uint32_t* __restrict__ cell_region,
+    uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, float inv, const uint32_t* __restrict__ cell_region,
     const uint64_t* __restrict__ nreg_p, uint32_t nreg_max, uint32_t* __restrict__ seg_start,
     uint32_t* __restrict__ seg_cnt, uint2* __restrict__ recs) {
     constexpr int kChunkPer = MANY ? 6 : 10;   // a chunk's entries per thread
@@ -373,8 +421,8 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     __shared__ uint2 stage[kStageRecs];             // the chunk's records in region order; h of the direct path
     __shared__ uint32_t wsum[kBinThreads / kWave];
     __shared__ uint32_t staged_total;
-    const uint32_t wgs = MANY ? (nb + per - 1u) / per : nb, k = blockIdx.x / wgs;
-    const uint32_t s0 = (blockIdx.x - k * wgs) * (MANY ? per : 1u), s1 = MANY ? min(nb, s0 + per) : s0 + 1u;
+    uint32_t k = blockIdx.x / nb, s0 = blockIdx.x - k * nb, s1 = s0 + 1u;
+    if (MANY && !place_share(g, hist, nb, inv, blockIdx.x, k, s0, s1)) return;
     const uint32_t c0 = g.cb[k], nc = g.cb[k + 1] - c0;
     if (nc == 0) return;
     const uint32_t nreg = (uint32_t)*nreg_p;
@@ -606,15 +654,6 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
             }
         }
     }
-}
-
-// Lane i's value in every lane of the wave (i uniform).
-__device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t i) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)i);
-}
-
-__device__ __forceinline__ uint64_t lane_value(uint64_t x, uint32_t i) {
-    return ((uint64_t)lane_value((uint32_t)(x >> 32), i) << 32) | lane_value((uint32_t)x, i);
 }
 
 // A wave-uniform word read from LDS, in a scalar register.
@@ -974,15 +1013,23 @@ hipError_t launch_bin_batch(const uint32_t* chrom_len, uint32_t n_chrom, const M
     if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
     // Shuffles per workgroup: groups of more than kGroupRecs entries take long enough
     // by themselves; of the others, as many as leave `rounds` workgroups for each of the
-    // two slots a CU has, one when a shuffle's work is mostly latency, up to 6 so that
+    // two slots a CU has: one when a workgroup's few shuffles are mostly latency, two when
+    // they are many (the shares do not fill one round evenly: 2e4 entries x 1000 223 us of
+    // placement at one round, 151 at two; 2000 x 100 19.8, 23.9), up to 6 so that
     // the last round costs little (1e5 entries x 2000: 3, 6, 10 rounds 671, 648, 658 us).
     const uint64_t groups = (uint64_t)n_chrom * nb, mean = na / n_chrom;
-    const uint64_t rounds = std::min<uint64_t>(std::max<uint64_t>(mean / 512, 1), 6);
+    const uint64_t few = groups < 32u * (uint64_t)device_cu_count() ? 1 : 2;
+    const uint64_t rounds = std::min<uint64_t>(std::max<uint64_t>(mean / 512, few), 6);
     const uint64_t slots = 2u * rounds * (uint64_t)device_cu_count();
     const uint32_t per = mean > kGroupRecs ? 1u : (uint32_t)std::min<uint64_t>((groups + slots - 1) / slots, nb);
+    // The chromosomes' shares: (nb + per - 1) / per workgroups for one of mean size; all
+    // together at most as many for each, and one for the rounding.
+    const uint64_t wgs = (nb + per - 1) / per;
+    const float inv = (float)wgs / group_cost((float)na / (float)n_chrom);
+    const uint64_t most = (uint64_t)(1.001 * (double)(n_chrom * wgs)) + n_chrom + 1;
     const auto place = per == 1 ? k_bin_place<false> : k_bin_place<true>;
-    hipLaunchKernelGGL(place, dim3(n_chrom * ((nb + per - 1) / per)), dim3(kBinThreads), 0, s, g,
-                       reinterpret_cast<const uint2*>(w.packed), tab.hist, tab.cursor, na, seed, sb, nb, per,
+    hipLaunchKernelGGL(place, dim3((uint32_t)(per == 1 ? groups : std::min(most, groups))), dim3(kBinThreads), 0, s, g,
+                       reinterpret_cast<const uint2*>(w.packed), tab.hist, tab.cursor, na, seed, sb, nb, inv,
                        w.cell_region, w.nreg, w.nreg_max, w.seg_start, w.seg_cnt, reinterpret_cast<uint2*>(w.recs));
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
     if (w.splits > 1)

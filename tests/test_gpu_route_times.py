@@ -75,3 +75,19 @@ def test_batch_of_few_large_pairs():
     total = torch.empty(1, dtype=torch.uint64, device=DEV)
     assert ratio(lambda: bits.bits_batch_run(plan), lambda: [bits.bits_count(r, *a, total=total) for a in q for r in refs]) < 2.0
     bits.bits_batch_destroy(plan)
+
+
+def test_binned_on_one_of_many_chromosomes():
+    """Shuffles of a set that lies on one of 256 chromosomes against the same set, reference and chromosome
+    alone (right 1.2, with as many shuffles a workgroup whatever the chromosome holds 8)."""
+    lengths = [240_000_000] + [100_000] * 255
+    rng = np.random.default_rng(15)
+    s = rng.integers(0, lengths[0] - 2000, 400_000)
+    b = rng.integers(0, lengths[0] - 2000, 1_000_000)
+    ref, q = bits.bits_sort_ref(up(b), up(b + 300)), (up(s), up(s + 300))
+
+    def run(gen):
+        return lambda: bits.bits_mc_binned(ref, *q, gen, 7, 0, 100, batch=100)
+
+    assert torch.equal(run(lengths)().totals.view(torch.int64), run(lengths[:1])().totals.view(torch.int64))
+    assert ratio(run(lengths), run(lengths[:1]), inner=2) < 3

@@ -11,8 +11,8 @@
 // tiles before it in its segment by decoupled look-back (the nearest tile
 // that has published its inclusive prefix ends the walk), and writes its keys
 // out in digit runs.  Every key is read once and written once per pass.  A
-// segment's digits that are constant over it are skipped (each tile reads the
-// segment's four histograms and works out the same schedule, so the sort
+// segment's digits that are constant over it are skipped (the tiles of the first
+// pass work out the schedule from the segment's four histograms, so the sort
 // never waits for the host and needs no launch for it).  Segments that fit
 // one tile are sorted by one workgroup in LDS.  Inputs are never written.
 #include <string.h>
@@ -68,7 +68,8 @@ struct SegDesc {
     uint32_t* vping;
     uint32_t* vout;
     uint32_t vmode;   // 0 keys only, 1 values from vin, 2 values = input index
-    uint32_t clear;   // status words cleared before the sort
+    uint32_t active;  // from the host: status words cleared before the sort; from pass 0 on: bit q
+                      // set if pass q moves keys (digit q takes two or more values in the segment)
     uint32_t* status; // gets BITS_FLAG_SORT if a tile gave up its look-back walk (nullable)
 };
 static_assert(kRoundsKeys[0] == kRoundsVals[0], "smallest tile");
@@ -76,6 +77,7 @@ static_assert(sizeof(SegDesc) == 72, "SegDesc layout");
 
 struct SortPlan {
     uint32_t next_tile[4];   // tile counter of each pass
+    uint32_t active;         // bit q: pass q moves the keys of some segment (set by pass 0)
 };
 
 constexpr int kDescChunk = 44;   // about 3 KB of kernel arguments
@@ -114,7 +116,7 @@ __global__ void __launch_bounds__(256) k_sort_init(SegDesc* dst, DescChunk chunk
     if (blockIdx.x == 0) {
         for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) dst[i] = chunk.d[i];
         for (uint32_t i = 0; i < count; ++i)
-            if (threadIdx.x < chunk.d[i].clear) chunk.d[i].status[threadIdx.x] = 0u;
+            if (threadIdx.x < chunk.d[i].active) chunk.d[i].status[threadIdx.x] = 0u;
     }
     for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nzero; k += (uint64_t)gridDim.x * blockDim.x)
         zero[k] = make_uint4(0u, 0u, 0u, 0u);
@@ -239,11 +241,11 @@ __device__ __forceinline__ void rank_keys(const uint32_t (&key)[ROUNDS], uint32_
 // w ranks keys [w ROUNDS 64, (w + 1) ROUNDS 64) of the tile.  The tile's digit
 // counts are published, the exclusive prefix over the segment's earlier tiles
 // is gathered by look-back (one thread per digit), and the tile, sorted by
-// digit in LDS, is written out in digit runs.  The last pass copies a segment
-// whose keys are all equal.
+// digit in LDS, is written out in digit runs.  Pass 0 copies a segment whose
+// keys are all equal.
 // Eight waves per SIMD (two workgroups a CU) up to 12 rounds.
 template <bool VALS, int ROUNDS>
-__global__ void __launch_bounds__(kSweepThreads, ROUNDS <= 12 ? 8 : 4) k_onesweep(const SegDesc* __restrict__ descs, uint32_t nseg,
+__global__ void __launch_bounds__(kSweepThreads, ROUNDS <= 12 ? 8 : 4) k_onesweep(SegDesc* __restrict__ descs, uint32_t nseg,
                                                             SortPlan* plan, int p,
                                                             unsigned long long* __restrict__ lb, uint32_t ntiles,
                                                             const uint32_t* __restrict__ seg_hist) {
@@ -256,6 +258,7 @@ __global__ void __launch_bounds__(kSweepThreads, ROUNDS <= 12 ? 8 : 4) k_oneswee
     __shared__ uint64_t tmp[4];
     __shared__ uint32_t nzc[kSweepWaves];
     __shared__ uint32_t tile_sh;
+    if (p != 0 && !((plan->active >> p) & 1u)) return;
     if (threadIdx.x == 0) tile_sh = atomicAdd(&plan->next_tile[p], 1u);
     for (int k = threadIdx.x; k < kSweepWaves * 256; k += kSweepThreads) (&wcnt[0][0])[k] = 0;
     __syncthreads();
@@ -269,42 +272,46 @@ __global__ void __launch_bounds__(kSweepThreads, ROUNDS <= 12 ? 8 : 4) k_oneswee
     const uint32_t dg = threadIdx.x;
     // The schedule: pass q is active when digit q takes two or more values in the segment;
     // the last active pass writes the output, earlier ones alternate so that the first
-    // reads the input.  The keys are loaded for the usual case, every pass active, while
-    // the histograms arrive.
-    const uint32_t hv = seg_hist[(size_t)s * 1024 + threadIdx.x];   // digit dg & 255 of pass dg / 256
+    // reads the input.  Pass 0 works it out while its keys arrive, and leaves it in the
+    // descriptor for the later ones, which then read the right buffer or nothing (with the
+    // keys of every pass loaded on the usual schedule, an index of 3e7 keys of one digit took
+    // 1090 us, 880 so, and one of 3e7 starts over the genome 910, 860).
     const uint32_t hp = dg < 256 ? seg_hist[((size_t)s * 4 + p) * 256 + dg] : 0u;
-    const uint32_t usual = p == 0 ? 0u : (p & 1) ? 1u : 2u;
+    uint32_t act = d.active;
+    if (p != 0 && !((act >> p) & 1u)) return;
+    const uint32_t na_ = (uint32_t)__popc(act), r_ = (uint32_t)__popc(act & ((1u << p) - 1u));
+    uint32_t to = ((na_ - 1u - r_) & 1u) ? 1u : 2u, from = p == 0 || r_ == 0u ? 0u : 3u - to;
     uint32_t key[ROUNDS], rank[ROUNDS];
-    const uint32_t* src = buf_ro(d, usual) + begin;
+    const uint32_t* src = buf_ro(d, from) + begin;
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
         const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
         key[r] = idx < cnt ? src[idx] : 0u;
     }
-    const uint64_t nz = __ballot(hv != 0u);
-    if (lane == 0) nzc[w] = (uint32_t)__popcll(nz);
-    __syncthreads();
-    uint32_t act = 0;
+    if (p == 0) {
+        const uint32_t hv = seg_hist[(size_t)s * 1024 + threadIdx.x];   // digit dg & 255 of pass dg / 256
+        const uint64_t nz = __ballot(hv != 0u);
+        if (lane == 0) nzc[w] = (uint32_t)__popcll(nz);
+        __syncthreads();
+        act = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-        if (nzc[4 * q] + nzc[4 * q + 1] + nzc[4 * q + 2] + nzc[4 * q + 3] >= 2u) act |= 1u << q;
-    const uint32_t na = (uint32_t)__popc(act), r = (uint32_t)__popc(act & ((1u << p) - 1u));
-    if (!((act >> p) & 1u)) {
-        if (act || p != 3) return;
-        for (uint32_t k = threadIdx.x; k < cnt; k += kSweepThreads) {
-            d.out[begin + k] = d.in[begin + k];
-            if (VALS && d.vmode) d.vout[begin + k] = d.vmode == 2 ? begin + k : d.vin[begin + k];
+        for (int q = 0; q < 4; ++q)
+            if (nzc[4 * q] + nzc[4 * q + 1] + nzc[4 * q + 2] + nzc[4 * q + 3] >= 2u) act |= 1u << q;
+        if (threadIdx.x == 0 && t == d.tile0) {
+            descs[s].active = act;
+            atomicOr(&plan->active, act);
         }
-        return;
-    }
-    const uint32_t to = ((na - 1u - r) & 1u) ? 1u : 2u, from = r == 0 ? 0u : 3u - to;
-    if (from != usual) {
-        src = buf_ro(d, from) + begin;
+        if (!act) {   // all keys equal: already sorted
 #pragma unroll
-        for (int k = 0; k < ROUNDS; ++k) {
-            const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)k) * kWave + lane;
-            key[k] = idx < cnt ? src[idx] : 0u;
+            for (int r = 0; r < ROUNDS; ++r) {
+                const uint32_t idx = ((uint32_t)w * ROUNDS + (uint32_t)r) * kWave + lane;
+                if (idx >= cnt) continue;
+                d.out[begin + idx] = key[r];
+                if (VALS && d.vmode) d.vout[begin + idx] = d.vmode == 2 ? begin + idx : d.vin[begin + idx];
+            }
         }
+        if (!(act & 1u)) return;
+        to = (__popc(act) - 1) & 1 ? 1u : 2u;
     }
     uint32_t* dst = buf_rw(d, to);
     // values: vmode 2 reads the input index on the first active pass
@@ -566,7 +573,7 @@ size_t sort_workspace_bytes(const uint64_t* n, uint32_t nseg, const uint32_t* vm
 }
 
 template <bool VALS, int ROUNDS>
-static void launch_passes(const SegDesc* descs, uint32_t nseg, SortPlan* plan, unsigned long long* lb, uint32_t ntiles,
+static void launch_passes(SegDesc* descs, uint32_t nseg, SortPlan* plan, unsigned long long* lb, uint32_t ntiles,
                           const uint32_t* seg_hist, hipStream_t s) {
     for (int p = 0; p < 4; ++p)
         hipLaunchKernelGGL((k_onesweep<VALS, ROUNDS>), dim3(ntiles), dim3(kSweepThreads), 0, s, descs, nseg, plan, p, lb,
@@ -611,7 +618,7 @@ int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, h
             ch.d[i].tile0 = tile0;
             ch.d[i].vmode = g.vmode;
             ch.d[i].status = g.status;
-            ch.d[i].clear = g.clear;
+            ch.d[i].active = g.clear;
             if (g.vmode) {
                 ch.d[i].vin = g.vmode == 1 ? g.vin : nullptr;
                 ch.d[i].vping = vping + voff;

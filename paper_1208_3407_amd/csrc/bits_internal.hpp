@@ -123,10 +123,12 @@ __host__ __device__ constexpr size_t search_lds_bytes(bool learned, uint32_t dep
 
 // Forms of the search kernels.  The path without a model (BITS_PATH_TIERED,
 // and AUTO on a reference without one) takes kModeDirect up to kDirectKeys
-// keys and kModeTiered above: a window of keys covers the whole bucket of a
-// small reference (1e6 queries against 3e5: 63 against 71 us through the line
-// heads), but misses as buckets grow (against 1e6: 88 and 86 us, against 2e6:
-// 335 and 144 us).
+// keys in buckets of at most kDirectBucket and kModeTiered else: a window of keys
+// covers the whole bucket of a small reference, but misses as buckets grow, with
+// the keys or with fewer levels of the tree (1e7 queries against 3e5 keys at
+// depth 13, 12, 11, 10, 0: 188, 294, 313, 475, 2270 us, through the line heads
+// 416, 407, 415, 406, 492; 1e6 against 1e5 at depth 13, 11, 10, 0: 29, 30, 38,
+// 208 and 29, 30, 30, 29).
 // AUTO takes the plain path up to kPlainKeys: the LDS tree then resolves all but
 // a step or two (1.5e7 queries against 1e3 keys 81 us, 206 with windows; 8e3
 // 155, 223; 1.6e4 205, 236; 6.4e4 455, 271).  Counting through the models takes
@@ -136,6 +138,10 @@ __host__ __device__ constexpr bool learned_mode(int mode) { return mode == kMode
 constexpr uint32_t kPlainKeys = 1u << 14;
 constexpr uint32_t kPairedKeys = 1u << 15;
 constexpr uint32_t kDirectKeys = 1u << 19;
+constexpr uint32_t kDirectBucket = 128;
+__host__ __device__ constexpr bool direct_form(uint32_t n, uint32_t depth) {
+    return n <= kDirectKeys && (n >> depth) <= kDirectBucket;
+}
 
 // Copy the first 2^d - 1 nodes of both trees into LDS: lds[0..2^d) starts,
 // lds[2^d..2^(d+1)) ends, 1-based BFS order (slot 0 unused).

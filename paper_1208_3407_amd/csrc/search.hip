@@ -801,9 +801,9 @@ __device__ __forceinline__ void icount_heads(const SearchArgs& sa, uint32_t* scr
 // r = #{K < x} to its bucket [base, base + len] and, on the way down, leaves
 // the bucket's bounding keys; keys are dense enough inside a bucket that a
 // straight line between them predicts r to a few keys (about sqrt(len)).
-//   n <= kDirectKeys   a window of 32 keys around the prediction gives r; a
+//   direct_form        a window of 32 keys around the prediction gives r; a
 //                      bucket of at most 28 keys is covered whole.
-//   larger n           j = #{H < x} = ceil(r / 32) over the line heads
+//   else               j = #{H < x} = ceil(r / 32) over the line heads
 //                      H[j] = K[32 j] (1/32 of the array, kept in L2 / the
 //                      Infinity Cache) by windows of 32 heads around the
 //                      predicted line (the median error is 2 heads at 1e7
@@ -1920,7 +1920,7 @@ __global__ void __launch_bounds__(1024)
         }
         if (sa.n) {   // uniform over the workgroup: every item of the loop is one reference
             uint32_t fst[QPL];
-            if (MODE == kModeTiered && sa.n <= kDirectKeys)
+            if (MODE == kModeTiered && direct_form(sa.n, sa.depth))
                 icount<QPL, kModeDirect>(sa, lds, as, ae, cnt, fst);
             else
                 icount<QPL, MODE>(sa, lds, as, ae, cnt, fst);
@@ -2046,10 +2046,10 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The kernel mode of a launch's path (the tiered path has one form per size).
+// The kernel mode of a launch's path (the tiered path has two forms).
 static int search_mode(const SearchArgs& sa, const LaunchCfg& cfg, bool counting = false) {
     if (cfg.path == BITS_PATH_LEARNED) return counting && sa.n <= kPairedKeys ? kModePaired : kModeLearned;
-    if (cfg.path == BITS_PATH_TIERED) return sa.n <= kDirectKeys ? kModeDirect : kModeTiered;
+    if (cfg.path == BITS_PATH_TIERED) return direct_form(sa.n, sa.depth) ? kModeDirect : kModeTiered;
     return kModePlain;
 }
 

@@ -100,3 +100,12 @@ def test_sort_of_equal_keys():
     s = rng.integers(0, 2_900_000_000, 3_000_000)
     varied, equal = (up(s), up(s)), (up(np.full(len(s), 12345)), up(np.full(len(s), 12345)))
     assert ratio(lambda: bits.bits_enum_index_build(*equal), lambda: bits.bits_enum_index_build(*varied)) < 0.6
+
+
+@pytest.mark.parametrize("depth", [0, 6])
+def test_count_with_a_shallow_tree(depth):
+    """The open search of a small reference whose top tree has few levels, or none, against the bisection it
+    replaces (right 0.3, with windows of keys 1.7 and 1.1)."""
+    lengths, A, B = datagen.w1_sets(seed=17, n_a=1_000_000, n_b=300_000)
+    ref, q = bits.bits_sort_ref(*project(lengths, B), depth=depth), project(lengths, A)
+    assert ratio(count_into(ref, q), count_into(ref, q, {"path": 1})) < 0.8

@@ -77,9 +77,10 @@ typedef enum bits_status {
                                      no model (the index the learned path is measured against) */
 
 /* Launch shape of the search kernels.  A NULL bits_launch* means the
- * library defaults, and so do block and qpl both 0 with path AUTO, LEARNED or
- * TIERED: counting, decisions and Monte-Carlo then choose both by the path and
- * the number of searches.  bits_autotune_count picks one by timing. */
+ * library defaults.  With block and qpl both 0 (and grid 0 on the learned
+ * path), counting, decisions and Monte-Carlo choose both by the number of
+ * searches on the learned and tiered paths; the plain path takes the defaults
+ * below.  bits_autotune_count times the shapes of one path. */
 typedef struct bits_launch {
     uint32_t block;   /* threads per workgroup: 256, 512 or 1024 (0 = default 1024); the learned
                          path uses a smaller one when its LDS scratch would not fit */

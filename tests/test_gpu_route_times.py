@@ -109,3 +109,12 @@ def test_count_with_a_shallow_tree(depth):
     lengths, A, B = datagen.w1_sets(seed=17, n_a=1_000_000, n_b=300_000)
     ref, q = bits.bits_sort_ref(*project(lengths, B), depth=depth), project(lengths, A)
     assert ratio(count_into(ref, q), count_into(ref, q, {"path": 1})) < 0.8
+
+
+def test_learned_count_with_a_given_grid():
+    """The learned path with only the number of workgroups given, against the default shape spelled out
+    (right 1.0, with workgroups of 256 threads 2.5)."""
+    lengths, A, B = datagen.w1_sets(seed=18, n_a=1_000_000, n_b=1_000_000)
+    ref = bits.bits_sort_ref(*project(lengths, B), learned=True, train={"epochs": 20, "max_points": 64})
+    q = project(lengths, A)
+    assert ratio(count_into(ref, q, {"grid": 32}), count_into(ref, q, {"grid": 32, "block": 1024, "qpl": 2})) < 1.5

@@ -28,10 +28,17 @@ constexpr uint32_t kMergeThreads = 1024;
 constexpr uint32_t kMergeWaves = kMergeThreads / kWave;
 constexpr uint32_t kChunk = 256;                     // query keys per chunk
 constexpr uint32_t kPerWave = kChunk / kMergeWaves;  // positions a wave walks
-// Reference keys of a chunk counted through the histogram (16-bit counters);
-// a reference with more in one chunk is searched by the chunk's keys instead.
-constexpr uint32_t kLongSlice = 4096;
+// Reference keys of a chunk counted through the histogram (16-bit counters); a
+// reference with more in one chunk is searched by the chunk's keys instead, and
+// where all have more than kDenseChunk together, already one with more than
+// kDenseSlice.  Placing a key costs a chain of reads (1024 keys in about a
+// microsecond), the searches one of steps (four references at once in 10 to 15).
+// 8 sets of 1e5 against 64 references of 1e4 to 5e5 that all lie within 4e6 bp:
+// 1310 us searched by 256 threads a reference at a time, 333 so (452 pair by pair).
+constexpr uint32_t kLongSlice = 4096, kDenseSlice = 512, kDenseChunk = 1u << 16;
 constexpr uint32_t kNoSet = 0xFFFFFFFFu;
+constexpr uint32_t kQuarters = kMergeThreads / kChunk;
+static_assert(kWave % kQuarters == 0, "long slices");
 static_assert(kLongSlice < 65536, "histogram counters are 16-bit");
 
 // The query sets' keys one after another (set i at offs[i]): ends into ks,
@@ -108,17 +115,31 @@ __global__ void __launch_bounds__(256) k_merge_splits(const BatchRef* __restrict
     }
 }
 
-// Workgroup w of group g (64 references) takes tasks [w T / W, (w + 1) T / W)
-// of the group's T = 2 * chunks (list, chunk) tasks and writes its sums,
+// Sum over the lanes up to this one.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o);
+        if (lane >= (uint32_t)o) x += y;
+    }
+    return x;
+}
+
+// Workgroup w of group g (64 references) takes every W-th, from the w-th on, of
+// the group's 2 * chunks (list, chunk) tasks and writes its sums,
 // ends' ranks minus starts' ranks modulo 2^64, to part[((g W + w) n_q + i) 64 + lane].
 // Dynamic LDS: the accumulators, n_q * 64 uint64.
+// (Neighbouring chunks go to different workgroups so that none has all the
+// chunks of a place where the references are dense: 333 us for those 64
+// references, 804 with tasks in a row; elsewhere within 2%, mostly faster.)
 // What bounds it: the latency of a chunk's steps between its six barriers
 // (slice bounds, reference keys, bisections), so waves per CU decide: 32 sets
 // of 3e6 keys in all against 64 references of 5e6 took 395 us with 512 threads
 // a workgroup and three a CU, 307 with 1024 and a third one waiting, 284 with
 // two of 1024 (chunks of 128 keys and four of 512: 263, but the splits then
 // cost more).
-__global__ void __launch_bounds__(kMergeThreads) k_merge_count(
+__global__ void __launch_bounds__(kMergeThreads, 8) k_merge_count(
     const BatchRef* __restrict__ refs, uint32_t n_ref, uint32_t n_q, const uint32_t* __restrict__ ks,
     const uint32_t* __restrict__ ke, const uint32_t* __restrict__ ss, const uint32_t* __restrict__ se, uint32_t total,
     uint32_t chunks, const uint32_t* __restrict__ splits, unsigned long long* __restrict__ part) {
@@ -136,9 +157,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_count(
     }
     for (uint32_t k = threadIdx.x; k < n_q * kWave; k += kMergeThreads) acc[k] = 0ull;
     const uint32_t tasks = 2u * chunks;
-    const uint32_t t0 = (uint32_t)((uint64_t)tasks * blockIdx.x / gridDim.x);
-    const uint32_t t1 = (uint32_t)((uint64_t)tasks * (blockIdx.x + 1) / gridDim.x);
-    for (uint32_t t = t0; t < t1; ++t) {
+    for (uint32_t t = blockIdx.x; t < tasks; t += gridDim.x) {
         const uint32_t a = t >= chunks ? 1u : 0u, c = t - a * chunks;
         const uint32_t b0 = c * kChunk, cnt = min(kChunk, total - b0);
         __syncthreads();   // the previous task is done with the LDS
@@ -152,16 +171,15 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_count(
             const uint32_t* sp = splits + ((uint64_t)a * (chunks + 1) + c) * n_ref + j0;
             const bool in = j0 + lane < n_ref;
             const uint32_t r0 = in ? sp[lane] : 0u, r1 = in ? sp[n_ref + lane] : 0u;
-            const uint32_t l = r1 - r0, s = l <= kLongSlice ? l : 0u;
-            uint32_t x = s;
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const uint32_t y = __shfl_up(x, o);
-                if (lane >= (uint32_t)o) x += y;
+            const uint32_t l = r1 - r0;
+            uint32_t s = l <= kLongSlice ? l : 0u, x = wave_prefix(s);
+            if (__shfl(x, kWave - 1) > kDenseChunk) {   // uniform
+                s = l <= kDenseSlice ? l : 0u;
+                x = wave_prefix(s);
             }
             first[lane] = r0;
-            len[lane] = l;
-            base[lane] = l <= kLongSlice ? r0 : 0u;
+            len[lane] = l - s;   // searched
+            base[lane] = s == l ? r0 : 0u;
             pre[lane] = x - s;
             if (lane == kWave - 1) pre[kWave] = x;
         }
@@ -185,14 +203,15 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_count(
             p += (a ? key[p] <= b : key[p] < b) ? 1u : 0u;
             if (p < cnt) atomicAdd(&hist[p * (kWave / 2) + lo / 2], 1u << (16 * (lo & 1u)));
         }
-        // references with long slices: a search per query key
-        if (__ballot(len[lane] > kLongSlice)) {
-            for (uint32_t j = 0; j < kWave; ++j) {
-                if (len[j] <= kLongSlice) continue;   // uniform
-                if (threadIdx.x < cnt && set[threadIdx.x] != kNoSet) {
-                    const uint64_t r = rank_of(arr[a][j], first[j], len[j], key[threadIdx.x], a != 0);
-                    atomicAdd(&acc[set[threadIdx.x] * kWave + j], (unsigned long long)(a ? 0ull - r : r));
-                }
+        // references with long slices: a search per query key, each quarter of the workgroup
+        // for another reference
+        for (uint64_t left = __ballot(len[lane] != 0u); left;) {
+            const uint32_t j1 = (uint32_t)__builtin_ctzll(left) / kQuarters * kQuarters;
+            left &= ~(((1ull << kQuarters) - 1ull) << j1);
+            const uint32_t k = threadIdx.x % kChunk, j = j1 + threadIdx.x / kChunk;
+            if (k < cnt && len[j] && set[k] != kNoSet) {
+                const uint64_t r = rank_of(arr[a][j], first[j], len[j], key[k], a != 0);
+                atomicAdd(&acc[set[k] * kWave + j], (unsigned long long)(a ? 0ull - r : r));
             }
         }
         __syncthreads();

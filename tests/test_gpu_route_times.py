@@ -118,3 +118,21 @@ def test_learned_count_with_a_given_grid():
     ref = bits.bits_sort_ref(*project(lengths, B), learned=True, train={"epochs": 20, "max_points": 64})
     q = project(lengths, A)
     assert ratio(count_into(ref, q, {"grid": 32}), count_into(ref, q, {"grid": 32, "block": 1024, "qpl": 2})) < 1.5
+
+
+def test_batch_over_references_dense_in_one_place():
+    """The sorted form over references whose keys all lie within a few million base pairs, against references
+    of the same sizes spread over the genome (right 1.2, one reference after the other 4.6)."""
+    rng = np.random.default_rng(19)
+    lengths = datagen.genome_g24()
+    sizes = np.rint(np.exp(rng.uniform(np.log(1e4), np.log(5e5), 64))).astype(int)
+    q = [fixed_length(lengths, 100_000, 300, k) for k in range(8)]
+
+    def plan(starts):
+        return bits.bits_batch_create([bits.bits_sort_ref(up(s), up(s + 199)) for s in starts], q)
+
+    dense = plan([(1e9 + rng.normal(0, 1e6, n)).astype(np.int64) for n in sizes])
+    spread = plan([rng.integers(0, int(np.sum(lengths)) - 200, n) for n in sizes])
+    assert ratio(lambda: bits.bits_batch_run(dense), lambda: bits.bits_batch_run(spread)) < 3
+    for p in (dense, spread):
+        bits.bits_batch_destroy(p)

@@ -2087,24 +2087,37 @@ static hipError_t launch_count_q(const SearchArgs& sa, const LaunchCfg& cfg, con
 // The shape of a search when the caller left it open.  Without a model: one
 // query per lane, and the largest workgroup that still gives every CU one
 // (each stages its own copy of the top trees).  With one: small workgroups,
-// which stage nothing and finish apart, and one query per lane, two in the
-// shuffles of a large set (1024 threads lowered to what the LDS scratch of two
-// queries per lane allows, before: counting 1e4 queries in 1e4 23.6 -> 14.3 us,
-// 1e5 in 5e6 34.0 -> 17.5, 5e7 in 5e7 3180 -> 3050; 1e5 x 100 shuffles in 1e6
-// one query 392, two 382, before 478 us; 1e4 x 100 in 1e5 200, 215, 258), and
-// in large counts against small references, whose two searches go in step
-// (1.5e7 in 2e4 455 and 439 us).
-static LaunchCfg open_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na, bool shuffles = false) {
+// which stage nothing and finish apart, and one query per lane (1024 threads
+// lowered to what the LDS scratch of two queries per lane allows, before:
+// counting 1e4 queries in 1e4 23.6 -> 14.3 us, 1e5 in 5e6 34.0 -> 17.5, 5e7 in
+// 5e7 3180 -> 3050), two in large counts against small references, whose two
+// searches go in step (1.5e7 in 2e4 455 and 439 us).
+static LaunchCfg open_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na) {
     LaunchCfg c = cfg;
     if (!c.open) return c;
     if (c.path == BITS_PATH_LEARNED) {
-        c.qpl = (shuffles ? na >= (1u << 22) : n <= kPairedKeys && na >= (1u << 20)) ? 2u : 1u;
+        c.qpl = n <= kPairedKeys && na >= (1u << 20) ? 2u : 1u;
         c.block = 256u;
     }
     if (c.path != BITS_PATH_TIERED) return c;
     const uint64_t cus = (uint64_t)device_cu_count();
     c.qpl = 1;
     c.block = na >= 1024 * cus ? 1024u : na >= 512 * cus ? 512u : 256u;
+    return c;
+}
+
+// The same for k_mc_sorted, na queries in all shuffles together.  A larger
+// workgroup sorts more placements at once, which pays when many of them search
+// a large reference (256, 512, 1024 threads: 1e6 x 200 against 5e7 keys 9730,
+// 9480, 9140 us, 1e6 x 50 2590, 2550, 2500; 1e6 x 10 798, 844, 925; 1e6 x 200
+// against 5e6 7320, 7370, 7250, against 1e6 6160, 6330, 6350; 1e5 x 100 against
+// 1e6 369, 374, 417).
+static LaunchCfg open_shuffle_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na) {
+    LaunchCfg c = open_shape(cfg, n, na);
+    if (c.open && c.path == BITS_PATH_LEARNED) {
+        c.qpl = 1u;
+        c.block = n >= (1u << 24) && na >= (1u << 25) ? 1024u : 256u;
+    }
     return c;
 }
 
@@ -2211,7 +2224,7 @@ hipError_t launch_mc(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t
                      const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
                      unsigned long long* totals, unsigned long long* observed, hipStream_t s) {
     if (!na) return hipSuccess;
-    const LaunchCfg cfg = open_shape(cfg0, sa.n, na * (nshuf ? nshuf : 1), nshuf != 0);
+    const LaunchCfg cfg = nshuf ? open_shuffle_shape(cfg0, sa.n, na * nshuf) : open_shape(cfg0, sa.n, na);
     switch (cfg.qpl) {
         case 1: return launch_mc_q<1>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
         case 4: return launch_mc_q<4>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);

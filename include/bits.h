@@ -67,7 +67,7 @@ typedef enum bits_status {
 
 /* Search path selection for a call (bits_launch.path). */
 #define BITS_PATH_AUTO    0u      /* learned index if the reference has one, else the tiered search,
-                                     or the plain one up to 2^14 intervals
+                                     or the plain one up to 2^14 intervals (2^16 in bits_mc_pvalue)
                                      (the batch plan: all references learned, else as bits_batch_create says) */
 #define BITS_PATH_PLAIN   1u      /* LDS Eytzinger top tree + bisection in HBM */
 #define BITS_PATH_LEARNED 2u      /* learned CDF index + error-window search over the line heads (needs learned ref) */

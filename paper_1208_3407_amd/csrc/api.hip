@@ -393,6 +393,7 @@ int mc_pvalue_impl(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
     rc = resolve_launch(ref, launch, &cfg);
     if (rc != BITS_OK) return rc;
     if (launch && launch->path == BITS_PATH_TIERED) return BITS_E_ARG;   // a counting-only path
+    if (cfg.path == BITS_PATH_TIERED && ref->n <= kPlainShuffleKeys) cfg.path = BITS_PATH_PLAIN;
     hipStream_t s = (hipStream_t)stream;
     auto* totals = (unsigned long long*)d_totals;
     auto* obs = (unsigned long long*)d_observed;

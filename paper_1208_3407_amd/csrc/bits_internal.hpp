@@ -131,11 +131,16 @@ __host__ __device__ constexpr size_t search_lds_bytes(bool learned, uint32_t dep
 // 208 and 29, 30, 30, 29).
 // AUTO takes the plain path up to kPlainKeys: the LDS tree then resolves all but
 // a step or two (1.5e7 queries against 1e3 keys 81 us, 206 with windows; 8e3
-// 155, 223; 1.6e4 205, 236; 6.4e4 455, 271).  Counting through the models takes
+// 155, 223; 1.6e4 205, 236; 6.4e4 455, 271); in query-ordered shuffles, which
+// run over one part of the reference at a time and find it in the nearest
+// caches, up to kPlainShuffleKeys (1e5 x 100 against 1.7e4, 5e4, 7e4, 1e5 keys
+// 152, 164, 194, 265 us, with windows 234, 233, 232, 236; 1e6 x 30 against 7e4
+// and 1e5 473 and 698, 584 and 585).  Counting through the models takes
 // kModePaired up to kPairedKeys keys, kModeLearned above.
 enum : int { kModePlain = 0, kModeLearned = 1, kModeTiered = 2, kModeDirect = 3, kModePaired = 4 };
 __host__ __device__ constexpr bool learned_mode(int mode) { return mode == kModeLearned || mode == kModePaired; }
 constexpr uint32_t kPlainKeys = 1u << 14;
+constexpr uint32_t kPlainShuffleKeys = 1u << 16;
 constexpr uint32_t kPairedKeys = 1u << 15;
 constexpr uint32_t kDirectKeys = 1u << 19;
 constexpr uint32_t kDirectBucket = 128;

@@ -136,3 +136,15 @@ def test_batch_over_references_dense_in_one_place():
     assert ratio(lambda: bits.bits_batch_run(dense), lambda: bits.bits_batch_run(spread)) < 3
     for p in (dense, spread):
         bits.bits_batch_destroy(p)
+
+
+def test_shuffles_against_a_small_reference():
+    """Query-ordered shuffles against 3e4 keys without a model on the open path, against the bisection
+    (right 1.0, with windows 1.55)."""
+    lengths, A, B = datagen.w1_sets(seed=20, n_a=100_000, n_b=30_000)
+    ref, q = bits.bits_sort_ref(*project(lengths, B)), project(lengths, A)
+
+    def run(launch):
+        return lambda: bits.bits_mc_pvalue(ref, *q, lengths, 7, 0, 100, launch=launch)
+
+    assert ratio(run(None), run({"path": 1}), inner=2) < 1.25

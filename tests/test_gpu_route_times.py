@@ -148,3 +148,13 @@ def test_shuffles_against_a_small_reference():
         return lambda: bits.bits_mc_pvalue(ref, *q, lengths, 7, 0, 100, launch=launch)
 
     assert ratio(run(None), run({"path": 1}), inner=2) < 1.25
+
+
+def test_queries_outside_the_reference():
+    """Queries that lie before or after all of a reference's keys on the open path, against the bisection,
+    which finds the same few keys in the nearest cache (right 0.9, with windows read for all 2.1)."""
+    rng = np.random.default_rng(21)
+    s = np.sort(rng.integers(0, 2_900_000_000, 5_000_000))
+    b = np.full(1_000_000, 1_000_000_000)
+    ref, q = bits.bits_sort_ref(up(b), up(b + 200)), (up(s), up(s + 300))
+    assert ratio(count_into(ref, q), count_into(ref, q, {"path": 1})) < 1.4

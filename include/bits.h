@@ -207,7 +207,11 @@ int bits_ref_bytes(uint64_t n, uint32_t depth, int learned, size_t *bytes);
 int bits_ref_init(void *d_block, size_t block_bytes, uint64_t n, uint32_t depth, int learned,
                   bits_ref *ref);
 
-/* Workspace bytes bits_sort_ref needs for n intervals. */
+/* Workspace bytes of bits_sort_ref for n intervals: 4 bytes per key (two keys
+ * per interval) and 2 KB per tile of the sort (4096 to 12288 keys by their
+ * number; none up to 8192 intervals), and what training needs.  All calls that
+ * sort also accept a smaller one, down to 2 KB per 20480 keys (16384 with
+ * values along), and take larger tiles, at some cost in speed. */
 int bits_sort_ref_workspace(uint64_t n, size_t *bytes);
 
 /* Builds the reference index from B (Algorithm 2's setup): B_S and B_E are
@@ -217,7 +221,7 @@ int bits_sort_ref_workspace(uint64_t n, size_t *bytes);
  * and its per-leaf error windows measured.  Clears the status word (then
  * BITS_FLAG_SORT reports a sort that could not complete).
  *   d_b_start, d_b_end  device, ref->n each, unsorted (not modified)
- *   d_ws, ws_bytes      device workspace >= bits_sort_ref_workspace(n)
+ *   d_ws, ws_bytes      device workspace (bits_sort_ref_workspace(n))
  *   train               host, NULL for defaults (ignored if not learned)
  * The intervals' start <= end is not checked here (starts and ends are sorted
  * independently); count calls check their queries. */

@@ -233,9 +233,8 @@ int bits_sort_ref(const uint32_t* d_b_start, const uint32_t* d_b_end, const bits
                   size_t ws_bytes, const bits_train* train, void* stream) {
     if (!ref_ok(ref)) return BITS_E_ARG;
     if (ref->n && (!d_b_start || !d_b_end || !d_ws)) return BITS_E_ARG;
-    size_t need = 0;
-    bits_sort_ref_workspace(ref->n, &need);
-    if (ref->n && ws_bytes < need) return BITS_E_WORKSPACE;
+    const uint64_t ns[2] = {ref->n, ref->n};
+    if (ref->n && ws_bytes < std::max(sort_workspace_least(ns, 2), rmi_workspace_bytes())) return BITS_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     if (ref->n) {
         const SortSeg segs[2] = {{d_b_start, ref->bs, ref->n, 0u, nullptr, nullptr, ref->status, kStatusBytes / 4},
@@ -254,7 +253,7 @@ int bits_sort_refs(const uint32_t* const* d_b_start, const uint32_t* const* d_b_
                    uint32_t n_ref, void* d_ws, size_t ws_bytes, const bits_train* train, void* stream) {
     if (n_ref == 0) return BITS_OK;
     if (!d_b_start || !d_b_end || !refs || !d_ws) return BITS_E_ARG;
-    std::vector<uint64_t> ns(n_ref);
+    std::vector<uint64_t> ns(2 * (size_t)n_ref);
     std::vector<SortSeg> segs;
     std::vector<FinishRef> fin;
     segs.reserve(2 * (size_t)n_ref);
@@ -262,14 +261,12 @@ int bits_sort_refs(const uint32_t* const* d_b_start, const uint32_t* const* d_b_
     for (uint32_t j = 0; j < n_ref; ++j) {
         if (!ref_ok(&refs[j])) return BITS_E_ARG;
         if (refs[j].n && (!d_b_start[j] || !d_b_end[j])) return BITS_E_ARG;
-        ns[j] = refs[j].n;
+        ns[2 * j] = ns[2 * j + 1] = refs[j].n;
         segs.push_back({d_b_start[j], refs[j].bs, refs[j].n, 0u, nullptr, nullptr, refs[j].status, kStatusBytes / 4});
         segs.push_back({d_b_end[j], refs[j].be, refs[j].n, 0u, nullptr, nullptr, refs[j].status});
         fin.push_back(finish_of(&refs[j]));
     }
-    size_t need = 0;
-    bits_sort_refs_workspace(ns.data(), n_ref, &need);
-    if (ws_bytes < need) return BITS_E_WORKSPACE;
+    if (ws_bytes < std::max(sort_workspace_least(ns.data(), 2 * n_ref), rmi_workspace_bytes())) return BITS_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     int rc = launch_sort(segs.data(), (uint32_t)segs.size(), d_ws, ws_bytes, s);
     if (rc != BITS_OK) return rc;
@@ -684,9 +681,8 @@ int bits_enum_index_build(const uint32_t* d_b_start, const uint32_t* d_b_end, ui
     const EnumLayout L = enum_layout(n);
     if (index_bytes < L.total) return BITS_E_WORKSPACE;
     if (!n) return BITS_OK;
-    size_t need = 0;
-    bits_enum_index_workspace(n, &need);
-    if (ws_bytes < need) return BITS_E_WORKSPACE;
+    const uint32_t vm = 2;
+    if (ws_bytes < sort_workspace_least(&n, 1, &vm)) return BITS_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char* b = (char*)d_index;
     uint32_t* starts = (uint32_t*)(b + L.starts);
@@ -763,7 +759,7 @@ int bits_enumerate(const void* d_index, uint64_t n, const uint32_t* d_a_start, c
 
 namespace {
 struct ResortWs {
-    size_t tab, status, s_in, e_in, s_out, e_out, sort, total;
+    size_t tab, status, s_in, e_in, s_out, e_out, sort, total, least;
     uint64_t stride;   // words from one round's keys to the next: whole 128-byte lines
 };
 ResortWs resort_ws(uint64_t nb, uint32_t batch) {
@@ -780,8 +776,8 @@ ResortWs resort_ws(uint64_t nb, uint32_t batch) {
     W.e_out = o; o += keys;
     W.sort = o;
     std::vector<uint64_t> ns(2 * (size_t)batch, nb);
-    o += align256(sort_workspace_bytes(ns.data(), 2 * batch));
-    W.total = o;
+    W.total = W.sort + align256(sort_workspace_bytes(ns.data(), 2 * batch));
+    W.least = W.sort + align256(sort_workspace_least(ns.data(), 2 * batch));
     return W;
 }
 }  // namespace
@@ -806,7 +802,7 @@ int bits_mc_resort(const uint32_t* d_a_start, const uint32_t* d_a_end, uint64_t 
     for (uint32_t c = 0; c < n_chrom; ++c) g += chrom_len[c];
     if (g > 0xFFFFFFFFull) return BITS_E_CHROM;
     const ResortWs W = resort_ws(nb, batch);
-    if (nb && (!d_ws || ws_bytes < W.total || ((uintptr_t)d_ws & 255u))) return BITS_E_WORKSPACE;
+    if (nb && (!d_ws || ws_bytes < W.least || ((uintptr_t)d_ws & 255u))) return BITS_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     auto* totals = (unsigned long long*)d_totals;
     auto* obs = (unsigned long long*)d_observed;
@@ -826,7 +822,7 @@ int bits_mc_resort(const uint32_t* d_a_start, const uint32_t* d_a_end, uint64_t 
         uint32_t* S_out = (uint32_t*)(w + W.s_out);
         uint32_t* E_out = (uint32_t*)(w + W.e_out);
         void* sort_ws = w + W.sort;
-        const size_t sort_bytes = W.total - W.sort;
+        const size_t sort_bytes = ws_bytes - W.sort;
         // B's per-interval table (chromosome offset, legal starts, length, index), computed once
         uint32_t* status = d_status ? d_status : (uint32_t*)(w + W.status);
         BITS_CHECK_HIP(launch_mc_zero(totals, ns, obs, &tab, s));

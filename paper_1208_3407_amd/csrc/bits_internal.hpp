@@ -359,7 +359,10 @@ struct SortSeg {
     uint32_t* status = nullptr;
     uint32_t clear = 0;
 };
+// The workspace for the tile these segments want, and the least one launch_sort
+// accepts for them (larger tiles).
 size_t sort_workspace_bytes(const uint64_t* n, uint32_t nseg, const uint32_t* vmode = nullptr);
+size_t sort_workspace_least(const uint64_t* n, uint32_t nseg, const uint32_t* vmode = nullptr);
 int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, hipStream_t s);
 // Trees, line tails and (heads != nullptr) line heads of sorted references.
 struct FinishRef {

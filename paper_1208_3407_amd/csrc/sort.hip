@@ -40,8 +40,8 @@ constexpr int kSweepWaves = kSweepThreads / kWave;
 // 7 rounds (2e6 keys: 166 us at 4 rounds, 150 at 7, 159 at 16; 1e7: 677, 540,
 // 543) until the look-back steps of many tiles cost more (2e7: 1121 at 7, 1040
 // at 16).
-constexpr int kRoundsKeys[2] = {4, 12};
-constexpr uint64_t kWantKeys[2] = {0, 110};
+constexpr int kRoundsKeys[3] = {4, 12, 20};
+constexpr uint64_t kWantKeys[3] = {0, 110, ~0ull};   // 20 only where the workspace holds no smaller tiles' words
 constexpr int kRoundsVals[3] = {4, 7, 16};
 constexpr uint64_t kWantVals[3] = {0, 200, 730};
 // A segment sorted by one workgroup.  At 16 rounds that takes longer (index of
@@ -72,7 +72,6 @@ struct SegDesc {
                       // set if pass q moves keys (digit q takes two or more values in the segment)
     uint32_t* status; // gets BITS_FLAG_SORT if a tile gave up its look-back walk (nullable)
 };
-static_assert(kRoundsKeys[0] == kRoundsVals[0], "smallest tile");
 static_assert(sizeof(SegDesc) == 72, "SegDesc layout");
 
 struct SortPlan {
@@ -513,9 +512,10 @@ struct WsLayout {
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The tile a sort takes, from its segments' sizes.
+constexpr int kShapes = 3;
 struct SortShape {
     bool vals, lone;   // lone: every segment fits one workgroup
-    int rounds;
+    int k, rounds;
     uint64_t ntiles;
 };
 
@@ -526,8 +526,9 @@ static uint64_t tiles_at(const uint64_t* n, uint32_t nseg, int rounds) {
     return t;
 }
 
-static SortShape sort_shape(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
-    SortShape S{false, true, 0, 0};
+// Tile k of the list that fits the segments; k < 0: the one wanted for their sizes.
+static SortShape sort_shape(const uint64_t* n, uint32_t nseg, const uint32_t* vmode, int k = -1) {
+    SortShape S{false, true, 0, 0, 0};
     uint64_t most = 0;
     for (uint32_t s = 0; s < nseg; ++s) {
         S.vals |= vmode && vmode[s];
@@ -536,16 +537,18 @@ static SortShape sort_shape(const uint64_t* n, uint32_t nseg, const uint32_t* vm
     S.lone = most <= kLoneTile;
     const int* R = S.vals ? kRoundsVals : kRoundsKeys;
     const uint64_t* want = S.vals ? kWantVals : kWantKeys;
-    int k = S.vals ? 2 : 1;
-    while (k > 0 && tiles_at(n, nseg, R[k]) < want[k]) --k;
+    if (k < 0) {
+        k = kShapes - 1;
+        while (k > 0 && tiles_at(n, nseg, R[k]) < want[k]) --k;
+    }
+    S.k = k;
     S.rounds = R[k];
     if (S.lone) S.rounds = most <= 4u * kSweepThreads ? 4 : 8;
     S.ntiles = tiles_at(n, nseg, S.rounds);
     return S;
 }
 
-static WsLayout ws_layout(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
-    const SortShape S = sort_shape(n, nseg, vmode);
+static WsLayout ws_layout(const uint64_t* n, uint32_t nseg, const uint32_t* vmode, const SortShape& S) {
     uint64_t nkeys = 0, nvals = 0;
     for (uint32_t s = 0; s < nseg; ++s) {
         nkeys += n[s];
@@ -556,8 +559,7 @@ static WsLayout ws_layout(const uint64_t* n, uint32_t nseg, const uint32_t* vmod
     // cleared by the first launch: [plan, zero_end)
     L.plan = o; o = align256(o + sizeof(SortPlan));
     L.seg_hist = o; o = align256(o + (S.lone ? 0 : (size_t)nseg * 1024 * 4));
-    // room for the smallest tiles, so that fewer segments of the same sizes never need more
-    L.lb = o; o = align256(o + (S.lone ? 0 : (size_t)tiles_at(n, nseg, kRoundsKeys[0]) * 256 * 8));
+    L.lb = o; o = align256(o + (S.lone ? 0 : (size_t)S.ntiles * 256 * 8));
     L.zero_end = S.lone ? L.lb : L.lb + (size_t)S.ntiles * 256 * 8;
     L.descs = o; o = align256(o + sizeof(SegDesc) * nseg);
     L.ping = o; o = align256(o + (S.lone ? 0 : (size_t)nkeys * 4));
@@ -566,10 +568,23 @@ static WsLayout ws_layout(const uint64_t* n, uint32_t nseg, const uint32_t* vmod
     return L;
 }
 
+// The tile wanted for the segments, or the next larger one whose look-back
+// words the workspace holds: a caller may have sized it for other segments, or
+// for larger tiles (20 rounds of keys: an index of 5e7 1738 us, 1446 at 12).
+static SortShape sort_shape_in(const uint64_t* n, uint32_t nseg, const uint32_t* vmode, size_t ws_bytes) {
+    SortShape S = sort_shape(n, nseg, vmode);
+    while (S.k + 1 < kShapes && ws_layout(n, nseg, vmode, S).total > ws_bytes) S = sort_shape(n, nseg, vmode, S.k + 1);
+    return S;
+}
+
 }  // namespace
 
 size_t sort_workspace_bytes(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
-    return ws_layout(n, nseg, vmode).total;
+    return ws_layout(n, nseg, vmode, sort_shape(n, nseg, vmode)).total;
+}
+
+size_t sort_workspace_least(const uint64_t* n, uint32_t nseg, const uint32_t* vmode) {
+    return ws_layout(n, nseg, vmode, sort_shape(n, nseg, vmode, kShapes - 1)).total;
 }
 
 template <bool VALS, int ROUNDS>
@@ -589,8 +604,8 @@ int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, h
         ns[i] = segs[i].n;
         vm[i] = segs[i].vmode;
     }
-    const WsLayout L = ws_layout(ns.data(), nseg, vm.data());
-    const SortShape S = sort_shape(ns.data(), nseg, vm.data());
+    const SortShape S = sort_shape_in(ns.data(), nseg, vm.data(), ws_bytes);
+    const WsLayout L = ws_layout(ns.data(), nseg, vm.data(), S);
     const uint32_t tile = (uint32_t)S.rounds * kSweepThreads;
     if (ws_bytes < L.total) return BITS_E_WORKSPACE;
     char* base = (char*)ws;
@@ -658,7 +673,8 @@ int launch_sort(const SortSeg* segs, uint32_t nseg, void* ws, size_t ws_bytes, h
         else launch_passes<true, kRoundsVals[2]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
     } else {
         if (S.rounds == kRoundsKeys[0]) launch_passes<false, kRoundsKeys[0]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
-        else launch_passes<false, kRoundsKeys[1]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
+        else if (S.rounds == kRoundsKeys[1]) launch_passes<false, kRoundsKeys[1]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
+        else launch_passes<false, kRoundsKeys[2]>(descs, nseg, plan, lb, ntiles, seg_hist, s);
     }
     BITS_CHECK_HIP(hipGetLastError());
     return BITS_OK;

@@ -2094,8 +2094,10 @@ static hipError_t launch_count_q(const SearchArgs& sa, const LaunchCfg& cfg, con
 }
 
 // The shape of a search when the caller left it open.  Without a model: one
-// query per lane, and the largest workgroup that still gives every CU one
-// (each stages its own copy of the top trees).  With one: small workgroups,
+// query per lane, and the largest workgroup that still gives every CU (of a
+// given number of workgroups, half of them) one
+// (each stages its own copy of the top trees; 1e5 queries by one workgroup of
+// 256 threads 1840 us, of 1024 840).  With one: small workgroups,
 // which stage nothing and finish apart, and one query per lane (1024 threads
 // lowered to what the LDS scratch of two queries per lane allows, before:
 // counting 1e4 queries in 1e4 23.6 -> 14.3 us, 1e5 in 5e6 34.0 -> 17.5, 5e7 in
@@ -2109,7 +2111,7 @@ static LaunchCfg open_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na) {
         c.block = 256u;
     }
     if (c.path != BITS_PATH_TIERED) return c;
-    const uint64_t cus = (uint64_t)device_cu_count();
+    const uint64_t cus = c.grid ? c.grid / 2 : (uint64_t)device_cu_count();
     c.qpl = 1;
     c.block = na >= 1024 * cus ? 1024u : na >= 512 * cus ? 512u : 256u;
     return c;

@@ -158,3 +158,11 @@ def test_queries_outside_the_reference():
     b = np.full(1_000_000, 1_000_000_000)
     ref, q = bits.bits_sort_ref(up(b), up(b + 200)), (up(s), up(s + 300))
     assert ratio(count_into(ref, q), count_into(ref, q, {"path": 1})) < 1.4
+
+
+def test_count_with_one_workgroup():
+    """The open search by one workgroup against the default shape spelled out (right 1.0, with a workgroup of
+    256 threads 2.2)."""
+    lengths, A, B = datagen.w1_sets(seed=22, n_a=100_000, n_b=1_000_000)
+    ref, q = bits.bits_sort_ref(*project(lengths, B)), project(lengths, A)
+    assert ratio(count_into(ref, q, {"grid": 1}), count_into(ref, q, {"grid": 1, "block": 1024, "qpl": 2}), inner=1) < 1.2

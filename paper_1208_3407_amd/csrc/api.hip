@@ -534,7 +534,7 @@ bool bin_ws_layout(uint64_t na, uint64_t n, const uint32_t* chrom_len, uint32_t 
     o += 4 * align256((size_t)na * sizeof(uint32_t)) + 2 * align256(BITS_MAX_CHROM * sizeof(uint32_t));
     W->rs = o; o = align256(o + nc * sizeof(uint32_t));
     W->re = o; o = align256(o + nc * sizeof(uint32_t));
-    // 12 bytes per cell of which one word is used: the size stays what the header
+    // 12 bytes per cell of which four words are used: the size stays what the header
     // states and callers may have laid out
     W->nreg = o;
     o = align256(o + nc * sizeof(uint32_t));
@@ -618,7 +618,7 @@ int bits_mc_binned(const bits_ref* ref, const uint32_t* d_a_start, const uint32_
         BITS_CHECK_HIP(launch_mc(make_search_args(ref, cfg), cfg, d_a_start, d_a_end, tab, na, seed, s0, 0, totals,
                                  obs, s));
         if (W.L.ncells && ns)   // a genome of length 0 holds no legal placement
-            BITS_CHECK_HIP(launch_bin_regions(chrom_len, n_chrom, ref->bs, ref->be, ref->n, bw, ref->status, s));
+            BITS_CHECK_HIP(launch_bin_regions(chrom_len, n_chrom, tab, na, ref->bs, ref->be, ref->n, bw, ref->status, s));
         BinTiming& tm = bin_timing();
         std::unique_lock<std::mutex> tl(tm.mu);
         tm.used = 0;

@@ -178,12 +178,24 @@ __device__ uint32_t block_scan_u32(uint32_t* h, uint32_t m, uint32_t* wsum) {
     return tot;
 }
 
+// A (shuffle, chromosome)'s work in 256 entries, counting what it takes besides
+// them: about 1.8 us with none, 3.9 with 830, 6.9 with 4200, 0.9 ns for each
+// further one.
+__host__ __device__ __forceinline__ uint32_t group_cost(uint32_t h) {
+    const uint32_t more = h >> 6;
+    return (h >> 8) + 8u + (more < 24u ? more : 24u);
+}
+
+// What a chromosome may cost while every workgroup takes the same number of shuffles.
+uint32_t bin_most(uint64_t na, uint32_t n_chrom) { return 2u * group_cost((uint32_t)(na / n_chrom)); }
+
 // Ranks of every cell's first coordinate in B_S and B_E, both bisections in
 // step so that their dependent loads overlap.
 __global__ void __launch_bounds__(256) k_bin_cells(BinGeom g, const uint32_t* __restrict__ bs,
                                                    const uint32_t* __restrict__ be, uint32_t n,
-                                                   uint32_t* __restrict__ rs, uint32_t* __restrict__ re) {
+                                                   uint32_t* __restrict__ rs, uint32_t* __restrict__ re, uint64_t* nreg) {
     const uint32_t ncells = g.cb[g.n_chrom];
+    if (blockIdx.x == 0 && threadIdx.x == 0) nreg[1] = 0ull;
     for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < ncells; c += gridDim.x * blockDim.x) {
         const uint32_t k = chrom_of_cell(g, c);
         const uint32_t lo = g.off[k] + ((c - g.cb[k]) << g.shift);
@@ -206,17 +218,20 @@ __global__ void __launch_bounds__(256) k_bin_cells(BinGeom g, const uint32_t* __
 // numbers from sum over k' < k of bound(k') on, bound = min(cells, keys /
 // kRegionKeys + 1) being the most it can have, so that no scan over
 // chromosomes is needed; the numbers it leaves unused are empty regions at its
-// end.  Writes cell -> region, the descriptors, and with the last chromosome
-// the sentinel {genome size, n, n} and the number of regions.
+// end.  Writes cell -> region, the descriptors, with the last chromosome
+// the sentinel {genome size, n, n} and the number of regions, and in nreg[1]
+// whether a chromosome's queries cost more than `heavy`.
 __global__ void __launch_bounds__(kBinThreads) k_bin_regions(BinGeom g, const uint32_t* __restrict__ rs,
                                                              const uint32_t* __restrict__ re, uint32_t n,
                                                              uint32_t nreg_max, uint32_t* __restrict__ cell_region,
                                                              RegionDesc* __restrict__ desc, uint64_t* nreg,
+                                                             const uint32_t* __restrict__ hist, uint32_t heavy,
                                                              uint32_t* status) {
     constexpr uint32_t kPer = kMaxCells / kBinThreads, kWaves = kBinThreads / kWave;
     __shared__ uint32_t found[kPer * kWaves], wsum[kWaves], sh_total;
     const uint32_t k = blockIdx.x, c0 = g.cb[k], nc = g.cb[k + 1] - c0, ncells = g.cb[g.n_chrom];
     if (nc == 0) return;
+    if (threadIdx.x == 0 && group_cost(hist[k]) > heavy) atomicOr((unsigned long long*)&nreg[1], 1ull);
     const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     auto merged = [&](uint32_t c) -> uint64_t { return c < ncells ? (uint64_t)rs[c] + re[c] : 2ull * n; };
     auto bound = [&](uint32_t q) -> uint32_t {
@@ -367,35 +382,38 @@ __device__ __forceinline__ uint32_t half16(const uint32_t* w, uint32_t j) {
 // several shuffles (1e5 entries in 24 chromosomes x 2000 shuffles: 800 -> 648 us;
 // 2000 x 100: 21.3 -> 18.9 us): as many as place_share gives it.
 
-// A (shuffle, chromosome)'s work in entries, counting what it takes besides
-// them: about 1.8 us with none, 3.9 with 830, 6.9 with 4200, 0.9 ns for each
-// further one.  Concave, so no spread of the entries over the chromosomes makes
-// the sum larger than the even one does.
-__host__ __device__ __forceinline__ float group_cost(float h) {
-    const float more = 4.0f * h;
-    return h + 2048.0f + (more < 6144.0f ? more : 6144.0f);
-}
-
 // The chromosome and the shuffles [s0, s1) of workgroup b when workgroups take
-// several: chromosome k has group_cost(hist[k]) inv workgroups, rounded, at
-// least 1 and at most nb, which split the shuffles evenly, so that a workgroup's
-// work does not depend on how the queries lie over the chromosomes (1e5
-// queries x 1000 shuffles on 24 of 256 chromosomes, 65 shuffles for each
-// workgroup: 5140 us; 1310 so, 2250 with one).  False past the last share.  All lanes call it.
-__device__ __forceinline__ bool place_share(const BinGeom& g, const uint32_t* __restrict__ hist, uint32_t nb, float inv,
+// several and a chromosome costs more than bin_most: of n_chrom * wgs workgroups
+// each chromosome has its part by group_cost (rounded, at least 1 and at most
+// nb), which split the shuffles evenly, so that a workgroup's work does not
+// depend on how the queries lie over the chromosomes (1e6 queries x 100 shuffles
+// on one of 256 chromosomes: 13370 us with as many shuffles for every
+// workgroup, 1960 so, 2210 with one; 1e5 x 1000 on 24 of 256: 5140, 1330,
+// 2250).  Sets spread more evenly keep the same number for all: to find the
+// shares costs every workgroup a microsecond (3e4 x 2000: 720 and 755 us).
+// There are less than n_chrom more of them; false past the last.  All lanes call it.
+__device__ __forceinline__ bool place_share(const uint32_t* __restrict__ hist, uint32_t n_chrom, uint32_t nb, uint32_t wgs,
                                             uint32_t b, uint32_t& k, uint32_t& s0, uint32_t& s1) {
+    constexpr uint32_t kPer = BITS_MAX_CHROM / kWave;
     const uint32_t lane = threadIdx.x & (kWave - 1);
+    uint32_t cost[kPer], sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        const uint32_t c = j * kWave + lane;
+        cost[j] = c < n_chrom ? group_cost(hist[c]) : 0u;
+        sum += cost[j];
+    }
+    const float inv = (float)(n_chrom * wgs) / (float)lane_value(wave_inclusive_scan<uint32_t>(sum), kWave - 1);
     uint32_t before = 0;
-    for (uint32_t j = 0; j < g.n_chrom; j += kWave) {
-        const uint32_t c = j + lane;
-        const uint32_t h = hist[min(c, g.n_chrom - 1u)];
-        const uint32_t v = c < g.n_chrom ? min(nb, max(1u, (uint32_t)(group_cost((float)h) * inv + 0.5f))) : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        const uint32_t v = cost[j] ? min(nb, max(1u, (uint32_t)((float)cost[j] * inv + 0.5f))) : 0u;
         const uint32_t x = wave_inclusive_scan<uint32_t>(v);
         const uint64_t past = __ballot(before + x > b);
         if (past) {
             const uint32_t l = (uint32_t)__builtin_ctzll(past), n = lane_value(v, l);
             const uint32_t i = b - (before + lane_value(x, l) - n);
-            k = j + l;
+            k = j * kWave + l;
             s0 = nb * i / n;
             s1 = nb * (i + 1u) / n;
             return true;
@@ -408,7 +426,7 @@ __device__ __forceinline__ bool place_share(const BinGeom& g, const uint32_t* __
 template <bool MANY>
 __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     BinGeom g, const uint2* __restrict__ packed, const uint32_t* __restrict__ hist, const uint32_t* __restrict__ cursor,
-    uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, float inv, const uint32_t* __restrict__ cell_region,
+    uint64_t na, uint64_t seed, uint64_t sb, uint32_t nb, uint32_t per, const uint32_t* __restrict__ cell_region,
     const uint64_t* __restrict__ nreg_p, uint32_t nreg_max, uint32_t* __restrict__ seg_start,
     uint32_t* __restrict__ seg_cnt, uint2* __restrict__ recs) {
     constexpr int kChunkPer = MANY ? 6 : 10;   // a chunk's entries per thread
@@ -421,8 +439,15 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_bin_place(
     __shared__ uint2 stage[kStageRecs];             // the chunk's records in region order; h of the direct path
     __shared__ uint32_t wsum[kBinThreads / kWave];
     __shared__ uint32_t staged_total;
-    uint32_t k = blockIdx.x / nb, s0 = blockIdx.x - k * nb, s1 = s0 + 1u;
-    if (MANY && !place_share(g, hist, nb, inv, blockIdx.x, k, s0, s1)) return;
+    const uint32_t wgs = MANY ? (nb + per - 1u) / per : nb;
+    uint32_t k = blockIdx.x / wgs, s0 = (blockIdx.x - k * wgs) * (MANY ? per : 1u), s1 = MANY ? min(nb, s0 + per) : s0 + 1u;
+    if (MANY) {
+        if (nreg_p[1]) {
+            if (!place_share(hist, g.n_chrom, nb, wgs, blockIdx.x, k, s0, s1)) return;
+        } else if (k >= g.n_chrom) {
+            return;
+        }
+    }
     const uint32_t c0 = g.cb[k], nc = g.cb[k + 1] - c0;
     if (nc == 0) return;
     const uint32_t nreg = (uint32_t)*nreg_p;
@@ -989,16 +1014,16 @@ bool bin_layout(const uint32_t* chrom_len, uint32_t n_chrom, uint64_t n, BinLayo
     return true;
 }
 
-hipError_t launch_bin_regions(const uint32_t* chrom_len, uint32_t n_chrom, const uint32_t* bs, const uint32_t* be,
+hipError_t launch_bin_regions(const uint32_t* chrom_len, uint32_t n_chrom, const McTable& tab, uint64_t na, const uint32_t* bs, const uint32_t* be,
                               uint32_t n, const BinWs& w, uint32_t* status, hipStream_t s) {
     BinGeom g;
     if (!bin_geometry(chrom_len, n_chrom, &g)) return hipErrorInvalidValue;
     const uint32_t ncells = g.cb[n_chrom];
     if (!ncells || !n) return hipErrorInvalidValue;
     const uint32_t gr = (uint32_t)std::min<uint64_t>((ncells + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_bin_cells, dim3(gr), dim3(256), 0, s, g, bs, be, n, w.rs, w.re);
+    hipLaunchKernelGGL(k_bin_cells, dim3(gr), dim3(256), 0, s, g, bs, be, n, w.rs, w.re, w.nreg);
     hipLaunchKernelGGL(k_bin_regions, dim3(n_chrom), dim3(kBinThreads), 0, s, g, w.rs, w.re, n, w.nreg_max,
-                       w.cell_region, reinterpret_cast<RegionDesc*>(w.desc), w.nreg, status);
+                       w.cell_region, reinterpret_cast<RegionDesc*>(w.desc), w.nreg, tab.hist, bin_most(na, n_chrom), status);
     return hipGetLastError();
 }
 
@@ -1022,14 +1047,10 @@ hipError_t launch_bin_batch(const uint32_t* chrom_len, uint32_t n_chrom, const M
     const uint64_t rounds = std::min<uint64_t>(std::max<uint64_t>(mean / 512, few), 6);
     const uint64_t slots = 2u * rounds * (uint64_t)device_cu_count();
     const uint32_t per = mean > kGroupRecs ? 1u : (uint32_t)std::min<uint64_t>((groups + slots - 1) / slots, nb);
-    // The chromosomes' shares: (nb + per - 1) / per workgroups for one of mean size; all
-    // together at most as many for each, and one for the rounding.
-    const uint64_t wgs = (nb + per - 1) / per;
-    const float inv = (float)wgs / group_cost((float)na / (float)n_chrom);
-    const uint64_t most = (uint64_t)(1.001 * (double)(n_chrom * wgs)) + n_chrom + 1;
+    const uint64_t wgs = n_chrom * ((nb + per - 1ull) / per);
     const auto place = per == 1 ? k_bin_place<false> : k_bin_place<true>;
-    hipLaunchKernelGGL(place, dim3((uint32_t)(per == 1 ? groups : std::min(most, groups))), dim3(kBinThreads), 0, s, g,
-                       reinterpret_cast<const uint2*>(w.packed), tab.hist, tab.cursor, na, seed, sb, nb, inv,
+    hipLaunchKernelGGL(place, dim3((uint32_t)(per == 1 ? wgs : wgs + n_chrom)), dim3(kBinThreads), 0, s, g,
+                       reinterpret_cast<const uint2*>(w.packed), tab.hist, tab.cursor, na, seed, sb, nb, per,
                        w.cell_region, w.nreg, w.nreg_max, w.seg_start, w.seg_cnt, reinterpret_cast<uint2*>(w.recs));
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
     if (w.splits > 1)

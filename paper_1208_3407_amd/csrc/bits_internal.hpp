@@ -277,7 +277,7 @@ struct BinLayout {
 bool bin_layout(const uint32_t* chrom_len, uint32_t n_chrom, uint64_t n, BinLayout* L);
 struct BinWs {                    // device buffers, carved from the caller's workspace
     uint32_t *rs, *re;            // [ncells]
-    uint64_t* nreg;               // number of regions
+    uint64_t* nreg;               // [2]: number of regions, whether a chromosome is heavy
     uint32_t* cell_region;        // [ncells]
     void* desc;                   // [nreg_max + 1] region descriptors (16 bytes)
     uint32_t *seg_start, *seg_cnt;    // [batch][nreg_max]
@@ -286,7 +286,7 @@ struct BinWs {                    // device buffers, carved from the caller's wo
     void* packed;                     // [na] {input index, length or 0}
     uint32_t nreg_max, splits;
 };
-hipError_t launch_bin_regions(const uint32_t* chrom_len, uint32_t n_chrom, const uint32_t* bs, const uint32_t* be,
+hipError_t launch_bin_regions(const uint32_t* chrom_len, uint32_t n_chrom, const McTable& tab, uint64_t na, const uint32_t* bs, const uint32_t* be,
                               uint32_t n, const BinWs& w, uint32_t* status, hipStream_t s);
 // Shuffles [sb, sb + nb) (absolute indices); totals points at shuffle sb's slot.
 hipError_t launch_bin_batch(const uint32_t* chrom_len, uint32_t n_chrom, const McTable& tab, uint64_t na,

@@ -1039,9 +1039,9 @@ hipError_t launch_bin_batch(const uint32_t* chrom_len, uint32_t n_chrom, const M
     // Shuffles per workgroup: groups of more than kGroupRecs entries take long enough
     // by themselves; of the others, as many as leave `rounds` workgroups for each of the
     // two slots a CU has: one when a workgroup's few shuffles are mostly latency, two when
-    // they are many (the shares do not fill one round evenly: 2e4 entries x 1000 223 us of
-    // placement at one round, 151 at two; 2000 x 100 19.8, 23.9), up to 6 so that
-    // the last round costs little (1e5 entries x 2000: 3, 6, 10 rounds 671, 648, 658 us).
+    // they are many (a few workgroups too many are a second round of them: 2e4 entries x
+    // 1000 184 us of placement at one round, 141 at two; 2000 x 100 18.6, 23.9), up to 6
+    // so that the last round costs little (1e5 entries x 2000: 3, 6, 10 rounds 671, 648, 658 us).
     const uint64_t groups = (uint64_t)n_chrom * nb, mean = na / n_chrom;
     const uint64_t few = groups < 32u * (uint64_t)device_cu_count() ? 1 : 2;
     const uint64_t rounds = std::min<uint64_t>(std::max<uint64_t>(mean / 512, few), 6);

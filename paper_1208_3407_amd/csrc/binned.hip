@@ -785,8 +785,8 @@ __device__ __forceinline__ void bin_count_region(const uint32_t* S, uint32_t ns,
         if (uniform(pre[mid]) <= p0) sc = mid; else hi = mid;
     }
     uint32_t end_c = uniform(pre[sc + 1]);   // the end of the counted step's shuffle
-    // the shuffle of the records being loaded, a step ahead, so that a wave has
-    // two record loads in flight
+    // the shuffle of the records being loaded, kAhead steps ahead, so that a wave has
+    // that many record loads in flight
     uint32_t sn = sc, end_n = end_c, base_n = uniform(base[sc]), lane_s = sc;
     auto load = [&](uint64_t b, uint32_t& of) {   // records [b, min(b + 64, p1)), b < p1
         const uint32_t e = (uint32_t)min(p1, b + kWave), p = (uint32_t)b + lane;

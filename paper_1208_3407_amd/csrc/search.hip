@@ -2117,17 +2117,18 @@ static LaunchCfg open_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na) {
     return c;
 }
 
-// The same for k_mc_sorted, na queries in all shuffles together.  A larger
-// workgroup sorts more placements at once, which pays when many of them search
-// a large reference (256, 512, 1024 threads: 1e6 x 200 against 5e7 keys 9730,
-// 9480, 9140 us, 1e6 x 50 2590, 2550, 2500; 1e6 x 10 798, 844, 925; 1e6 x 200
-// against 5e6 7320, 7370, 7250, against 1e6 6160, 6330, 6350; 1e5 x 100 against
-// 1e6 369, 374, 417).
-static LaunchCfg open_shuffle_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na) {
-    LaunchCfg c = open_shape(cfg, n, na);
+// The same for the shuffles.  A larger workgroup sorts more placements at once,
+// which pays when many of them, over items of many shuffles, search a large
+// reference (256, 512, 1024 threads: 1e6 x 200 against 5e7 keys 9730, 9480,
+// 9140 us, 1e6 x 50 2590, 2550, 2500, 1e6 x 10 798, 844, 925; 1e6 x 400
+// against 1e7 16000, 15650, 15270, 1e6 x 40 1729, 1716, 1734, 1e7 x 10 7200,
+// 7610, 8050; 1e6 x 160 against 5e6 5830, 5880, 5770, against 2e6 5290, 5400,
+// 5375; 1e5 x 100 against 1e6 369, 374, 417).
+static LaunchCfg open_shuffle_shape(const LaunchCfg& cfg, uint32_t n, uint64_t na, uint64_t nshuf) {
+    LaunchCfg c = open_shape(cfg, n, na * nshuf);
     if (c.open && c.path == BITS_PATH_LEARNED) {
         c.qpl = 1u;
-        c.block = n >= (1u << 24) && na >= (1u << 25) ? 1024u : 256u;
+        c.block = n >= (1u << 23) && nshuf >= kMaxChunk / 2 && na * nshuf >= (1u << 25) ? 1024u : 256u;
     }
     return c;
 }
@@ -2235,7 +2236,7 @@ hipError_t launch_mc(const SearchArgs& sa, const LaunchCfg& cfg0, const uint32_t
                      const McTable& tab, uint64_t na, uint64_t seed, uint64_t s0, uint64_t nshuf,
                      unsigned long long* totals, unsigned long long* observed, hipStream_t s) {
     if (!na) return hipSuccess;
-    const LaunchCfg cfg = nshuf ? open_shuffle_shape(cfg0, sa.n, na * nshuf) : open_shape(cfg0, sa.n, na);
+    const LaunchCfg cfg = nshuf ? open_shuffle_shape(cfg0, sa.n, na, nshuf) : open_shape(cfg0, sa.n, na);
     switch (cfg.qpl) {
         case 1: return launch_mc_q<1>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);
         case 4: return launch_mc_q<4>(sa, cfg, as, ae, tab, na, seed, s0, nshuf, totals, observed, s);

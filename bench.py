@@ -691,10 +691,10 @@ def main():
                      "peak_measured_copy": copy_gbs, "frac_of_measured": achieved / copy_gbs,
                      "compulsory_bytes_per_pass": compulsory,
                      "frac_compulsory_per_pass": compulsory / (pass_ms / 1e3) / 1e9 / HBM_PEAK_GBS,
-                     "limiter": ("VALU issue: the two bucket searches and the per-shuffle sums"
+                     "limiter": ("VALU issue and LDS reads together: the two bucket searches and the per-shuffle sums"
                                  if dom == "k_bin_search" else
                                  "VALU issue: two Philox draws per placement and the LDS ranking of each chunk; "
-                                 "the record writes are about 1.6x the design bytes (partly written lines)")},
+                                 "the record writes are about 1.3x the design bytes (partly written lines)")},
         "roofline_lds": {"bound": "lds", "kernel": "k_bin_search", "achieved": lds_ach, "peak": LDS_PEAK_GBS,
                          "unit": "GB/s", "frac": None if lds_ach is None else lds_ach / LDS_PEAK_GBS,
                          "launch_ms": launch_ms["k_bin_search"],

@@ -345,7 +345,7 @@ int bits_mc_binned_workspace(uint64_t na, uint64_t n, const uint32_t *chrom_len,
  *      in region order (8 bytes per placement into d_ws);
  *   2. search: one workgroup per region stages the region's slices of B_S
  *      and B_E in LDS and counts every placement of the pass that starts in
- *      the region by two bisections there (Algorithm 1); ends past the
+ *      the region by two searches there (Algorithm 1); ends past the
  *      region continue in HBM;
  *   3. the per-region sums are added to d_totals.
  * The total of each shuffle is a sum over its placements, so this order
@@ -481,7 +481,8 @@ typedef struct bits_batch_plan bits_batch_plan;   /* opaque host object */
  * reference and query tables, and the larger of the work list (16 bytes per
  * 256 queries and reference) and, from 2^22 queries x references on (up to
  * 192 sets and 2^26 queries), the sorted form's lists (about 44 bytes per
- * query plus 1 byte per query and 32 references). */
+ * query plus 1 byte per query and 32 references) and its partial sums (512
+ * bytes per query set and workgroup, at most 512 workgroups). */
 int bits_batch_workspace(const uint64_t *na, uint32_t n_q, uint32_t n_ref, size_t *bytes);
 
 /* Builds a plan that computes d_pair_totals[i * n_ref + j] = total count of
@@ -524,7 +525,10 @@ int bits_batch_destroy(bits_batch_plan *plan);
 /* Times bits_count on the given queries for every candidate launch shape
  * (block 256/512/1024, qpl 1/2/4, LDS depth 8..ref->depth, the given path)
  * with HIP events and writes the fastest to *best and its time to *best_ms.
- * `path` is BITS_PATH_PLAIN, BITS_PATH_LEARNED or BITS_PATH_TIERED.  Writes d_total. */
+ * `path` is BITS_PATH_PLAIN, BITS_PATH_LEARNED or BITS_PATH_TIERED.  *best is the
+ * fastest shape of that path; without a model, the tiered search, which BITS_PATH_AUTO
+ * takes above 2^14 intervals, may be faster than any shape of BITS_PATH_PLAIN.
+ * Writes d_total. */
 int bits_autotune_count(const bits_ref *ref, const uint32_t *d_a_start, const uint32_t *d_a_end,
                         uint64_t na, uint64_t *d_total, uint32_t path, bits_launch *best,
                         float *best_ms, void *stream);
@@ -533,7 +537,11 @@ int bits_autotune_count(const bits_ref *ref, const uint32_t *d_a_start, const ui
  * of the persistent kernel (block 256/512/1024, qpl 1/2/4, and on the plain
  * path LDS depth 8..max depth of the references), times its graph replay with
  * HIP events (one warm-up, best of three) and writes the fastest shape to
- * *best and its time to *best_ms.  Arguments as bits_batch_create; the
+ * *best and its time to *best_ms.  Only shapes of the path given are timed
+ * (BITS_PATH_PLAIN or BITS_PATH_LEARNED): *best names a path and a shape, so a
+ * plan made with it takes neither the windowed search nor the sorted form that
+ * bits_batch_create may take, and that may be faster, with the launch left
+ * open.  Arguments as bits_batch_create; the
  * caller may pass a sample of each query set (a prefix) to bound the tuning
  * time.  Writes d_pair_totals; waits on `stream`. */
 int bits_autotune_batch(const bits_ref *refs, uint32_t n_ref, const uint32_t *const *d_a_start,

@@ -620,7 +620,9 @@ def bits_batch_destroy(plan: BatchPlan):
 
 
 def bits_autotune_count(ref: Ref, a_start, a_end, path: int = BITS_PATH_PLAIN, stream=None):
-    """Fastest launch shape for bits_count on these queries (timed with HIP events)."""
+    """Fastest launch shape of this path for bits_count on these queries (timed with HIP
+    events).  Without a model the tiered path, which AUTO takes above 2^14 intervals, may
+    be faster than any shape of the plain one."""
     dev = _device()
     a_start, a_end = _u32_dev(a_start, "a_start"), _u32_dev(a_end, "a_end")
     total = torch.empty(1, dtype=torch.uint64, device=dev)
@@ -635,8 +637,9 @@ def bits_autotune_count(ref: Ref, a_start, a_end, path: int = BITS_PATH_PLAIN, s
 def bits_autotune_batch(refs: Sequence[Ref], queries: Sequence[Tuple[torch.Tensor, torch.Tensor]],
                         path: int = BITS_PATH_PLAIN, stream=None):
     """Fastest launch shape of the batch plan over these (query set, reference) pairs:
-    every candidate shape's graph replay timed with HIP events.  Pass a prefix of each
-    query set to bound the tuning time."""
+    every candidate shape of this path's graph replay timed with HIP events (a plan with the
+    launch left open may take a faster form that has no shape).  Pass a prefix of each query
+    set to bound the tuning time."""
     dev = _device()
     queries = [(_u32_dev(s, "a_start"), _u32_dev(e, "a_end")) for s, e in queries]
     nq, nr = len(queries), len(refs)

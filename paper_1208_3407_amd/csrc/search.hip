@@ -816,9 +816,9 @@ __device__ __forceinline__ void icount_heads(const SearchArgs& sa, uint32_t* scr
 // dens = the bucket's keys per coordinate.  Exact whatever the prediction
 // (window_search).  All 64 lanes call it.
 // Bound by random reads: one window of heads (L2) and one data line per
-// search.  1e7 queries against 1e7 (half clustered): 0.60 ms, against
+// search.  1e7 queries against 1e7 (half clustered): 0.55 ms, against
 // 3.85 ms for the bisection of the bucket in HBM and about 0.35 ms for the
-// data lines alone; 5e7 against 5e7: 4.0 against 18.5 ms.  A whole bisection
+// data lines alone; 5e7 against 5e7: 3.8 against 18.5 ms.  A whole bisection
 // of the heads costs one L2 request per step where the window costs two.
 template <int NC, bool DIRECT>
 __device__ __forceinline__ void rank_tiered(const Arrays& A, const uint32_t* tree0, const uint32_t* tree1, uint32_t d,
